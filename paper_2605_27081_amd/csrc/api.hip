@@ -2,6 +2,7 @@
 #include <stdarg.h>
 #include <string.h>
 
+#include <atomic>
 #include <mutex>
 #include <utility>
 #include <vector>
@@ -33,6 +34,23 @@ remoe_status check_hip(hipError_t e, const char *what)
 {
     if (e == hipSuccess) return REMOE_OK;
     return fail(REMOE_E_HIP, "%s: %s", what, hipGetErrorString(e));
+}
+
+constexpr int MAX_DEVICES = 64;
+
+remoe_status compute_units(int *out)
+{
+    static std::atomic<int> known[MAX_DEVICES];
+    int dev = -1;
+    REMOE_HIP_TRY(hipGetDevice(&dev));
+    if (dev < 0 || dev >= MAX_DEVICES) return fail(REMOE_E_UNSUPPORTED, "device ordinal %d outside 0..%d", dev, MAX_DEVICES - 1);
+    int n = known[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
+        REMOE_HIP_TRY(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev));
+        known[dev].store(n, std::memory_order_relaxed);
+    }
+    *out = n;
+    return REMOE_OK;
 }
 
 // ---- optional per-kernel timing (benchmarks only) --------------------------------------------
@@ -173,7 +191,6 @@ Workspace layout(const remoe_layer_desc *d, int64_t T, void *base_v)
 constexpr size_t DECODE_STATIC_BYTES = 4352 + (size_t)8 * 4 * (2048 + 8192) * 8;
 static __device__ __align__(256) unsigned char g_decode_scratch[DECODE_STATIC_BYTES];
 
-constexpr int MAX_DEVICES = 64;
 std::mutex g_scratch_mutex;
 void *g_decode_scratch_ptr[MAX_DEVICES] = {};
 

@@ -28,6 +28,9 @@ remoe_status check_hip(hipError_t e, const char *what);
         if (st__ != REMOE_OK) return st__;                             \
     } while (0)
 
+// Compute units of the current device (looked up once per device).
+remoe_status compute_units(int *out);
+
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 

@@ -32,6 +32,7 @@
 // logical tiles to its workgroups in arrival order, which keeps an expert's weights and the current
 // A rows hot in that XCD's L2.
 #include "common.h"
+#include "lds_copy.h"
 
 namespace remoe {
 
@@ -52,34 +53,6 @@ typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;   // four bf16 of 
 // a 128-byte period), and rows r, r+8 land in row slots of opposite parity, so 16 consecutive
 // lanes also cover a full 256-byte period.  The 8-lanes-per-row copies into LDS stay conflict-free.
 __device__ __forceinline__ int lds_slot(int r, int c) { return ((r ^ ((r >> 3) & 1)) << 3) + (c ^ (r & 7)); }
-
-// 64 lanes x 16 bytes, global -> LDS without passing through registers: lane l's 16 bytes, read from
-// base + off (wave-uniform 64-bit base, per-lane 32-bit byte offset), land at lds_base + 16 l
-// (lds_base wave-uniform, handed over in M0).  Written as assembly so that the compiler keeps no
-// books on these copies: its own bookkeeping makes every later LDS read wait for all of them,
-// which would undo the overlap.  Every wait for a copy in this file is therefore explicit.
-// The compiler pads its own instructions with the wait states the hardware asks for but does not
-// look inside an assembly block, so the block must not depend on any:
-//   * the address goes in as a per-lane 64-bit value in vector registers (the compiler's own add of
-//     base and offset in front of the block).  With the base in a scalar register pair the copy
-//     would read a scalar register as a memory address, and a scalar register that a vector
-//     instruction has just written (a spilled base restored with v_readlane) may not be used that
-//     way for five wait states: whether that happened would depend on register allocation;
-//   * M0 is written inside the block and the one wait state the copy needs behind that write is
-//     part of the block.  Nothing else in this kernel touches M0 (the compiler reserves it and has
-//     no use for it here; a host-side test of the generated code checks that).
-__device__ __forceinline__ void copy16_to_lds(const char *base, uint32_t off, const void *lds_base)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    const uint32_t dst = (uint32_t)(uintptr_t)lds_base;   // the low 32 bits of a generic LDS pointer are the LDS offset
-    const char *src = base + off;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(src) : "memory");
-#else
-    (void)base;
-    (void)off;
-    (void)lds_base;
-#endif
-}
 
 // Entry idx of a list that no kernel writes while this one runs (the tile list of the permute step),
 // fetched through the constant address space: a scalar load, which neither occupies the vector
@@ -605,9 +578,9 @@ remoe_status launch_grouped_gemm_bf16(int mode, const GroupedGemmArgs &g, hipStr
     if (!p.tile_ctr) return fail(REMOE_E_INVALID_ARG, "grouped_gemm_bf16 needs tile counters");
     // persistent launch: one workgroup per compute unit (a multiple of 8, one share per XCD), fewer
     // when the upper bound of tiles is smaller
-    int dev = 0, n_cu = 0;
-    REMOE_HIP_TRY(hipGetDevice(&dev));
-    REMOE_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
+    int n_cu = 0;
+    const remoe_status st_cu = compute_units(&n_cu);
+    if (st_cu != REMOE_OK) return st_cu;
     const int64_t nblk = (int64_t)g.max_tiles * ceil_div(g.n_out, bn);
     int64_t n_wg = ceil_div(nblk, 8) * 8;
     const int64_t resident = n_cu >= 8 ? (int64_t)(n_cu / 8) * 8 : 8;

@@ -1,8 +1,10 @@
-// Router kernel: fp32-accurate logits on the matrix cores, then a lane-per-token top-k and softmax.
+// Router kernel: fp32-accurate logits on the matrix cores, then the top-k and softmax in the same workgroup.
 //
 // Computes the paper's routing step (Sec. 3.1): P_t = Softmax(h_t^T theta_gate), E_t = Top-K(P_t).
-// One workgroup (4 wavefronts) owns 128 tokens and all N_r <= 128 experts, so every token's full
-// logit row ends in one workgroup: 32 tokens x (NT*32) experts per wavefront as NT accumulators.
+// One workgroup of 4 wavefronts owns a block of tokens and all N_r <= 128 experts.  The experts are cut
+// into NE tiles of 32 (NE = 1, 2 or 4); wavefront w computes expert tile w % NE for MT tiles of 32
+// tokens, the 4 / NE wavefronts of one expert tile taking different tokens, so a workgroup owns
+// 32 * MT * 4 / NE tokens and every token's full logit row ends in one workgroup.
 //
 // Logits.  The gate weights are fp32 and the logits must carry fp32 accuracy (near ties decide
 // which experts run).  For fp32 hidden states the products run on v_mfma_f32_32x32x2_f32.  For bf16
@@ -11,36 +13,38 @@
 // significand bits in all), so x*hi, x*mid and x*lo are exact fp32 products and three
 // v_mfma_f32_32x32x16_bf16 with fp32 accumulation replace sixteen fp32 MFMA steps.
 //
-// Top-k.  The logits are parked in LDS, one padded row per token.  Two neighbouring lanes share a
-// token, each scanning half of its experts in ascending id and keeping the 9 largest (K <= 8, plus
-// the runner-up for the margin) by insertion into a sorted register list; strict comparisons keep
-// the lower id first among equal logits.  The halves are merged through a lane swap, the softmax
-// denominator is summed the same way, and the pair writes ids and weights of its token.
+// Data path.  Slices of 32 k-values of the gate matrix and of the tokens move global -> LDS directly, in
+// full lines, into a ring of 3 or 4 stages (no staging registers, one barrier per slice).  A wavefront reads
+// its expert tile's fp32 weights and its token rows one slice ahead of the MFMAs and splits the weights in
+// registers.  What bounds it: the split, 44 vector instructions per 3 MT MFMAs, repeated by every workgroup.
+// (Loading each lane's weights straight into the operand registers needs no LDS for them, but the 64 lanes of
+// such a load touch 32 rows: 34 us against 27 us for 32 tokens, 112 against 101 us for 65,536.)  Before, the
+// split pieces went through LDS, between two barriers: 72 us and 113 us, with an insertion top-k by two
+// lanes per token.
+//
+// Top-k.  The logits are parked in LDS, one padded row per token.  Eight neighbouring lanes share a
+// token, each holding NE * 4 consecutive experts in registers.  K rounds (one more when the margin is
+// asked for) each take the maximum over the eight lanes and the lowest id that holds it, and strike
+// that id out; lane j keeps the winner of round j and writes it.
 #include "common.h"
+#include "lds_copy.h"
 
 namespace remoe {
 
 namespace {
 
-constexpr int RT_BM = 128;   // tokens per workgroup
-constexpr int RT_BK = 32;    // reduction slice per LDS stage (elements)
-constexpr int RT_LIST = 9;   // sorted candidates kept per lane: MAX top_k + 1
+constexpr int RT_BLOCK = 256;          // threads
+constexpr int RT_BK = 32;              // k-values per slice
+constexpr int RT_LANES = 8;            // lanes per token in the top-k
 
-// ---- fp32 path: LDS tiles hold rows of 32 floats = 8 chunks of 16 bytes; chunk c of row r lives in
-// row slot r ^ ((r >> 3) & 1) at chunk position c ^ (r & 7), so that the rows a wavefront reads at
-// once spread over all banks whether 8 or 16 lanes are served per cycle.
-__device__ __forceinline__ int swz_f32(int r, int c)
-{
-    return (r ^ ((r >> 3) & 1)) * RT_BK + ((c ^ (r & 7)) << 2);
-}
-
-// ---- bf16 path: rows of 32 bf16 = 4 chunks of 16 bytes; chunk c of row r sits at chunk position
-// c ^ ((r >> 2) & 3), which makes 16 consecutive rows of one logical chunk cover all 16 slots of a
-// 256-byte period.  Returns the offset in 16-byte units.
-__device__ __forceinline__ int swz_bf16(int r, int c) { return r * 4 + (c ^ ((r >> 2) & 3)); }
+// 128-byte rows (fp32 values) are 8 chunks of 16 bytes; chunk c of row r lives in row slot r ^ ((r >> 3) & 1)
+// at chunk position c ^ (r & 7): 16 consecutive rows of one logical chunk cover all banks once.
+__device__ __forceinline__ int slot_f32(int r, int c) { return ((r ^ ((r >> 3) & 1)) << 3) + (c ^ (r & 7)); }
+// 64-byte rows (bf16 tokens) are 4 chunks; chunk c of row r sits at chunk position c ^ ((r >> 2) & 3)
+__device__ __forceinline__ int slot_bf16(int r, int c) { return r * 4 + (c ^ ((r >> 2) & 3)); }
 
 // round-to-nearest-even bf16 pieces of two neighbouring fp32 weights: w = hi + mid + lo up to 2^-24
-// relative, each piece packed the way the LDS tiles hold it (first weight in the low half); three
+// relative, each piece packed the way the MFMA operand holds it (first weight in the low half); three
 // packed conversions (v_cvt_pk_bf16_f32) for the pair
 __device__ __forceinline__ void split3_pair(float w0, float w1, uint32_t &hi, uint32_t &mid, uint32_t &lo)
 {
@@ -51,322 +55,331 @@ __device__ __forceinline__ void split3_pair(float w0, float w1, uint32_t &hi, ui
     lo = pack_bf16x2(q0, q1);
 }
 
-// Logit rows in LDS: experts [0, NE/2) then 4 floats of padding, experts [NE/2, NE), 4 more.  With a
-// row stride of NE + 8 floats the 16-byte reads of 8 tokens x 2 halves fall into 16 different slots.
+// Logit rows in LDS.  The lanes of a token read 16-byte pieces of their own NE * 4 consecutive experts;
+// 4 floats of padding behind every 32 experts (and none behind a row of 32) spread the eight lanes of a
+// token and of its neighbours over the banks.
 template <int NE> struct LogitLayout {
-    static constexpr int HALF = NE / 2;
-    static constexpr int STRIDE = NE + 8;
-    __device__ static __forceinline__ int at(int row, int col) { return row * STRIDE + col + (col >= HALF ? 4 : 0); }
+    static constexpr int STRIDE = NE * 36 + (NE == 1 ? 0 : 4);
+    __device__ static __forceinline__ int at(int row, int col) { return row * STRIDE + col + 4 * (col >> 5); }
 };
 
-// ---- logits of fp32 hidden states: 2-stage LDS pipeline, v_mfma_f32_32x32x2_f32
-template <int NT>
-__device__ __forceinline__ void logits_f32(const float *__restrict__ x, int64_t t0, int64_t T, int H,
-                                           const float *__restrict__ wr, int N, float *smem,
-                                           floatx16_t (&acc)[NT], int tid)
-{
-    constexpr int NE = NT * 32;
-    constexpr int A_FLOATS = RT_BM * RT_BK;
-    constexpr int B_FLOATS = NE * RT_BK;
-    float *As = smem;
-    float *Bs = smem + 2 * A_FLOATS;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int li = lane & 31, lh = lane >> 5;
+// Operands of one slice in registers: read from the stage (xs: token rows, wst: the 32 rows of this
+// wavefront's expert tile) one slice ahead of the MFMAs that use them.
+template <int MT, typename XT> struct Frags;
 
-    floatx4_t av[4], bv[NT];
-#define RT_LOAD_F32(k0)                                                                        \
-    _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                             \
-        const int q_ = tid + 256 * i, r_ = q_ >> 3, c_ = q_ & 7;                               \
-        int64_t t_ = t0 + r_;                                                                  \
-        if (t_ >= T) t_ = T - 1;                                                               \
-        av[i] = *reinterpret_cast<const floatx4_t *>(x + t_ * H + (k0) + c_ * 4);              \
-    }                                                                                          \
-    _Pragma("unroll") for (int i = 0; i < NT; ++i) {                                            \
-        const int q_ = tid + 256 * i, r_ = q_ >> 3, c_ = q_ & 7;                               \
-        const floatx4_t zero_ = {0.f, 0.f, 0.f, 0.f};                                           \
-        bv[i] = (r_ < N) ? *reinterpret_cast<const floatx4_t *>(wr + (int64_t)r_ * H + (k0) + c_ * 4) \
-                         : zero_;                                                              \
-    }
-#define RT_STORE_F32(as, bs)                                                                   \
-    _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                             \
-        const int q_ = tid + 256 * i, r_ = q_ >> 3, c_ = q_ & 7;                               \
-        *reinterpret_cast<floatx4_t *>((as) + swz_f32(r_, c_)) = av[i];                         \
-    }                                                                                          \
-    _Pragma("unroll") for (int i = 0; i < NT; ++i) {                                            \
-        const int q_ = tid + 256 * i, r_ = q_ >> 3, c_ = q_ & 7;                               \
-        *reinterpret_cast<floatx4_t *>((bs) + swz_f32(r_, c_)) = bv[i];                         \
-    }
-
-    const int nk = H / RT_BK;
-    RT_LOAD_F32(0)
-    RT_STORE_F32(As, Bs)
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-        if (kt + 1 < nk) { RT_LOAD_F32((kt + 1) * RT_BK) }
-        const float *as = As + cur * A_FLOATS;
-        const float *bs = Bs + cur * B_FLOATS;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            // this lane's four k values of the group: 8q + 4*lh + {0..3}
-            const floatx4_t a4 = *reinterpret_cast<const floatx4_t *>(as + swz_f32(wave * 32 + li, 2 * q + lh));
-            floatx4_t b4[NT];
-#pragma unroll
-            for (int n = 0; n < NT; ++n)
-                b4[n] = *reinterpret_cast<const floatx4_t *>(bs + swz_f32(n * 32 + li, 2 * q + lh));
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-#pragma unroll
-                for (int n = 0; n < NT; ++n)
-                    acc[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(a4[s], b4[n][s], acc[n], 0, 0, 0);
-            }
-        }
-        if (kt + 1 < nk) { RT_STORE_F32(As + (cur ^ 1) * A_FLOATS, Bs + (cur ^ 1) * B_FLOATS) }
-        __syncthreads();
-    }
-#undef RT_LOAD_F32
-#undef RT_STORE_F32
-}
-
-// ---- logits of bf16 hidden states: x as stored, weights as three bf16 pieces, v_mfma_f32_32x32x16_bf16
-template <int NT>
-__device__ __forceinline__ void logits_bf16(const bf16_t *__restrict__ x, int64_t t0, int64_t T, int H,
-                                            const float *__restrict__ wr, int N, float *smem,
-                                            floatx16_t (&acc)[NT], int tid)
-{
-    constexpr int NE = NT * 32;
-    constexpr int A_U4 = RT_BM * 4;          // 16-byte units of one x stage
-    constexpr int P_U4 = NE * 4;             // ... of one weight piece
-    constexpr int STAGE_U4 = A_U4 + 3 * P_U4;
-    u32x4_t *base = reinterpret_cast<u32x4_t *>(smem);
-    const int lane = tid & 63, wave = tid >> 6;
-    const int li = lane & 31, lh = lane >> 5;
-
-    u32x4_t xv[2];
-    floatx4_t wv[NT];
-#define RT_LOAD_BF16(k0)                                                                       \
-    _Pragma("unroll") for (int i = 0; i < 2; ++i) {                                             \
-        const int q_ = tid + 256 * i, r_ = q_ >> 2, c_ = q_ & 3;                               \
-        int64_t t_ = t0 + r_;                                                                  \
-        if (t_ >= T) t_ = T - 1;                                                               \
-        xv[i] = *reinterpret_cast<const u32x4_t *>(x + t_ * H + (k0) + c_ * 8);                \
-    }                                                                                          \
-    _Pragma("unroll") for (int i = 0; i < NT; ++i) {                                            \
-        const int q_ = tid + 256 * i, r_ = q_ >> 3, c_ = q_ & 7;                               \
-        const floatx4_t zero_ = {0.f, 0.f, 0.f, 0.f};                                           \
-        wv[i] = (r_ < N) ? *reinterpret_cast<const floatx4_t *>(wr + (int64_t)r_ * H + (k0) + c_ * 4) \
-                         : zero_;                                                              \
-    }
-    // a thread holds 4 consecutive k of one weight row: half a 16-byte chunk of each piece
-#define RT_STORE_BF16(st)                                                                      \
-    _Pragma("unroll") for (int i = 0; i < 2; ++i) {                                             \
-        const int q_ = tid + 256 * i, r_ = q_ >> 2, c_ = q_ & 3;                               \
-        (st)[swz_bf16(r_, c_)] = xv[i];                                                        \
-    }                                                                                          \
-    _Pragma("unroll") for (int i = 0; i < NT; ++i) {                                            \
-        const int q_ = tid + 256 * i, r_ = q_ >> 3, c_ = q_ & 7;                               \
-        uint32_t h_[2], m_[2], l_[2];                                                          \
-        split3_pair(wv[i][0], wv[i][1], h_[0], m_[0], l_[0]);                                  \
-        split3_pair(wv[i][2], wv[i][3], h_[1], m_[1], l_[1]);                                  \
-        uint2 *dst_ = reinterpret_cast<uint2 *>((st) + A_U4 + swz_bf16(r_, c_ >> 1)) + (c_ & 1); \
-        dst_[0] = make_uint2(h_[0], h_[1]);                                                    \
-        dst_[2 * P_U4] = make_uint2(m_[0], m_[1]);                                              \
-        dst_[4 * P_U4] = make_uint2(l_[0], l_[1]);                                              \
-    }
-
-    const int nk = H / RT_BK;
-    RT_LOAD_BF16(0)
-    RT_STORE_BF16(base)
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-        if (kt + 1 < nk) { RT_LOAD_BF16((kt + 1) * RT_BK) }
-        const u32x4_t *st = base + cur * STAGE_U4;
-        if (NT == 4) {
-            // 128 experts: wavefront w takes expert tile w for all four token tiles, so a k-step reads
-            // 4 token fragments + 3 weight pieces from LDS (7 KB) instead of 1 + 12 (13 KB); the sums
-            // are the same, element by element and in the same order
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                bf16x8_t a8[NT], w8[3];
-#pragma unroll
-                for (int m = 0; m < NT; ++m)
-                    a8[m] = *reinterpret_cast<const bf16x8_t *>(&st[swz_bf16(m * 32 + li, 2 * ks + lh)]);
-#pragma unroll
-                for (int pc = 0; pc < 3; ++pc)
-                    w8[pc] = *reinterpret_cast<const bf16x8_t *>(
-                        &st[A_U4 + pc * P_U4 + swz_bf16(wave * 32 + li, 2 * ks + lh)]);
-#pragma unroll
-                for (int pc = 0; pc < 3; ++pc)
-#pragma unroll
-                    for (int m = 0; m < NT; ++m)
-                        acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a8[m], w8[pc], acc[m], 0, 0, 0);
-            }
-        } else
+template <int MT> struct Frags<MT, bf16_t> {
+    floatx4_t w[4];            // this lane's eight k values of k-step ks: 16 ks + 8 lh + {0..7}
+    bf16x8_t a[2][MT];
+    __device__ __forceinline__ void read(const u32x4_t *xs, const u32x4_t *wst, int row0, int li, int lh)
+    {
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-            // this lane's eight k values of the step: 16 ks + 8 lh + {0..7} = chunk 2 ks + lh
-            const bf16x8_t a8 = *reinterpret_cast<const bf16x8_t *>(&st[swz_bf16(wave * 32 + li, 2 * ks + lh)]);
-            bf16x8_t b8[NT][3];
 #pragma unroll
-            for (int n = 0; n < NT; ++n)
+            for (int i = 0; i < 2; ++i) w[2 * ks + i] = *reinterpret_cast<const floatx4_t *>(&wst[slot_f32(li, 4 * ks + 2 * lh + i)]);
 #pragma unroll
-                for (int pc = 0; pc < 3; ++pc)
-                    b8[n][pc] = *reinterpret_cast<const bf16x8_t *>(
-                        &st[A_U4 + pc * P_U4 + swz_bf16(n * 32 + li, 2 * ks + lh)]);
+            for (int m = 0; m < MT; ++m) a[ks][m] = *reinterpret_cast<const bf16x8_t *>(&xs[slot_bf16(row0 + m * 32 + li, 2 * ks + lh)]);
+        }
+    }
+    __device__ __forceinline__ void mfma(floatx16_t (&acc)[MT]) const
+    {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            u32x4_t piece[3];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const floatx4_t w4 = w[2 * ks + (q >> 1)];
+                uint32_t hi, mid, lo;
+                split3_pair(w4[2 * (q & 1)], w4[2 * (q & 1) + 1], hi, mid, lo);
+                piece[0][q] = hi;
+                piece[1][q] = mid;
+                piece[2][q] = lo;
+            }
 #pragma unroll
             for (int pc = 0; pc < 3; ++pc)
 #pragma unroll
-                for (int n = 0; n < NT; ++n)
-                    acc[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a8, b8[n][pc], acc[n], 0, 0, 0);
+                for (int m = 0; m < MT; ++m)
+                    acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][m], __builtin_bit_cast(bf16x8_t, piece[pc]), acc[m], 0, 0, 0);
         }
-        if (kt + 1 < nk) { RT_STORE_BF16(base + (cur ^ 1) * STAGE_U4) }
-        __syncthreads();
     }
-#undef RT_LOAD_BF16
-#undef RT_STORE_BF16
-}
-
-template <int NT, typename XT> struct SmemFloats {
-    static constexpr int NE = NT * 32;
-    static constexpr int TILES = sizeof(XT) == 4 ? 2 * (RT_BM * RT_BK + NE * RT_BK)            // fp32 tiles
-                                                 : 2 * (RT_BM * 4 + 3 * NE * 4) * 4;           // bf16 tiles
-    static constexpr int LOGITS = RT_BM * LogitLayout<NE>::STRIDE;
-    static constexpr int VALUE = TILES > LOGITS ? TILES : LOGITS;
 };
 
-// (v, id) goes into the descending list if it beats an entry; what falls off the end is dropped
-#define RT_INSERT(v_in, id_in, BEATS)                                                          \
-    {                                                                                          \
-        float v_ = (v_in);                                                                     \
-        int id_ = (id_in);                                                                     \
-        _Pragma("unroll") for (int s = 0; s < RT_LIST; ++s) {                                   \
-            const bool gt_ = BEATS(v_, id_, val[s], idx[s]);                                   \
-            const float tv_ = gt_ ? val[s] : v_;                                               \
-            const int ti_ = gt_ ? idx[s] : id_;                                                \
-            val[s] = gt_ ? v_ : val[s];                                                        \
-            idx[s] = gt_ ? id_ : idx[s];                                                       \
-            v_ = tv_;                                                                          \
-            id_ = ti_;                                                                         \
-        }                                                                                      \
-    }
-#define RT_BEATS_SCAN(v, i, lv, li_) ((v) > (lv))                                  /* ids arrive ascending */
-#define RT_BEATS_ANY(v, i, lv, li_) ((v) > (lv) || ((v) == (lv) && (i) < (li_)))   /* any order */
-
-template <int NT, typename XT>
-__global__ __launch_bounds__(256) void route_kernel(const XT *__restrict__ x, int64_t T, int H,
-                                                    const float *__restrict__ wr, int N, int K,
-                                                    int renorm, int32_t *__restrict__ out_idx,
-                                                    float *__restrict__ out_w,
-                                                    float *__restrict__ out_margin,
-                                                    float *__restrict__ out_probs)
-{
-    constexpr int NE = NT * 32;
-    typedef LogitLayout<NE> LL;
-    __shared__ __attribute__((aligned(16))) float smem[SmemFloats<NT, XT>::VALUE];
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int li = lane & 31;   // row / column inside a 32x32 MFMA tile
-    const int lh = lane >> 5;
-    const int64_t t0 = (int64_t)blockIdx.x * RT_BM;
-
-    floatx16_t acc[NT];
+template <int MT> struct Frags<MT, float> {
+    floatx4_t w[4];            // this lane's four k values of group q: 8 q + 4 lh + {0..3} = chunk 2 q + lh
+    floatx4_t a[4][MT];
+    __device__ __forceinline__ void read(const u32x4_t *xs, const u32x4_t *wst, int row0, int li, int lh)
+    {
 #pragma unroll
-    for (int n = 0; n < NT; ++n)
+        for (int q = 0; q < 4; ++q) {
+            w[q] = *reinterpret_cast<const floatx4_t *>(&wst[slot_f32(li, 2 * q + lh)]);
+#pragma unroll
+            for (int m = 0; m < MT; ++m) a[q][m] = *reinterpret_cast<const floatx4_t *>(&xs[slot_f32(row0 + m * 32 + li, 2 * q + lh)]);
+        }
+    }
+    __device__ __forceinline__ void mfma(floatx16_t (&acc)[MT]) const
+    {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int m = 0; m < MT; ++m) acc[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q][m][s], w[q][s], acc[m], 0, 0, 0);
+    }
+};
+
+// reductions over the eight lanes of a token (quad permutes, then the mirror of the half row)
+#if defined(__HIP_DEVICE_COMPILE__)
+#define RT_DPP(v, ctrl) __builtin_amdgcn_mov_dpp((v), ctrl, 0xF, 0xF, true)
+#else
+#define RT_DPP(v, ctrl) (v)
+#endif
+#define RT_DPP_F(v, ctrl) __int_as_float(RT_DPP(__float_as_int(v), ctrl))
+__device__ __forceinline__ float max8(float v)
+{
+    v = fmaxf(v, RT_DPP_F(v, 0xB1));
+    v = fmaxf(v, RT_DPP_F(v, 0x4E));
+    return fmaxf(v, RT_DPP_F(v, 0x141));
+}
+__device__ __forceinline__ float sum8(float v)
+{
+    v += RT_DPP_F(v, 0xB1);
+    v += RT_DPP_F(v, 0x4E);
+    return v + RT_DPP_F(v, 0x141);
+}
+__device__ __forceinline__ int min8(int v)
+{
+    int o = RT_DPP(v, 0xB1);
+    v = o < v ? o : v;
+    o = RT_DPP(v, 0x4E);
+    v = o < v ? o : v;
+    o = RT_DPP(v, 0x141);
+    return o < v ? o : v;
+}
+
+// Top-k, softmax weights, margin and probabilities of one token whose logit row lies in LDS; the eight
+// lanes sub = 0..7 of a token call this together.
+template <int NE>
+__device__ __forceinline__ void route_topk(const float *row, int sub, int64_t t, bool live, int N, int K, int renorm,
+                                           int32_t *__restrict__ out_idx, float *__restrict__ out_w,
+                                           float *__restrict__ out_margin, float *__restrict__ out_probs)
+{
+    constexpr int E = NE * 4;              // experts of one lane
+    const float NEG_INF = -__builtin_inff();
+    const int e0 = sub * E;
+    const float *mine = row + e0 + 4 * (e0 >> 5);
+    float val[E];
+#pragma unroll
+    for (int j = 0; j < E; j += 4) {
+        const floatx4_t v4 = *reinterpret_cast<const floatx4_t *>(mine + j);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) val[j + i] = (e0 + j + i < N) ? v4[i] : NEG_INF;
+    }
+    float m = val[0];
+#pragma unroll
+    for (int j = 1; j < E; ++j) m = fmaxf(m, val[j]);
+    const float zmax = max8(m);
+    // softmax denominator over all N experts, maximum subtracted
+    float part = 0.f;
+#pragma unroll
+    for (int j = 0; j < E; ++j) part += __expf(val[j] - zmax);
+    const float den = sum8(part);
+
+    float my_v = NEG_INF, zk = zmax, zk1 = NEG_INF;
+    int my_e = 0;
+    const int rounds = (out_margin && K < N) ? K + 1 : K;
+    float top = zmax;
+    for (int r = 0; r < rounds; ++r) {
+        int id = 0x7FFFFFFF;
+#pragma unroll
+        for (int j = E - 1; j >= 0; --j) id = (val[j] == top) ? e0 + j : id;    // the lowest id that holds the maximum
+        id = min8(id);
+        if (r == sub) { my_v = top; my_e = id; }
+        if (r == K - 1) zk = top;
+        if (r == K) zk1 = top;
+        const int gone = id - e0;
+        m = NEG_INF;
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            val[j] = (j == gone) ? NEG_INF : val[j];
+            m = fmaxf(m, val[j]);
+        }
+        top = max8(m);
+    }
+    const float p = sub < K ? __expf(my_v - zmax) : 0.f;
+    const float sel = sum8(p);
+    if (!live) return;
+    if (sub < K) {
+        out_idx[t * K + sub] = my_e < N ? my_e : N - 1;      // (a row of NaNs names no expert; ids stay in range)
+        out_w[t * K + sub] = p * (1.0f / (renorm ? sel : den));
+    }
+    if (out_margin && sub == 0) out_margin[t] = (K < N) ? zk - zk1 : __builtin_inff();
+    if (out_probs) {
+        const float rden = 1.0f / den;
+        float *o = out_probs + t * N + e0;
+        const bool wide = (N & 3) == 0 && (reinterpret_cast<uintptr_t>(out_probs) & 15) == 0;
+#pragma unroll
+        for (int j = 0; j < E; j += 4) {
+            const floatx4_t v4 = *reinterpret_cast<const floatx4_t *>(mine + j);
+            floatx4_t p4;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) p4[i] = __expf(v4[i] - zmax) * rden;
+            if (wide) {
+                if (e0 + j < N) *reinterpret_cast<floatx4_t *>(o + j) = p4;
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (e0 + j + i < N) o[j + i] = p4[i];
+            }
+        }
+    }
+}
+
+template <int NE, int MT, typename XT>
+__global__ __launch_bounds__(RT_BLOCK, 2) void route_kernel(const XT *__restrict__ x, int64_t T, int H,
+                                                            const float *__restrict__ wr, int N, int K, int renorm,
+                                                            int32_t *__restrict__ out_idx, float *__restrict__ out_w,
+                                                            float *__restrict__ out_margin, float *__restrict__ out_probs)
+{
+    typedef LogitLayout<NE> LL;
+    constexpr bool BF16 = sizeof(XT) == 2;
+    constexpr int TOKENS = 32 * MT * (4 / NE);
+    constexpr int W_U4 = NE * 32 * 8;                               // 16-byte units of the weight stage
+    constexpr int X_U4 = TOKENS * (BF16 ? 4 : 8);                   // ... of the token stage
+    constexpr int STAGE = W_U4 + X_U4;
+    constexpr int STAGES = STAGE * 16 > 20480 ? 3 : 4;
+    constexpr int LOGIT_U4 = TOKENS * LL::STRIDE / 4;
+    constexpr int W_COPIES = NE;                                    // copy instructions (1 KB each) per wavefront and slice
+    constexpr int X_TOTAL = X_U4 / 64, X_COPIES = X_TOTAL >= 4 ? X_TOTAL / 4 : 1;
+    constexpr int COPIES = W_COPIES + X_COPIES;
+    __shared__ u32x4_t smem[STAGES * STAGE > LOGIT_U4 ? STAGES * STAGE : LOGIT_U4];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 31;              // row / column inside a 32x32 MFMA tile
+    const int lh = lane >> 5;
+    const int et = wave % NE;              // expert tile
+    const int row0 = (wave / NE) * MT * 32;
+    const int64_t t0 = (int64_t)blockIdx.x * TOKENS;
+
+    // What this lane fetches for its landing places: copy i of a wavefront fills the 64 chunks behind
+    // group * 64.  Expert rows past N and tokens past T repeat the last one (masked or not stored later).
+    uint32_t w_off[W_COPIES], x_off[X_COPIES];
+#pragma unroll
+    for (int i = 0; i < W_COPIES; ++i) {
+        const int rs = (wave * W_COPIES + i) * 8 + (lane >> 3), r = rs ^ ((rs >> 3) & 1), c = (lane & 7) ^ (r & 7);
+        w_off[i] = (uint32_t)(((r < N ? r : N - 1) * H + c * 4) * 4);
+    }
+    const int64_t left = T - t0;
+#pragma unroll
+    for (int i = 0; i < X_COPIES; ++i) {
+        const int grp = (X_TOTAL >= 4 ? wave * X_COPIES + i : wave % X_TOTAL);      // fewer than 4 groups: fetched twice
+        int r, c;
+        if (BF16) {
+            r = grp * 16 + (lane >> 2);
+            c = (lane & 3) ^ ((r >> 2) & 3);
+        } else {
+            const int rs = grp * 8 + (lane >> 3);
+            r = rs ^ ((rs >> 3) & 1);
+            c = (lane & 7) ^ (r & 7);
+        }
+        x_off[i] = (uint32_t)((r < left ? r : (int)left - 1) * H * (int)sizeof(XT) + c * 16);
+    }
+    const char *w_base = reinterpret_cast<const char *>(wr), *x_base = reinterpret_cast<const char *>(x + t0 * H);
+    const int nk = H / RT_BK;
+    // slice j of the reduction -> stage `st` (past the end: the last slice again, so that the count of
+    // outstanding copies never varies)
+#define RT_COPY(j, st)                                                                                            \
+    {                                                                                                             \
+        const int j_ = (j) < nk ? (j) : nk - 1;                                                                   \
+        const char *wb_ = w_base + (int64_t)j_ * RT_BK * 4, *xb_ = x_base + (int64_t)j_ * RT_BK * (int)sizeof(XT); \
+        _Pragma("unroll") for (int i = 0; i < W_COPIES; ++i)                                                      \
+            copy16_to_lds(wb_, w_off[i], (st) + (wave * W_COPIES + i) * 64);                                      \
+        _Pragma("unroll") for (int i = 0; i < X_COPIES; ++i)                                                      \
+            copy16_to_lds(xb_, x_off[i], (st) + W_U4 + (X_TOTAL >= 4 ? wave * X_COPIES + i : wave % X_TOTAL) * 64); \
+    }
+
+    floatx16_t acc[MT];
+#pragma unroll
+    for (int n = 0; n < MT; ++n)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[n][r] = 0.f;
 
-    if (sizeof(XT) == 4)
-        logits_f32<NT>(reinterpret_cast<const float *>(x), t0, T, H, wr, N, smem, acc, tid);
-    else
-        logits_bf16<NT>(reinterpret_cast<const bf16_t *>(x), t0, T, H, wr, N, smem, acc, tid);
+#pragma unroll
+    for (int j = 0; j < STAGES - 1; ++j) RT_COPY(j, smem + j * STAGE)
+    int cur = 0, fill = STAGES - 1;        // stage of slice kt, stage that slice kt + STAGES - 1 goes to
+    // Slice kt has landed (this wavefront's part, then everyone's), and everyone has read slice kt - 1, whose
+    // stage is refilled; slice kt is read into one register set while the other, slice kt - 1, is multiplied.
+#define RT_NEXT(kt, set)                                                                                          \
+    {                                                                                                             \
+        wait_vmem<(STAGES - 2) * COPIES>();                                                                       \
+        lds_barrier();                                                                                            \
+        RT_COPY((kt) + STAGES - 1, smem + fill * STAGE)                                                           \
+        const u32x4_t *st_ = smem + cur * STAGE;                                                                  \
+        set.read(st_ + W_U4, st_ + et * 256, row0, li, lh);                                                       \
+        __builtin_amdgcn_sched_barrier(0);                                                                        \
+        cur = cur + 1 == STAGES ? 0 : cur + 1;                                                                    \
+        fill = fill + 1 == STAGES ? 0 : fill + 1;                                                                 \
+    }
+    Frags<MT, XT> fa, fb;
+    RT_NEXT(0, fa)
+    int kt = 1;
+    for (; kt + 1 < nk; kt += 2) {
+        RT_NEXT(kt, fb)
+        fa.mfma(acc);
+        RT_NEXT(kt + 1, fa)
+        fb.mfma(acc);
+    }
+    if (kt < nk) {
+        RT_NEXT(kt, fb)
+        fa.mfma(acc);
+        fb.mfma(acc);
+    } else {
+        fa.mfma(acc);
+    }
+#undef RT_NEXT
+#undef RT_COPY
+    wait_vmem<0>();
+    lds_barrier();
 
-    // park the logits (the tile stages are idle after the last barrier of the loop)
-    float *Ls = smem;
+    // park the logits (every copy has landed, every stage has been read)
+    float *Ls = reinterpret_cast<float *>(smem);
 #pragma unroll
-    for (int n = 0; n < NT; ++n)
+    for (int n = 0; n < MT; ++n)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            // (bf16 hidden states, 128 experts: accumulator n is token tile n of expert tile `wave`)
-            const bool by_expert = sizeof(XT) == 2 && NT == 4;
-            const int row = (by_expert ? n : wave) * 32 + (r >> 2) * 8 + lh * 4 + (r & 3);
-            Ls[LL::at(row, (by_expert ? wave : n) * 32 + li)] = acc[n][r];
-        }
+        for (int r = 0; r < 16; ++r)
+            Ls[LL::at(row0 + n * 32 + (r >> 2) * 8 + lh * 4 + (r & 3), et * 32 + li)] = acc[n][r];
     __syncthreads();
+#pragma unroll 1
+    for (int g = 0; g < TOKENS; g += RT_BLOCK / RT_LANES) {
+        const int tl = g + tid / RT_LANES;
+        route_topk<NE>(Ls + tl * LL::STRIDE, tid % RT_LANES, t0 + tl, t0 + tl < T, N, K, renorm, out_idx, out_w, out_margin, out_probs);
+    }
+}
 
-    // ---- top-k: lanes 2j and 2j+1 take token j of the workgroup, one half of the experts each
-    const float NEG_INF = -__builtin_inff();
-    const int tl = tid >> 1, half = tid & 1;
-    const int64_t t = t0 + tl;
-    const int e_base = half * LL::HALF;
-    const float *row = Ls + tl * LL::STRIDE + half * (LL::HALF + 4);
-    float val[RT_LIST];
-    int idx[RT_LIST];
-#pragma unroll
-    for (int s = 0; s < RT_LIST; ++s) { val[s] = NEG_INF; idx[s] = 0x7FFFFFFF; }
-#pragma unroll 2
-    for (int e4 = 0; e4 < LL::HALF; e4 += 4) {
-        const floatx4_t v4 = *reinterpret_cast<const floatx4_t *>(row + e4);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int e = e_base + e4 + j;
-            RT_INSERT((e < N) ? v4[j] : NEG_INF, e, RT_BEATS_SCAN)
-        }
-    }
-    // merge with the neighbour's list (both lanes end with the same merged list)
-    {
-        float pv[RT_LIST];
-        int pi[RT_LIST];
-#pragma unroll
-        for (int s = 0; s < RT_LIST; ++s) {
-            pv[s] = swap_with_neighbour(val[s]);
-            pi[s] = __float_as_int(swap_with_neighbour(__int_as_float(idx[s])));
-        }
-#pragma unroll
-        for (int s = 0; s < RT_LIST; ++s) RT_INSERT(pv[s], pi[s], RT_BEATS_ANY)
-    }
-    // softmax denominator over all N experts, maximum subtracted
-    const float zmax = val[0];
-    float part = 0.f;
-    for (int e4 = 0; e4 < LL::HALF; e4 += 4) {
-        const floatx4_t v4 = *reinterpret_cast<const floatx4_t *>(row + e4);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) part += (e_base + e4 + j < N) ? __expf(v4[j] - zmax) : 0.f;
-    }
-    const float den = part + swap_with_neighbour(part);
-
-    if (t < T) {
-        float pk[RT_LIST - 1];
-        float sel = 0.f;
-#pragma unroll
-        for (int j = 0; j < RT_LIST - 1; ++j) {
-            pk[j] = (j < K) ? __expf(val[j] - zmax) : 0.f;
-            sel += pk[j];
-        }
-        const float inv = 1.0f / (renorm ? sel : den);
-        // the even lane writes the ids, the odd lane the weights
-#pragma unroll
-        for (int j = 0; j < RT_LIST - 1; ++j) {
-            if (j < K) {
-                if (half == 0) out_idx[t * K + j] = idx[j];
-                else out_w[t * K + j] = pk[j] * inv;
-            }
-        }
-        if (out_margin && half == 0) {
-            float zk = val[0], zk1 = val[1];
-#pragma unroll
-            for (int j = 1; j < RT_LIST - 1; ++j)
-                if (j < K) { zk = val[j]; zk1 = val[j + 1]; }
-            out_margin[t] = (K < N) ? zk - zk1 : __builtin_inff();
-        }
-        if (out_probs) {
-            const float rden = 1.0f / den;
-            for (int e = 0; e < LL::HALF; ++e)
-                if (e_base + e < N) out_probs[t * N + e_base + e] = __expf(row[e] - zmax) * rden;
-        }
-    }
+// Tokens per workgroup.  A workgroup's time is one serial chain over the reduction whatever its width, and one
+// wavefront per SIMD issues a vector instruction every 8 cycles at best, so as long as the blocks do not fill
+// the chip the narrowest block is the fastest; beyond that a wider block splits the weights for more
+// tokens at a time.  Hence the fewest token tiles that still give one workgroup per compute unit, up to what the
+// LDS holds twice.  H = 2048, bf16, 1 / 2 / 4 token tiles: 128 experts, 4096 tokens 27 / 31 / 46 us, 16384 tokens
+// 45 / 35 / 47, 65536 tokens 169 / 119 / 101; 64 experts, 16384 tokens 26 / 30 / 47, 65536 tokens 80 / 63 / 62.
+template <int NE, typename XT>
+remoe_status launch_tiles(const XT *x, int64_t T, int H, const float *wr, int N, int K, int renorm, int32_t *out_idx,
+                          float *out_w, float *out_margin, float *out_probs, hipStream_t stream)
+{
+    constexpr int UNIT = 32 * (4 / NE);    // tokens of a workgroup per token tile of a wavefront
+    const dim3 block(RT_BLOCK);
+#define RT_LAUNCH(MT)                                                                                              \
+    hipLaunchKernelGGL((route_kernel<NE, MT, XT>), dim3((unsigned)ceil_div(T, UNIT * MT)), block, 0, stream, x, T, H, wr, N, K, \
+                       renorm, out_idx, out_w, out_margin, out_probs)
+    constexpr bool BF16 = sizeof(XT) == 2;
+    constexpr int MAX_MT = NE == 1 ? (BF16 ? 2 : 1) : (BF16 ? 4 : 2);
+    int cus = 0;
+    const remoe_status st = compute_units(&cus);
+    if (st != REMOE_OK) return st;
+    const int64_t mt = ceil_div(T, (int64_t)UNIT * cus);
+    if (mt > 2 && MAX_MT >= 4) RT_LAUNCH((MAX_MT >= 4 ? 4 : 1));
+    else if (mt > 1 && MAX_MT >= 2) RT_LAUNCH((MAX_MT >= 2 ? 2 : 1));
+    else RT_LAUNCH(1);
+#undef RT_LAUNCH
+    return check_hip(hipGetLastError(), "route_kernel launch");
 }
 
 template <typename XT>
@@ -374,17 +387,9 @@ remoe_status launch_typed(const XT *x, int64_t T, int H, const float *wr, int N,
                           int32_t *out_idx, float *out_w, float *out_margin, float *out_probs,
                           hipStream_t stream)
 {
-    const dim3 grid((unsigned)ceil_div(T, RT_BM)), block(256);
-    if (N <= 32)
-        hipLaunchKernelGGL((route_kernel<1, XT>), grid, block, 0, stream, x, T, H, wr, N, K, renorm,
-                           out_idx, out_w, out_margin, out_probs);
-    else if (N <= 64)
-        hipLaunchKernelGGL((route_kernel<2, XT>), grid, block, 0, stream, x, T, H, wr, N, K, renorm,
-                           out_idx, out_w, out_margin, out_probs);
-    else
-        hipLaunchKernelGGL((route_kernel<4, XT>), grid, block, 0, stream, x, T, H, wr, N, K, renorm,
-                           out_idx, out_w, out_margin, out_probs);
-    return check_hip(hipGetLastError(), "route_kernel launch");
+    if (N <= 32) return launch_tiles<1, XT>(x, T, H, wr, N, K, renorm, out_idx, out_w, out_margin, out_probs, stream);
+    if (N <= 64) return launch_tiles<2, XT>(x, T, H, wr, N, K, renorm, out_idx, out_w, out_margin, out_probs, stream);
+    return launch_tiles<4, XT>(x, T, H, wr, N, K, renorm, out_idx, out_w, out_margin, out_probs, stream);
 }
 
 }  // namespace
