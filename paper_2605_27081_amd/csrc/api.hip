@@ -340,10 +340,6 @@ remoe_status moe_forward(const remoe_layer_desc *desc, const void *x, int64_t n_
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     const int H = desc->hidden, I = desc->inter, Is = desc->shared_inter, K = desc->top_k, N = desc->n_experts;
     const bool f32 = desc->dtype == REMOE_F32;
-    auto gemm = [&](int mode, const GroupedGemmArgs &g) {
-        return f32 ? launch_grouped_gemm_f32(mode, g, stream) : launch_grouped_gemm_bf16(mode, g, stream);
-    };
-
     // 1. router: logits, top-k, softmax weights
     {
         ProfScope prof(REMOE_PROF_ROUTE, stream);
@@ -357,49 +353,41 @@ remoe_status moe_forward(const remoe_layer_desc *desc, const void *x, int64_t n_
     }
     if (st != REMOE_OK) return st;
     // 3. routed experts: gate/up + SwiGLU, then the down projection (the fp32 kernel also applies the gate weight)
-    GroupedGemmArgs g{};
+    // 4. shared expert (dense, one group): rows T*K .. T*K+T-1 of the row buffer
+    GroupedGemmArgs g{}, s{};
     g.a = x; g.lda = H; g.a_rows = T; g.row_gather = ws.pb.slot_token;
     g.b0 = w_gate; g.b1 = w_up; g.k_dim = H; g.n_out = I;
     g.tile_expert = ws.pb.tile_expert; g.tile_row0 = ws.pb.tile_row0; g.tile_rows = ws.pb.tile_rows;
     g.n_tiles = ws.pb.n_tiles; g.max_tiles = ws.max_tiles;
     g.c = ws.hbuf; g.ldc = I; g.c_row_offset = 0;
     g.tile_ctr = ws.pb.gemm_ctr;
-    {
-        ProfScope prof(REMOE_PROF_GATE_UP, stream);
-        st = gemm(0, g);
-    }
+    s.a = x; s.lda = H; s.a_rows = T; s.b0 = ws_gate; s.b1 = ws_up; s.k_dim = H; s.n_out = Is;
+    s.dense_rows = T; s.max_tiles = (int)ceil_div(T, gemm_tile_m());
+    s.c = ws.hsbuf; s.ldc = Is;
+    s.tile_ctr = ws.pb.gemm_ctr + 16;
+    // bf16: routed and shared tiles in one launch (timed as the routed kind); fp32: one launch each
+    auto gemm = [&](int mode, int kind, int shared_kind) {
+        {
+            ProfScope prof(kind, stream);
+            const remoe_status st_ = f32 ? launch_grouped_gemm_f32(mode, g, stream)
+                                         : launch_grouped_gemm_bf16(mode, g, Is > 0 ? &s : nullptr, stream);
+            if (st_ != REMOE_OK || !f32 || Is == 0) return st_;
+        }
+        ProfScope prof(shared_kind, stream);
+        return launch_grouped_gemm_f32(mode, s, stream);
+    };
+    st = gemm(0, REMOE_PROF_GATE_UP, REMOE_PROF_SHARED_GATE_UP);
     if (st != REMOE_OK) return st;
     g.a = ws.hbuf; g.lda = I; g.a_rows = T * K; g.row_gather = nullptr;
     g.b0 = w_down; g.b1 = nullptr; g.k_dim = I; g.n_out = H;
     g.row_scale = f32 ? ws.pb.slot_w : nullptr;   // bf16: the combine step applies the gate weights
     g.c = ws.rows; g.ldc = H;
     g.tile_ctr = ws.pb.gemm_ctr + 8;
-    {
-        ProfScope prof(REMOE_PROF_DOWN, stream);
-        st = gemm(1, g);
-    }
+    s.a = ws.hsbuf; s.lda = Is; s.a_rows = T; s.b0 = ws_down; s.b1 = nullptr; s.k_dim = Is; s.n_out = H;
+    s.c = ws.rows; s.ldc = H; s.c_row_offset = T * K;
+    s.tile_ctr = ws.pb.gemm_ctr + 24;
+    st = gemm(1, REMOE_PROF_DOWN, REMOE_PROF_SHARED_DOWN);
     if (st != REMOE_OK) return st;
-    // 4. shared expert (dense, one group): rows T*K .. T*K+T-1 of the row buffer
-    if (Is > 0) {
-        GroupedGemmArgs s{};
-        s.a = x; s.lda = H; s.a_rows = T; s.b0 = ws_gate; s.b1 = ws_up; s.k_dim = H; s.n_out = Is;
-        s.dense_rows = T; s.max_tiles = (int)ceil_div(T, gemm_tile_m());
-        s.c = ws.hsbuf; s.ldc = Is;
-        s.tile_ctr = ws.pb.gemm_ctr + 16;
-        {
-            ProfScope prof(REMOE_PROF_SHARED_GATE_UP, stream);
-            st = gemm(0, s);
-        }
-        if (st != REMOE_OK) return st;
-        s.a = ws.hsbuf; s.lda = Is; s.a_rows = T; s.b0 = ws_down; s.b1 = nullptr; s.k_dim = Is; s.n_out = H;
-        s.c = ws.rows; s.ldc = H; s.c_row_offset = T * K;
-        s.tile_ctr = ws.pb.gemm_ctr + 24;
-        {
-            ProfScope prof(REMOE_PROF_SHARED_DOWN, stream);
-            st = gemm(1, s);
-        }
-        if (st != REMOE_OK) return st;
-    }
     // 5. combine the K (+1) rows of every token
     ProfScope prof(REMOE_PROF_COMBINE, stream);
     return launch_combine(desc->dtype, ws.rows, ws.pb.pair_slot, f32 ? nullptr : out_w, T, K, H, T * K, Is > 0, x,

@@ -112,7 +112,8 @@ struct GroupedGemmArgs {
     uint32_t *tile_ctr;       // bf16 kernel: 8 tile counters (one per XCD), zero when the launch starts
 };
 int gemm_tile_m();
-remoe_status launch_grouped_gemm_bf16(int mode, const GroupedGemmArgs &g, hipStream_t stream);
+// bf16, row tiles of gemm_tile_m() slots; the shared expert (or NULL) runs in the same launch.
+remoe_status launch_grouped_gemm_bf16(int mode, const GroupedGemmArgs &routed, const GroupedGemmArgs *shared, hipStream_t stream);
 remoe_status launch_grouped_gemm_f32(int mode, const GroupedGemmArgs &g, hipStream_t stream);
 
 // y[t] = sum_j rows[pair_slot[t*K+j]] + s_t * rows[shared_row0 + t]
