@@ -144,6 +144,7 @@ struct Workspace {
     void *hbuf = nullptr;     // [T*K, I]            SwiGLU activations of the routed experts
     void *hsbuf = nullptr;    // [T, I_s]            SwiGLU activations of the shared expert
     void *rows = nullptr;     // [T*K (+T), H]       weighted per-(token, expert) outputs, then shared rows
+    int tile_m = 0;           // rows of a GEMM row tile
     int max_tiles = 0;
 };
 
@@ -154,6 +155,31 @@ template <typename P> void carve(char *base, size_t &off, P *&ptr, size_t bytes)
     off += bytes;
 }
 
+// Rows per GEMM row tile: 256 (gemm_bf16.hip, and fp32 layers) or 32, 64, 128 (gemm_stream.hip).  Few rows per expert
+// leave a tall tile empty, and a launch of few tiles leaves compute units idle; tall tiles in turn fetch
+// fewer operand bytes per product.  The lines below are where the whole layer's time crosses, measured on layers of
+// 8 to 128 experts, H 1024-4096, I 512-1472, with and without shared expert, for example (us, smaller / larger tile):
+//   32 / 64 rows    64 tokens, 60 experts top-4 (4.3 rows per expert) 230 / 241; 128 tokens (8.5 rows) 255 / 251
+//   64 / 128 rows   333 tokens, 60 experts top-4 (22 rows) 284 / 296; 512 tokens, 64 experts top-6 (48 rows) 293 / 286
+//   128 / 256 rows  1500 tokens, 128 experts top-8 (94 rows) 311 / 339; 3000 tokens (188 rows) 432 / 382
+// and by the number of column x row tiles of the gate/up launch (256 compute units; the constant, not the device's,
+// so that the workspace size is a function of its arguments alone):
+//   64 / 128 rows   2048 tokens, 10 experts top-1 (128-row tiles: 126) 136 / 142; 3000 tokens (170) 168 / 151
+//   128 / 256 rows  4096 tokens, 10 experts top-1 (256-row tiles: 126) 168 / 178; 6000 tokens (170) 236 / 191
+int forward_tile_m(const remoe_layer_desc *d, int64_t T)
+{
+    const double rows = (double)T * d->top_k / d->n_experts;
+    auto tiles = [&](int m) {
+        const double per_expert = rows / m + 0.5;
+        return d->n_experts * (per_expert > 1.0 ? per_expert : 1.0) * ceil_div(d->inter, 128) +
+               (double)(ceil_div(T, m) * ceil_div(d->shared_inter, 128));
+    };
+    constexpr double ENOUGH = 256 * 5 / 8;
+    if (d->dtype == REMOE_F32 || (rows >= 120.0 && tiles(256) >= ENOUGH)) return gemm_tile_m();
+    if (rows >= 40.0 && tiles(128) >= ENOUGH) return 128;
+    return rows > 6.0 ? 64 : 32;
+}
+
 Workspace layout(const remoe_layer_desc *d, int64_t T, void *base_v)
 {
     Workspace w;
@@ -161,7 +187,8 @@ Workspace layout(const remoe_layer_desc *d, int64_t T, void *base_v)
     const size_t es = d->dtype == REMOE_F32 ? 4 : 2;
     const int64_t pairs = T * d->top_k;
     const int64_t n_blk = ceil_div(T, permute_tokens_per_block());
-    w.max_tiles = (int)(ceil_div(pairs, gemm_tile_m()) + d->n_experts);
+    w.tile_m = forward_tile_m(d, T);
+    w.max_tiles = (int)(pairs / w.tile_m + (pairs < d->n_experts ? pairs : d->n_experts));   // full tiles + a ragged one per expert
     size_t off = 0;
     carve(base, off, w.pb.blk_hist, sizeof(int32_t) * 2 * n_blk * d->n_experts);
     carve(base, off, w.pb.offsets, sizeof(int32_t) * (d->n_experts + 1));
@@ -349,7 +376,7 @@ remoe_status moe_forward(const remoe_layer_desc *desc, const void *x, int64_t n_
     // 2. sort (token, j) pairs by expert; build the GEMM tile list
     {
         ProfScope prof(REMOE_PROF_PERMUTE, stream);
-        st = launch_permute(out_idx, out_w, T, K, N, gemm_tile_m(), ws.max_tiles, ws.pb, stream);
+        st = launch_permute(out_idx, out_w, T, K, N, ws.tile_m, ws.max_tiles, ws.pb, stream);
     }
     if (st != REMOE_OK) return st;
     // 3. routed experts: gate/up + SwiGLU, then the down projection (the fp32 kernel also applies the gate weight)
@@ -362,15 +389,17 @@ remoe_status moe_forward(const remoe_layer_desc *desc, const void *x, int64_t n_
     g.c = ws.hbuf; g.ldc = I; g.c_row_offset = 0;
     g.tile_ctr = ws.pb.gemm_ctr;
     s.a = x; s.lda = H; s.a_rows = T; s.b0 = ws_gate; s.b1 = ws_up; s.k_dim = H; s.n_out = Is;
-    s.dense_rows = T; s.max_tiles = (int)ceil_div(T, gemm_tile_m());
+    s.dense_rows = T; s.max_tiles = (int)ceil_div(T, ws.tile_m);
     s.c = ws.hsbuf; s.ldc = Is;
     s.tile_ctr = ws.pb.gemm_ctr + 16;
     // bf16: routed and shared tiles in one launch (timed as the routed kind); fp32: one launch each
     auto gemm = [&](int mode, int kind, int shared_kind) {
         {
             ProfScope prof(kind, stream);
+            const GroupedGemmArgs *both = Is > 0 ? &s : nullptr;
             const remoe_status st_ = f32 ? launch_grouped_gemm_f32(mode, g, stream)
-                                         : launch_grouped_gemm_bf16(mode, g, Is > 0 ? &s : nullptr, stream);
+                                     : ws.tile_m < gemm_tile_m() ? launch_stream_gemm(mode, g, both, ws.tile_m, stream)
+                                                                 : launch_grouped_gemm_bf16(mode, g, both, stream);
             if (st_ != REMOE_OK || !f32 || Is == 0) return st_;
         }
         ProfScope prof(shared_kind, stream);

@@ -114,6 +114,8 @@ struct GroupedGemmArgs {
 int gemm_tile_m();
 // bf16, row tiles of gemm_tile_m() slots; the shared expert (or NULL) runs in the same launch.
 remoe_status launch_grouped_gemm_bf16(int mode, const GroupedGemmArgs &routed, const GroupedGemmArgs *shared, hipStream_t stream);
+// The same for row tiles of tile_m = 32, 64 or 128 slots.
+remoe_status launch_stream_gemm(int mode, const GroupedGemmArgs &routed, const GroupedGemmArgs *shared, int tile_m, hipStream_t stream);
 remoe_status launch_grouped_gemm_f32(int mode, const GroupedGemmArgs &g, hipStream_t stream);
 
 // y[t] = sum_j rows[pair_slot[t*K+j]] + s_t * rows[shared_row0 + t]
