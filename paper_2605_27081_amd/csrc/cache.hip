@@ -323,6 +323,9 @@ __global__ void zero_u64_kernel(unsigned long long *p, int64_t n)
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0ull;
 }
 
+// V neighbouring steps per thread (4 when the table's rows allow 4-byte loads), the bytes summed two and two
+// in 16-bit halves (at most 257 layers of at most 255).
+template <int V>
 __global__ __launch_bounds__(256) void step_summary_kernel(const uint8_t *__restrict__ miss, int64_t L, int64_t n,
                                                            uint16_t *__restrict__ out_all,
                                                            unsigned long long *__restrict__ hist, int hist_len)
@@ -330,31 +333,52 @@ __global__ __launch_bounds__(256) void step_summary_kernel(const uint8_t *__rest
     __shared__ uint32_t lh[SS_MAX_HIST];
     for (int v = threadIdx.x; v < hist_len; v += blockDim.x) lh[v] = 0u;
     __syncthreads();
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        uint32_t a = 0;
-        for (int64_t l = 0; l < L; ++l) a += miss[l * n + i];
-        out_all[i] = (uint16_t)a;
-        atomicAdd(&lh[(int)a < hist_len ? a : (uint32_t)(hist_len - 1)], 1u);   // sums beyond the table share its last bin
+    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * V; i < n; i += (int64_t)gridDim.x * blockDim.x * V) {
+        uint32_t even = 0, odd = 0;
+#pragma unroll 8
+        for (int64_t l = 0; l < L; ++l) {
+            const uint32_t w = V == 4 ? *reinterpret_cast<const uint32_t *>(miss + l * n + i) : (uint32_t)miss[l * n + i];
+            even += w & 0x00FF00FFu;
+            odd += (w >> 8) & 0x00FF00FFu;
+        }
+        const uint32_t a[4] = {even & 0xFFFFu, odd & 0xFFFFu, even >> 16, odd >> 16};
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            out_all[i + j] = (uint16_t)a[j];
+            atomicAdd(&lh[(int)a[j] < hist_len ? a[j] : (uint32_t)(hist_len - 1)], 1u);   // sums beyond the table share its last bin
+        }
     }
     __syncthreads();
     for (int v = threadIdx.x; v < hist_len; v += blockDim.x)
         if (lh[v]) atomicAdd(&hist[v], (unsigned long long)lh[v]);   // integer sums: exact in any order
 }
 
-// percentile p = smallest v whose cumulative count reaches p percent of the n steps
-__global__ void step_percentile_kernel(const unsigned long long *__restrict__ hist, int hist_len, unsigned long long n,
-                                       int32_t *__restrict__ out_pct)
+// percentile p = smallest v whose cumulative count reaches p percent of the n steps.  One wavefront: lane l
+// sums its share of the bins, the shares are scanned, and the lane in whose share the count is reached finds
+// the bin (a single thread walking the table took 23 us for 385 bins).
+__global__ __launch_bounds__(64) void step_percentile_kernel(const unsigned long long *__restrict__ hist, int hist_len, unsigned long long n,
+                                                             int32_t *__restrict__ out_pct)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    const int lane = threadIdx.x;
+    const int per = (hist_len + 63) / 64, lo = lane * per, hi = lo + per < hist_len ? lo + per : hist_len;
+    unsigned long long mine = 0;
+    for (int v = lo; v < hi; ++v) mine += hist[v];
+    unsigned long long upto = mine;                  // inclusive scan over the lanes
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned long long o = __shfl_up(upto, off, 64);
+        if (lane >= off) upto += o;
+    }
     const unsigned long long pcts[3] = {50ull, 95ull, 99ull};
+    if (lane < 3 && n == 0) out_pct[lane] = -1;
+    if (n == 0) return;
     for (int k = 0; k < 3; ++k) {
-        unsigned long long cum = 0;
-        int32_t ans = -1;
-        for (int v = 0; v < hist_len && ans < 0; ++v) {
+        const unsigned long long target = pcts[k] * n;
+        if (100ull * upto < target || 100ull * (upto - mine) >= target) continue;
+        unsigned long long cum = upto - mine;
+        for (int v = lo; v < hi; ++v) {
             cum += hist[v];
-            if (n > 0 && 100ull * cum >= pcts[k] * n) ans = v;
+            if (100ull * cum >= target) { out_pct[k] = v; break; }
         }
-        out_pct[k] = ans;
     }
 }
 
@@ -375,15 +399,25 @@ __global__ __launch_bounds__(256) void balance_kernel(const int32_t *__restrict_
                                                       uint32_t *__restrict__ out_load, int32_t *__restrict__ out_used,
                                                       double *__restrict__ out_entropy, double *__restrict__ out_cv)
 {
-    __shared__ uint32_t load[128];
+    __shared__ uint32_t load[128], bins[4][128];      // a histogram per wavefront: fewer lanes meet in one bin
     const int64_t s = blockIdx.x;
-    if (threadIdx.x < 128) load[threadIdx.x] = 0u;
+    for (int q = threadIdx.x; q < 4 * 128; q += 256) (&bins[0][0])[q] = 0u;
     __syncthreads();
     const int32_t *tr = idx + s * T * K;
-    for (int64_t q = threadIdx.x; q < T * K; q += blockDim.x) {
-        const int e = tr[q];
-        if (e >= 0 && e < N) atomicAdd(&load[e], 1u);
+    uint32_t *mine = bins[threadIdx.x >> 6];
+    auto add = [&](int e) { if ((uint32_t)e < (uint32_t)N) atomicAdd(&mine[e], 1u); };
+    const int64_t n = T * K, n4 = (reinterpret_cast<uintptr_t>(tr) & 15) == 0 ? n / 4 : 0;
+#pragma unroll 2
+    for (int64_t q = threadIdx.x; q < n4; q += 256) {
+        const int4 v = reinterpret_cast<const int4 *>(tr)[q];
+        add(v.x);
+        add(v.y);
+        add(v.z);
+        add(v.w);
     }
+    for (int64_t q = n4 * 4 + threadIdx.x; q < n; q += 256) add(tr[q]);
+    __syncthreads();
+    if (threadIdx.x < 128) load[threadIdx.x] = (bins[0][threadIdx.x] + bins[1][threadIdx.x]) + (bins[2][threadIdx.x] + bins[3][threadIdx.x]);
     __syncthreads();
     if (threadIdx.x < N) out_load[s * N + threadIdx.x] = load[threadIdx.x];
     if (threadIdx.x < 64) {
@@ -475,9 +509,11 @@ remoe_status launch_step_summary(const uint8_t *miss, int64_t L, int64_t S, int6
     unsigned long long *h = reinterpret_cast<unsigned long long *>(hist);
     hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(256), 0, stream, h, (int64_t)hist_len);
     if (n > 0) {
-        int64_t blocks = ceil_div(n, 256);
+        const bool wide = (n & 3) == 0 && ((reinterpret_cast<uintptr_t>(miss) & 3) == 0);
+        int64_t blocks = ceil_div(n, wide ? 1024 : 256);
         if (blocks > 2048) blocks = 2048;
-        hipLaunchKernelGGL(step_summary_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, miss, L, n, out_all, h, hist_len);
+        if (wide) hipLaunchKernelGGL(step_summary_kernel<4>, dim3((unsigned)blocks), dim3(256), 0, stream, miss, L, n, out_all, h, hist_len);
+        else hipLaunchKernelGGL(step_summary_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, stream, miss, L, n, out_all, h, hist_len);
     }
     hipLaunchKernelGGL(step_percentile_kernel, dim3(1), dim3(64), 0, stream, h, hist_len, (unsigned long long)n, pct);
     return check_hip(hipGetLastError(), "step_summary launch");
