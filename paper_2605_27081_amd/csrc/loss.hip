@@ -11,57 +11,31 @@
 // computed in fp64 (the work is ~7 N logarithms per step, nothing next to the expert GEMMs), with
 // SymKL(P,Q) = (1/2) sum_k (P[k] - Q[k]) (ln P[k] - ln Q[k]).
 //
-// loss_partial_kernel: grid (chunk, sequence); a workgroup's 4 wavefronts take the steps (and the
-// windows) of its chunk in turn, lane l holding experts l and l + 64; per-wavefront fp64 sums are
-// combined in wavefront order and written to the workspace.  loss_final_kernel adds the chunks of
-// a sequence in chunk order and applies the normalisations, so results repeat bit for bit.
+// loss_partial_kernel: grid (chunk, sequence); a workgroup walks its chunk of steps in blocks whose
+// logarithms lie in LDS (loss_rows.h), a wavefront per step with lane l holding experts l and l + 64, and
+// then its chunk of the windows; per-wavefront fp64 sums are combined in wavefront order and written to
+// the workspace.  loss_final_kernel adds the chunks of a sequence (a lane per chunk, fixed order) and applies the
+// normalisations, so results repeat bit for bit.
+//
+// Bound by the fp64 logarithms: (1 + halo / steps) + 1 per entry instead of the 2 + |D| of a step that computes
+// its partners' itself.  8 sequences x 2048 steps, 64 experts, |D| = 5: 130 us before, 22 us now.
 #include "common.h"
+#include "loss_rows.h"
 
 namespace remoe {
 
 namespace {
 
-constexpr int LS_CHUNKS = 16;           // chunks of steps (and of windows) per sequence
-constexpr int LS_WAVES = 4;
+constexpr int LS_CHUNKS = 64;           // chunks of steps (and of windows) per sequence, a lane each in the last sum
 constexpr int LS_TERMS = 5;             // sum m_t, sum KL, sum SymKL adjacent, sum lag term, sum window entropy
 
-__device__ __forceinline__ double wsum64(double v)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-        const unsigned lo = __shfl_xor((unsigned)(b & 0xFFFFFFFFull), off, 64);
-        const unsigned hi = __shfl_xor((unsigned)(b >> 32), off, 64);
-        v += __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-    }
-    return v;
-}
+// this lane's share of KL(a || b): a ln(a / b), 0 where a = 0 (ln b = -inf where b = 0)
+__device__ __forceinline__ double kl_part(double a, double la, double lb) { return a > 0.0 ? a * (la - lb) : 0.0; }
 
-struct Row {
-    double p0, p1, l0, l1;              // probabilities of experts lane, lane + 64 and their logarithms
-};
-
-__device__ __forceinline__ Row load_row(const float *__restrict__ base, int64_t t, int N, int lane)
+// ... of SymKL(a, b) = (1/2) (a - b) (ln a - ln b), 0 where a = b
+__device__ __forceinline__ double symkl_part(double a, double la, double b, double lb)
 {
-    Row r;
-    r.p0 = lane < N ? (double)base[t * N + lane] : 0.0;
-    r.p1 = lane + 64 < N ? (double)base[t * N + lane + 64] : 0.0;
-    r.l0 = r.p0 > 0.0 ? log(r.p0) : 0.0;
-    r.l1 = r.p1 > 0.0 ? log(r.p1) : 0.0;
-    return r;
-}
-
-// this lane's share of KL(a || b): a ln(a / b), 0 where a = 0 (ln b = -inf where b = 0 and a > 0)
-__device__ __forceinline__ double kl_part(double a, double la, double b, double lb)
-{
-    if (!(a > 0.0)) return 0.0;
-    return a * (la - (b > 0.0 ? lb : -__builtin_inf()));
-}
-
-__device__ __forceinline__ double symkl_part(const Row &a, const Row &b)
-{
-    return 0.5 * (kl_part(a.p0, a.l0, b.p0, b.l0) + kl_part(b.p0, b.l0, a.p0, a.l0) +
-                  kl_part(a.p1, a.l1, b.p1, b.l1) + kl_part(b.p1, b.l1, a.p1, a.l1));
+    return a == b ? 0.0 : 0.5 * (a - b) * (la - lb);
 }
 
 struct LossArgs {
@@ -70,13 +44,18 @@ struct LossArgs {
     int64_t T;
     int N, K, n_lags, window;
     int lags[8];
+    RowBlocks blk;
     double *partial;                    // [S, LS_CHUNKS, LS_TERMS]
     double *out;                        // [S, 6]
 };
 
-__global__ __launch_bounds__(LS_WAVES * 64) void loss_partial_kernel(const LossArgs a)
+// HALVES: 64-expert halves of a row
+template <int HALVES>
+__global__ __launch_bounds__(LR_WAVES * 64) void loss_partial_kernel(const LossArgs a)
 {
-    __shared__ double part[LS_WAVES][LS_TERMS];
+    extern __shared__ double logs[];
+    __shared__ double part[LR_WAVES][LS_TERMS];
+    __shared__ double2 table[LT_BINS];
     const int chunk = blockIdx.x;
     const int64_t s = blockIdx.y;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -85,41 +64,48 @@ __global__ __launch_bounds__(LS_WAVES * 64) void loss_partial_kernel(const LossA
     const float *P = a.probs + s * T * N, *Q = a.probs_ref + s * T * N;
     const int32_t *E = a.idx + s * T * K;
     double acc[LS_TERMS] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    fill_log_table(table);
+    bool has_unit = false;
+    for (int i = 0; i < a.n_lags; ++i) has_unit |= a.lags[i] == 1;
 
     const int64_t per = (T + LS_CHUNKS - 1) / LS_CHUNKS;
     const int64_t t_lo = chunk * per, t_hi = (t_lo + per < T) ? t_lo + per : T;
-    for (int64_t t = t_lo + wave; t < t_hi; t += LS_WAVES) {
-        const Row pt = load_row(P, t, N, lane);
-        const Row qt = load_row(Q, t, N, lane);
-        acc[1] += kl_part(pt.p0, pt.l0, qt.p0, qt.l0) + kl_part(pt.p1, pt.l1, qt.p1, qt.l1);
-        if (t >= 1) {
-            if (lane < K) acc[0] += (double)P[t * N + E[(t - 1) * K + lane]];
-            for (int i = 0; i < a.n_lags; ++i) {
-                const int d = a.lags[i];
-                if (t - d < 0) continue;
-                const double v = symkl_part(pt, load_row(P, t - d, N, lane));
-                acc[3] += v;
-                if (d == 1) acc[2] += v;
+    for (int64_t b0 = t_lo; b0 < t_hi; b0 += a.blk.steps) {
+        const int64_t b1 = b0 + a.blk.steps < t_hi ? b0 + a.blk.steps : t_hi;
+        const int64_t r0 = b0 > a.blk.halo ? b0 - a.blk.halo : 0;
+        __syncthreads();                // the block before is done with the LDS
+        stage_logs(P, r0, b1, N, table, logs);
+        __syncthreads();
+        for (int64_t t = b0 + wave; t < b1; t += LR_WAVES) {
+            if (t >= 1 && lane < K) acc[0] += (double)P[t * N + E[(t - 1) * K + lane]];
+#pragma unroll
+            for (int h = 0; h < HALVES; ++h) {
+                const int e = lane + 64 * h;
+                if (e >= N) continue;
+                const double p = (double)P[t * N + e], lp = logs[(t - r0) * N + e];
+                acc[1] += kl_part(p, lp, log_f32(Q[t * N + e], table));
+                if (t < 1) continue;
+                if (!has_unit) acc[2] += symkl_part(p, lp, (double)P[(t - 1) * N + e], logs[(t - 1 - r0) * N + e]);
+                for (int i = 0; i < a.n_lags; ++i) {
+                    const int d = a.lags[i];
+                    if (t - d < 0) continue;
+                    const double r = (double)P[(t - d) * N + e];
+                    const double v = symkl_part(p, lp, r, d <= a.blk.halo ? logs[(t - d - r0) * N + e] : log_f32((float)r, table));
+                    acc[3] += v;
+                    if (d == 1) acc[2] += v;
+                }
             }
-            bool has_unit = false;
-            for (int i = 0; i < a.n_lags; ++i) has_unit |= a.lags[i] == 1;
-            if (!has_unit) acc[2] += symkl_part(pt, load_row(P, t - 1, N, lane));
         }
     }
     // windows of this chunk
     const int64_t n_win = T / a.window;
     const int64_t wper = (n_win + LS_CHUNKS - 1) / LS_CHUNKS;
-    const int64_t b_lo = chunk * wper, b_hi = (b_lo + wper < n_win) ? b_lo + wper : n_win;
-    for (int64_t b = b_lo + wave; b < b_hi; b += LS_WAVES) {
-        double m0 = 0.0, m1 = 0.0;
-        for (int j = 0; j < a.window; ++j) {
-            const int64_t t = b * a.window + j;
-            if (lane < N) m0 += (double)P[t * N + lane];
-            if (lane + 64 < N) m1 += (double)P[t * N + lane + 64];
-        }
-        m0 /= (double)a.window;
-        m1 /= (double)a.window;
-        acc[4] -= (m0 > 0.0 ? m0 * log(m0) : 0.0) + (m1 > 0.0 ? m1 * log(m1) : 0.0);
+    const int64_t w_lo = chunk * wper, w_hi = (w_lo + wper < n_win) ? w_lo + wper : n_win;
+    __syncthreads();
+    for (int64_t b = w_lo; b < w_hi; ++b) {
+        double m0, m1;
+        window_mean(P, b * a.window, a.window, N, logs, m0, m1);
+        if (wave == 0) acc[4] -= (m0 > 0.0 ? m0 * log(m0) : 0.0) + (m1 > 0.0 ? m1 * log(m1) : 0.0);
     }
 #pragma unroll
     for (int k = 0; k < LS_TERMS; ++k) {
@@ -129,18 +115,20 @@ __global__ __launch_bounds__(LS_WAVES * 64) void loss_partial_kernel(const LossA
     __syncthreads();
     if (threadIdx.x < LS_TERMS) {
         double v = 0.0;
-        for (int w = 0; w < LS_WAVES; ++w) v += part[w][threadIdx.x];
+        for (int w = 0; w < LR_WAVES; ++w) v += part[w][threadIdx.x];
         a.partial[(s * LS_CHUNKS + chunk) * LS_TERMS + threadIdx.x] = v;
     }
 }
 
-__global__ void loss_final_kernel(const LossArgs a, int64_t S)
+// one wavefront per sequence, a lane per chunk
+__global__ __launch_bounds__(64) void loss_final_kernel(const LossArgs a)
 {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= S) return;
-    double sum[LS_TERMS] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int c = 0; c < LS_CHUNKS; ++c)
-        for (int k = 0; k < LS_TERMS; ++k) sum[k] += a.partial[(s * LS_CHUNKS + c) * LS_TERMS + k];
+    const int64_t s = blockIdx.x;
+    const int lane = threadIdx.x;
+    double sum[LS_TERMS];
+#pragma unroll
+    for (int k = 0; k < LS_TERMS; ++k) sum[k] = wsum64(a.partial[(s * LS_CHUNKS + lane) * LS_TERMS + k]);
+    if (lane != 0) return;
     const int64_t T = a.T;
     const double pairs = T > 1 ? (double)(T - 1) : 1.0;
     const int64_t n_win = T / a.window;
@@ -168,10 +156,15 @@ remoe_status launch_loss_forward(const float *probs, const float *probs_ref, con
     a.probs = probs; a.probs_ref = probs_ref; a.idx = idx;
     a.T = T; a.N = N; a.K = K; a.n_lags = n_lags; a.window = window;
     for (int i = 0; i < 8; ++i) a.lags[i] = i < n_lags ? lags[i] : 0;
+    a.blk = plan_rows(N, lags, n_lags, 1);
     a.partial = static_cast<double *>(workspace);
     a.out = out;
-    hipLaunchKernelGGL(loss_partial_kernel, dim3(LS_CHUNKS, (unsigned)S), dim3(LS_WAVES * 64), 0, stream, a);
-    hipLaunchKernelGGL(loss_final_kernel, dim3((unsigned)ceil_div(S, 64)), dim3(64), 0, stream, a, S);
+    const size_t rows_bytes = sizeof(double) * (size_t)a.blk.rows * N, win_bytes = sizeof(double) * LR_WAVES * 128;
+    const size_t lds = rows_bytes > win_bytes ? rows_bytes : win_bytes;
+    const dim3 grid(LS_CHUNKS, (unsigned)S), block(LR_WAVES * 64);
+    if (N <= 64) hipLaunchKernelGGL(loss_partial_kernel<1>, grid, block, lds, stream, a);
+    else hipLaunchKernelGGL(loss_partial_kernel<2>, grid, block, lds, stream, a);
+    hipLaunchKernelGGL(loss_final_kernel, dim3((unsigned)S), dim3(64), 0, stream, a);
     return check_hip(hipGetLastError(), "loss kernels launch");
 }
 

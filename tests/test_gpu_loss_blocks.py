@@ -1,0 +1,38 @@
+"""Router regularisers and their gradient across the blocks of steps their kernels work in, against the oracle.
+
+A block keeps the logarithms of its rows and of the partners within its halo in LDS; partners farther away, zero and
+denormal probabilities, chunks shorter than a block and sequences longer than one take other paths.
+"""
+import pytest
+import torch
+
+import oracle
+import paper_2605_27081_amd as remoe
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("S,T,N,K,window,lags", [
+    (1, 700, 128, 8, 64, [1, 16, 31, 200]), (2, 65, 64, 6, 64, [3, 40]), (1, 9, 65, 3, 2, [1, 8]), (3, 4500, 16, 2, 4500, [2, 90]),
+    (70, 33, 33, 5, 7, []), (1, 2, 128, 1, 1, [1])])
+def test_losses_across_blocks(S, T, N, K, window, lags):
+    print(f"loss blocks S={S} T={T} N={N} window={window} lags={lags}", flush=True)
+    g = torch.Generator().manual_seed(T * 31 + N)
+    P = torch.softmax(1.5 * torch.randn(S, T, N, generator=g), -1)
+    Q = torch.softmax(1.5 * torch.randn(S, T, N, generator=g), -1)
+    P[:, T // 2, N // 2] = P[:, max(T // 2 - 1, 0), N // 2] = 1e-41      # denormal, next to its partner
+    idx = torch.rand(S, T, N, generator=g).topk(K, -1).indices.int()
+    p, q, i = P.to(DEV), Q.to(DEV), idx.to(DEV)
+    vals = torch.empty(S, 6, dtype=torch.float64, device=DEV)
+    dz = torch.empty(S, T, N, device=DEV)
+    remoe.remoe_loss_forward(p, q, i, lags, window, vals, torch.empty(remoe.remoe_loss_workspace_bytes(S), dtype=torch.uint8, device=DEV))
+    coef = [1.0, 0.4, 0.7, 0.3, 0.2]
+    remoe.remoe_loss_backward(p, q, i, lags, window, coef, vals, dz,
+                              torch.empty(remoe.remoe_loss_backward_workspace_bytes(S, T, N, window), dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    want = oracle.remoe_losses(P, Q, idx, lags, window)
+    assert torch.allclose(vals.cpu(), want, rtol=1e-12, atol=1e-14)       # fp64 on both sides, other summation trees
+    grad = oracle.remoe_loss_grad(P, Q, idx, lags, window, coef)
+    err = ((dz.cpu().double() - grad).abs().amax() / grad.abs().amax()).item()
+    assert err <= 1.5e-7, err                                             # one rounding to fp32
