@@ -116,8 +116,8 @@ def main():
     ws3 = torch.empty(remoe.remoe_gate_grad_workspace_bytes(S * T, N, H), dtype=torch.uint8, device=DEV)
     ms = timed(lambda: remoe.remoe_gate_grad(dz.view(S * T, N), x, dw, ws3), args.repeat)
     flops = 2.0 * S * T * N * H
-    line("remoe_gate_grad", ms, flops=flops, tflops=round(flops / ms / 1e9, 1), peak_tflops=157.3,
-         frac=round(flops / ms / 1e9 / 157.3, 3), bound="mfma (fp32)")
+    line("remoe_gate_grad", ms, flops=flops, tflops=round(flops / ms / 1e9, 1), peak_tflops=round(2500.0 / 3, 1),
+         frac=round(3 * flops / ms / 1e9 / 2500.0, 3), bound="mfma (bf16, three products per fp32-accurate one)")
     return 0
 
 

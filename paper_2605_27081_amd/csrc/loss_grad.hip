@@ -21,12 +21,18 @@
 //   sides, lie in LDS (loss_rows.h); one wavefront per step, lane l holding experts l and l + 64; fp64
 //   arithmetic from the fp32 probabilities, fp32 result.  8 sequences x 2048 steps, 64 experts, |D| = 5:
 //   81 us + 19 us for the window logarithms before, 23 us + 5 us now.
-// gate_grad_partial_kernel: dz^T x on the fp32 matrix cores (v_mfma_f32_32x32x2_f32).  Both operands
-//   are read from global memory directly in the instruction's operand layout (lane (i, k) takes
-//   dz[t0 + k][e0 + i] and x[t0 + k][h0 + i]: 32 consecutive floats per half wavefront), so no LDS
-//   staging is needed.  A wavefront owns all experts x 64 hidden columns for a range of tokens; the
-//   four wavefronts of a workgroup add their accumulators through LDS, each workgroup writes its
-//   partial tile, and gate_grad_reduce_kernel adds the partial tiles in a fixed order.
+// gate_grad_bf16_kernel (bf16 hidden states): dz^T x on the bf16 matrix cores.  x is exact in bf16; each fp32
+//   dz is split into three bf16 pieces (hi + mid + lo, 24+ significand bits in all), so that every product is
+//   exact in fp32 and the sums are fp32, as with fp32 instructions but at a fifth of their matrix time.  The
+//   reduction runs over tokens, the slow index of both operands: a lane reads its own column of eight token rows
+//   (4-byte loads, 128 contiguous bytes per half wavefront and row) and packs neighbouring tokens in registers; for
+//   x every 4-byte load is two neighbouring columns, which belong to two MFMA column tiles.  A wavefront owns
+//   64 experts x 128 hidden columns for a range of tokens; the four wavefronts
+//   of a workgroup add their accumulators through LDS and gate_grad_reduce_kernel adds the workgroups' tiles,
+//   both in a fixed order.  16,384 tokens, 64 experts, H 2048: 61 + 9 us with fp32 MFMAs, 27 + 5 us now.
+// gate_grad_partial_kernel (fp32 hidden states): the same on the fp32 matrix cores (v_mfma_f32_32x32x2_f32), both
+//   operands read from global memory directly in the instruction's operand layout (lane (i, k) takes
+//   dz[t0 + k][e0 + i] and x[t0 + k][h0 + i]: 32 consecutive floats per half wavefront).
 #include "common.h"
 #include "loss_rows.h"
 
@@ -153,14 +159,149 @@ struct GateArgs {
 
 // loads through pointers known to point to device memory (global, not flat, address space)
 __device__ __forceinline__ float load_global_f32(const void *p) { return *(const __attribute__((address_space(1))) float *)p; }
-template <class XT> __device__ __forceinline__ float x_as_float(const XT *p);
-template <> __device__ __forceinline__ float x_as_float<float>(const float *p) { return load_global_f32(p); }
-template <> __device__ __forceinline__ float x_as_float<bf16_t>(const bf16_t *p)
+// two neighbouring bf16 values (the row they lie in need not be 4-byte aligned)
+__device__ __forceinline__ uint32_t load_global_bf16x2(const void *p)
 {
-    return __uint_as_float((uint32_t)(*(const __attribute__((address_space(1))) bf16_t *)p) << 16);
+    typedef uint32_t __attribute__((aligned(2))) u32_a2;
+    return *(const __attribute__((address_space(1))) u32_a2 *)p;
 }
 
-template <class XT, int NE>
+// The tokens [t_lo, t_hi) of a wavefront: the workgroup's chunk in equal parts, a multiple of `unit` each.
+__device__ __forceinline__ void wave_tokens(const GateArgs &a, int chunk, int wave, int unit, int64_t &t_lo, int &n_tok)
+{
+    const int64_t per_wg = (a.T + a.chunks - 1) / a.chunks;
+    const int64_t per_wave = ((per_wg + GG_WAVES - 1) / GG_WAVES + unit - 1) / unit * unit;
+    const int64_t wg_lo = chunk * per_wg, wg_hi = (wg_lo + per_wg < a.T) ? wg_lo + per_wg : a.T;
+    t_lo = wg_lo + wave * per_wave;
+    const int64_t t_hi = t_lo + per_wave < wg_hi ? t_lo + per_wave : wg_hi;
+    n_tok = (int)(t_hi > t_lo ? t_hi - t_lo : 0);
+}
+
+// Adds the four wavefronts' accumulators in wavefront order (one at a time through one LDS buffer: a small
+// footprint lets several workgroups share a compute unit); wavefront 0 ends with the sum.
+template <int TILES>
+__device__ __forceinline__ void sum_waves(floatx16_t (&acc)[TILES], float *red, int wave, int lane)
+{
+    for (int w = 1; w < GG_WAVES; ++w) {
+        if (wave == w) {
+#pragma unroll
+            for (int i = 0; i < TILES; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) red[(i * 16 + r) * 64 + lane] = acc[i][r];
+        }
+        __syncthreads();
+        if (wave == 0) {
+#pragma unroll
+            for (int i = 0; i < TILES; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][r] += red[(i * 16 + r) * 64 + lane];
+        }
+        __syncthreads();
+    }
+}
+
+// NE: 32-row tiles of experts; NP: pairs of 32-column tiles (64 hidden columns each)
+template <int NE, int NP>
+__global__ __launch_bounds__(GG_WAVES * 64, 2) void gate_grad_bf16_kernel(const GateArgs a)
+{
+    __shared__ float red[NE * NP * 2 * 16 * 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int li = lane & 31, lh = lane >> 5;
+    const int h0 = blockIdx.x * NP * 64, e0 = blockIdx.z * NE * 32;
+    const int N = a.N, H = a.H;
+    floatx16_t acc[NE * NP * 2];
+#pragma unroll
+    for (int i = 0; i < NE * NP * 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+
+    int64_t t_lo;
+    int n_tok;
+    wave_tokens(a, blockIdx.y, wave, 16, t_lo, n_tok);
+    const char *dz_w = reinterpret_cast<const char *>(a.dz + t_lo * N);
+    const char *x_w = reinterpret_cast<const char *>(static_cast<const bf16_t *>(a.x) + t_lo * H + h0);
+    uint32_t dz_col[NE], x_col[NP];
+    float live_e[NE];
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+        const int col = e0 + e * 32 + li;
+        dz_col[e] = (uint32_t)(col < N ? col : N - 1) * 4u;
+        live_e[e] = col < N ? 1.0f : 0.f;
+    }
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        const int col = h0 + p * 64 + 2 * li < H ? p * 64 + 2 * li : 0;      // a ragged last block: columns past H are not stored
+        x_col[p] = (uint32_t)col * 2u;
+    }
+
+    // 16 tokens per pass: the lane's eight are 16 i + 8 lh + {0..7}.  Tokens past the end repeat the last
+    // one with a factor 0 on dz; the loads of the next pass are in flight during the MFMAs of this one.
+    float dv[NE][8];
+    uint32_t xv[NP][8];
+#define GB_LOAD(i)                                                                                              \
+    _Pragma("unroll") for (int j = 0; j < 8; ++j) {                                                             \
+        const int t_ = 16 * (i) + 8 * lh + j;                                                                   \
+        const uint32_t tc_ = (uint32_t)(t_ < n_tok ? t_ : n_tok - 1);                                           \
+        _Pragma("unroll") for (int e = 0; e < NE; ++e) dv[e][j] = load_global_f32(dz_w + tc_ * (uint32_t)N * 4u + dz_col[e]); \
+        _Pragma("unroll") for (int p = 0; p < NP; ++p) xv[p][j] = load_global_bf16x2(x_w + tc_ * (uint32_t)H * 2u + x_col[p]);    \
+    }
+    const int passes = (n_tok + 15) >> 4;
+    if (passes > 0) { GB_LOAD(0) }
+#pragma unroll 1
+    for (int i = 0; i < passes; ++i) {
+        u32x4_t piece[NE][3], col[NP][2];
+        const int left = n_tok - 16 * i - 8 * lh;             // live tokens of this lane's eight
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float w0 = 2 * q < left ? dv[e][2 * q] * live_e[e] : 0.f, w1 = 2 * q + 1 < left ? dv[e][2 * q + 1] * live_e[e] : 0.f;
+                const uint32_t hi = pack_bf16x2(w0, w1);
+                const float r0 = w0 - __uint_as_float(hi << 16), r1 = w1 - __uint_as_float(hi & 0xFFFF0000u);
+                const uint32_t mid = pack_bf16x2(r0, r1);
+                piece[e][0][q] = hi;
+                piece[e][1][q] = mid;
+                piece[e][2][q] = pack_bf16x2(r0 - __uint_as_float(mid << 16), r1 - __uint_as_float(mid & 0xFFFF0000u));
+            }
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                col[p][0][q] = __builtin_amdgcn_perm(xv[p][2 * q + 1], xv[p][2 * q], 0x05040100u);       // low halves: column 2 li
+                col[p][1][q] = __builtin_amdgcn_perm(xv[p][2 * q + 1], xv[p][2 * q], 0x07060302u);       // high halves: column 2 li + 1
+            }
+        __builtin_amdgcn_sched_barrier(0);
+        if (i + 1 < passes) { GB_LOAD(i + 1) }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int pc = 0; pc < 3; ++pc)
+#pragma unroll
+            for (int e = 0; e < NE; ++e)
+#pragma unroll
+                for (int p = 0; p < NP * 2; ++p)
+                    acc[e * NP * 2 + p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, piece[e][pc]),
+                                                                                 __builtin_bit_cast(bf16x8_t, col[p >> 1][p & 1]),
+                                                                                 acc[e * NP * 2 + p], 0, 0, 0);
+    }
+#undef GB_LOAD
+    sum_waves(acc, red, wave, lane);
+    if (wave == 0) {
+        float *out = a.partial + (int64_t)blockIdx.y * N * H;
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int row = e0 + e * 32 + (r >> 2) * 8 + lh * 4 + (r & 3), c = h0 + p * 64 + 2 * li;     // expert, first column
+                    if (row < N && c < H)
+                        *reinterpret_cast<float2 *>(out + (int64_t)row * H + c) =
+                            make_float2(acc[e * NP * 2 + 2 * p][r], acc[e * NP * 2 + 2 * p + 1][r]);
+                }
+    }
+}
+
+template <int NE>
 __global__ __launch_bounds__(GG_WAVES * 64) void gate_grad_partial_kernel(const GateArgs a)
 {
     __shared__ float red[NE * GG_NH * 16 * 64];   // one wavefront's accumulators at a time
@@ -169,7 +310,7 @@ __global__ __launch_bounds__(GG_WAVES * 64) void gate_grad_partial_kernel(const 
     const int h0 = blockIdx.x * GG_COLS;
     const int chunk = blockIdx.y;
     const int N = a.N, H = a.H;
-    const XT *x = static_cast<const XT *>(a.x);
+    const float *x = static_cast<const float *>(a.x);
 
     floatx16_t acc[NE][GG_NH];
 #pragma unroll
@@ -179,12 +320,9 @@ __global__ __launch_bounds__(GG_WAVES * 64) void gate_grad_partial_kernel(const 
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[e][n][r] = 0.f;
 
-    // this wavefront's tokens: an even number per wavefront so that token pairs never straddle
-    const int64_t per_wg = (a.T + a.chunks - 1) / a.chunks;
-    const int64_t per_wave = ((per_wg + GG_WAVES - 1) / GG_WAVES + 1) & ~(int64_t)1;
-    const int64_t wg_lo = chunk * per_wg, wg_hi = (wg_lo + per_wg < a.T) ? wg_lo + per_wg : a.T;
-    int64_t t_lo = wg_lo + wave * per_wave, t_hi = t_lo + per_wave;
-    if (t_hi > wg_hi) t_hi = wg_hi;
+    int64_t t_lo;
+    int n_tok;
+    wave_tokens(a, chunk, wave, 2, t_lo, n_tok);       // an even number per wavefront so that token pairs never straddle
 
     // GG_UN token pairs per pass.  The operand loads of the next pass are issued before the MFMAs of
     // the current one (two register sets), so that a wavefront alone on its SIMD still overlaps load
@@ -192,7 +330,6 @@ __global__ __launch_bounds__(GG_WAVES * 64) void gate_grad_partial_kernel(const 
     // multiplication: a conditional load is a branch, and behind every branch the compiler waits for
     // all loads in flight.  (What a masked load reads is other tokens' or experts' data of the same call.)
     constexpr int GG_UN = 2;
-    const int n_tok = (int)(t_hi > t_lo ? t_hi - t_lo : 0);
     const int n_pairs = (n_tok + 1) >> 1;
     const char *dz_w = reinterpret_cast<const char *>(a.dz + t_lo * N);
     const char *x_w = reinterpret_cast<const char *>(x + t_lo * H + h0);
@@ -211,7 +348,7 @@ __global__ __launch_bounds__(GG_WAVES * 64) void gate_grad_partial_kernel(const 
         _Pragma("unroll") for (int e = 0; e < NE; ++e)                                                   \
             av[u][e] = load_global_f32(dz_w + (uint32_t)(tc_ * N) * 4u + dz_col[e]);                     \
         _Pragma("unroll") for (int n = 0; n < GG_NH; ++n)                                                \
-            bv[u][n] = x_as_float<XT>(reinterpret_cast<const XT *>(x_w + (uint32_t)(tc_ * H + n * 32 + li) * (uint32_t)sizeof(XT))); \
+            bv[u][n] = load_global_f32(x_w + (uint32_t)(tc_ * H + n * 32 + li) * 4u);                     \
     }
     // the masks are applied here, not where the values are requested: a use right behind a load is a wait
 #define GG_MFMA(av, bv, first_pair)                                                                      \
@@ -239,29 +376,7 @@ __global__ __launch_bounds__(GG_WAVES * 64) void gate_grad_partial_kernel(const 
 #undef GG_LOAD
 #undef GG_MFMA
 
-    // add the four wavefronts' accumulators in wavefront order (one at a time through one LDS buffer:
-    // a small LDS footprint lets several workgroups share a compute unit and hide each other's load
-    // latency), then write the workgroup's tile
-    for (int w = 1; w < GG_WAVES; ++w) {
-        if (wave == w) {
-#pragma unroll
-            for (int e = 0; e < NE; ++e)
-#pragma unroll
-                for (int n = 0; n < GG_NH; ++n)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) red[((e * GG_NH + n) * 16 + r) * 64 + lane] = acc[e][n][r];
-        }
-        __syncthreads();
-        if (wave == 0) {
-#pragma unroll
-            for (int e = 0; e < NE; ++e)
-#pragma unroll
-                for (int n = 0; n < GG_NH; ++n)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[e][n][r] += red[((e * GG_NH + n) * 16 + r) * 64 + lane];
-        }
-        __syncthreads();
-    }
+    sum_waves(reinterpret_cast<floatx16_t (&)[NE * GG_NH]>(acc), red, wave, lane);
     if (wave == 0) {
         float *out = a.partial + (int64_t)chunk * N * H;
 #pragma unroll
@@ -282,6 +397,7 @@ __global__ void gate_grad_reduce_kernel(const GateArgs a)
     const int64_t total = (int64_t)a.N * a.H;
     if (q >= total) return;
     float v = 0.f;
+#pragma unroll 8
     for (int c = 0; c < a.chunks; ++c) v += a.partial[(int64_t)c * total + q];
     a.dw[q] = v;
 }
@@ -350,17 +466,22 @@ remoe_status launch_gate_grad(const float *dz, const void *x, int x_dtype, int64
     a.chunks = gate_grad_chunks(T, H);
     a.partial = static_cast<float *>(workspace);
     a.dw = dw;
-    const dim3 grid((unsigned)(H / GG_COLS), (unsigned)a.chunks), block(GG_WAVES * 64);
+    const dim3 block(GG_WAVES * 64);
     const int ne = (N + 31) / 32;
-#define GG_LAUNCH(XT)                                                                                              \
-    switch (ne) {                                                                                                  \
-    case 1: hipLaunchKernelGGL((gate_grad_partial_kernel<XT, 1>), grid, block, 0, stream, a); break;               \
-    case 2: hipLaunchKernelGGL((gate_grad_partial_kernel<XT, 2>), grid, block, 0, stream, a); break;               \
-    case 3: hipLaunchKernelGGL((gate_grad_partial_kernel<XT, 3>), grid, block, 0, stream, a); break;               \
-    default: hipLaunchKernelGGL((gate_grad_partial_kernel<XT, 4>), grid, block, 0, stream, a); break;              \
+    if (x_dtype == REMOE_BF16) {
+        // more than 64 experts in two passes over x: four expert tiles with both operands' next loads do not fit the registers
+        const dim3 grid((unsigned)ceil_div(H, 128), (unsigned)a.chunks, (unsigned)ceil_div(ne, 2));
+        if (ne == 1) hipLaunchKernelGGL((gate_grad_bf16_kernel<1, 2>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((gate_grad_bf16_kernel<2, 2>), grid, block, 0, stream, a);
+    } else {
+        const dim3 grid((unsigned)(H / GG_COLS), (unsigned)a.chunks);
+        switch (ne) {
+        case 1: hipLaunchKernelGGL(gate_grad_partial_kernel<1>, grid, block, 0, stream, a); break;
+        case 2: hipLaunchKernelGGL(gate_grad_partial_kernel<2>, grid, block, 0, stream, a); break;
+        case 3: hipLaunchKernelGGL(gate_grad_partial_kernel<3>, grid, block, 0, stream, a); break;
+        default: hipLaunchKernelGGL(gate_grad_partial_kernel<4>, grid, block, 0, stream, a); break;
+        }
     }
-    if (x_dtype == REMOE_BF16) { GG_LAUNCH(bf16_t) } else { GG_LAUNCH(float) }
-#undef GG_LAUNCH
     const int64_t total = (int64_t)N * H;
     hipLaunchKernelGGL(gate_grad_reduce_kernel, dim3((unsigned)ceil_div(total, 256)), dim3(256), 0, stream, a);
     return check_hip(hipGetLastError(), "gate gradient kernels launch");
