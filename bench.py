@@ -197,9 +197,8 @@ def main():
     layer_tflops = flops_step / (elapsed / args.steps) / 1e12
 
     # ---- roofline of the dominant kernel: routed gate/up GEMM + SwiGLU ------------------------
-    # algorithmic flops per launch (bf16 layers run the shared expert's tiles in the routed experts' launches)
-    shared_inter = cfg.shared_inter if cfg.dtype == "bf16" else 0
-    gate_up_flops = 2.0 * T * H * 2 * (K * cfg.inter + shared_inter)
+    # algorithmic flops per launch (the shared expert's tiles run in the routed experts' launches)
+    gate_up_flops = 2.0 * T * H * 2 * (K * cfg.inter + cfg.shared_inter)
     dom = prof.get("gate_up")
     roofline = None
     if dom:
@@ -224,7 +223,7 @@ def main():
     if cfg.dtype == "bf16":
         es = 2
         work = {
-            "down": ("mfma", 2.0 * T * (K * cfg.inter + shared_inter) * H, BF16_MFMA_PEAK_TFLOPS, 1e12, "TFLOP/s"),
+            "down": ("mfma", 2.0 * T * (K * cfg.inter + cfg.shared_inter) * H, BF16_MFMA_PEAK_TFLOPS, 1e12, "TFLOP/s"),
             # K (+1 with a shared expert) rows of H values read per token, one written
             "combine": ("hbm", float(T) * (K + (2 if cfg.shared_inter else 1)) * H * es, HBM_PEAK_GBS, 1e9, "GB/s"),
             # the hidden states once and the gate matrix once; the routing out

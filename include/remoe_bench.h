@@ -25,10 +25,10 @@ extern "C" {
 typedef enum {
     REMOE_PROF_ROUTE = 0,          /* router GEMM + top-k + softmax                  */
     REMOE_PROF_PERMUTE = 1,        /* token -> expert sort and tile list             */
-    REMOE_PROF_GATE_UP = 2,        /* gate/up GEMM + SwiGLU (bf16: with the shared expert's) */
-    REMOE_PROF_DOWN = 3,           /* down GEMM (bf16: with the shared expert's)     */
-    REMOE_PROF_SHARED_GATE_UP = 4, /* shared expert of fp32 layers: gate/up GEMM + SwiGLU */
-    REMOE_PROF_SHARED_DOWN = 5,    /* shared expert of fp32 layers: down GEMM        */
+    REMOE_PROF_GATE_UP = 2,        /* gate/up GEMM + SwiGLU, routed and shared       */
+    REMOE_PROF_DOWN = 3,           /* down GEMM, routed and shared                   */
+    REMOE_PROF_SHARED_GATE_UP = 4, /* unused (the shared expert runs in the launches above) */
+    REMOE_PROF_SHARED_DOWN = 5,    /* unused                                         */
     REMOE_PROF_COMBINE = 6,        /* sum of a token's rows                          */
     REMOE_PROF_TRACE_REUSE = 7,    /* adjacent-step overlap                          */
     REMOE_PROF_LRU = 8,            /* LRU cache misses                               */

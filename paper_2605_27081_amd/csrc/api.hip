@@ -145,6 +145,7 @@ struct Workspace {
     void *hsbuf = nullptr;    // [T, I_s]            SwiGLU activations of the shared expert
     void *rows = nullptr;     // [T*K (+T), H]       weighted per-(token, expert) outputs, then shared rows
     int tile_m = 0;           // rows of a GEMM row tile
+    int h_pitch = 0, hs_pitch = 0;   // row pitches of hbuf, hsbuf
     int max_tiles = 0;
 };
 
@@ -175,7 +176,8 @@ int forward_tile_m(const remoe_layer_desc *d, int64_t T)
                (double)(ceil_div(T, m) * ceil_div(d->shared_inter, 128));
     };
     constexpr double ENOUGH = 256 * 5 / 8;
-    if (d->dtype == REMOE_F32 || (rows >= 120.0 && tiles(256) >= ENOUGH)) return gemm_tile_m();
+    if (d->dtype == REMOE_F32) return rows >= 24.0 && tiles(64) >= 2 * ENOUGH ? 64 : 32;
+    if (rows >= 120.0 && tiles(256) >= ENOUGH) return gemm_tile_m();
     if (rows >= 40.0 && tiles(128) >= ENOUGH) return 128;
     return rows > 6.0 ? 64 : 32;
 }
@@ -185,6 +187,8 @@ Workspace layout(const remoe_layer_desc *d, int64_t T, void *base_v)
     Workspace w;
     char *base = static_cast<char *>(base_v);
     const size_t es = d->dtype == REMOE_F32 ? 4 : 2;
+    w.h_pitch = (int)align_up(d->inter, 32);          // bf16 sizes are multiples of 64 already
+    w.hs_pitch = (int)align_up(d->shared_inter, 32);
     const int64_t pairs = T * d->top_k;
     const int64_t n_blk = ceil_div(T, permute_tokens_per_block());
     w.tile_m = forward_tile_m(d, T);
@@ -199,9 +203,8 @@ Workspace layout(const remoe_layer_desc *d, int64_t T, void *base_v)
     carve(base, off, w.pb.gemm_ctr, sizeof(uint32_t) * GEMM_CTR_SETS * 8);
     carve(base, off, w.pb.pair_slot, sizeof(int32_t) * pairs);
     carve(base, off, w.pb.slot_token, sizeof(int32_t) * pairs);
-    carve(base, off, w.pb.slot_w, sizeof(float) * pairs);
-    carve(base, off, w.hbuf, es * pairs * d->inter);
-    carve(base, off, w.hsbuf, es * T * d->shared_inter);
+    carve(base, off, w.hbuf, es * pairs * w.h_pitch);
+    carve(base, off, w.hsbuf, es * T * w.hs_pitch);
     carve(base, off, w.rows, es * (pairs + (d->shared_inter ? T : 0)) * d->hidden);
     w.total = align_up(off, 256);
     return w;
@@ -366,7 +369,6 @@ remoe_status moe_forward(const remoe_layer_desc *desc, const void *x, int64_t n_
 
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     const int H = desc->hidden, I = desc->inter, Is = desc->shared_inter, K = desc->top_k, N = desc->n_experts;
-    const bool f32 = desc->dtype == REMOE_F32;
     // 1. router: logits, top-k, softmax weights
     {
         ProfScope prof(REMOE_PROF_ROUTE, stream);
@@ -376,50 +378,43 @@ remoe_status moe_forward(const remoe_layer_desc *desc, const void *x, int64_t n_
     // 2. sort (token, j) pairs by expert; build the GEMM tile list
     {
         ProfScope prof(REMOE_PROF_PERMUTE, stream);
-        st = launch_permute(out_idx, out_w, T, K, N, ws.tile_m, ws.max_tiles, ws.pb, stream);
+        st = launch_permute(out_idx, T, K, N, ws.tile_m, ws.max_tiles, ws.pb, stream);
     }
     if (st != REMOE_OK) return st;
-    // 3. routed experts: gate/up + SwiGLU, then the down projection (the fp32 kernel also applies the gate weight)
+    // 3. routed experts: gate/up + SwiGLU, then the down projection (the combine step applies the gate weights)
     // 4. shared expert (dense, one group): rows T*K .. T*K+T-1 of the row buffer
     GroupedGemmArgs g{}, s{};
     g.a = x; g.lda = H; g.a_rows = T; g.row_gather = ws.pb.slot_token;
     g.b0 = w_gate; g.b1 = w_up; g.k_dim = H; g.n_out = I;
     g.tile_expert = ws.pb.tile_expert; g.tile_row0 = ws.pb.tile_row0; g.tile_rows = ws.pb.tile_rows;
     g.n_tiles = ws.pb.n_tiles; g.max_tiles = ws.max_tiles;
-    g.c = ws.hbuf; g.ldc = I; g.c_row_offset = 0;
+    g.c = ws.hbuf; g.ldc = ws.h_pitch; g.c_row_offset = 0;
     g.tile_ctr = ws.pb.gemm_ctr;
     s.a = x; s.lda = H; s.a_rows = T; s.b0 = ws_gate; s.b1 = ws_up; s.k_dim = H; s.n_out = Is;
     s.dense_rows = T; s.max_tiles = (int)ceil_div(T, ws.tile_m);
-    s.c = ws.hsbuf; s.ldc = Is;
+    s.c = ws.hsbuf; s.ldc = ws.hs_pitch;
     s.tile_ctr = ws.pb.gemm_ctr + 16;
-    // bf16: routed and shared tiles in one launch (timed as the routed kind); fp32: one launch each
-    auto gemm = [&](int mode, int kind, int shared_kind) {
-        {
-            ProfScope prof(kind, stream);
-            const GroupedGemmArgs *both = Is > 0 ? &s : nullptr;
-            const remoe_status st_ = f32 ? launch_grouped_gemm_f32(mode, g, stream)
-                                     : ws.tile_m < gemm_tile_m() ? launch_stream_gemm(mode, g, both, ws.tile_m, stream)
-                                                                 : launch_grouped_gemm_bf16(mode, g, both, stream);
-            if (st_ != REMOE_OK || !f32 || Is == 0) return st_;
-        }
-        ProfScope prof(shared_kind, stream);
-        return launch_grouped_gemm_f32(mode, s, stream);
+    // routed and shared tiles in one launch
+    auto gemm = [&](int mode, int kind) {
+        const GroupedGemmArgs *both = Is > 0 ? &s : nullptr;
+        ProfScope prof(kind, stream);
+        return ws.tile_m < gemm_tile_m() ? launch_stream_gemm(desc->dtype, mode, g, both, ws.tile_m, stream)
+                                         : launch_grouped_gemm_bf16(mode, g, both, stream);
     };
-    st = gemm(0, REMOE_PROF_GATE_UP, REMOE_PROF_SHARED_GATE_UP);
+    st = gemm(0, REMOE_PROF_GATE_UP);
     if (st != REMOE_OK) return st;
-    g.a = ws.hbuf; g.lda = I; g.a_rows = T * K; g.row_gather = nullptr;
+    g.a = ws.hbuf; g.lda = ws.h_pitch; g.a_rows = T * K; g.row_gather = nullptr;
     g.b0 = w_down; g.b1 = nullptr; g.k_dim = I; g.n_out = H;
-    g.row_scale = f32 ? ws.pb.slot_w : nullptr;   // bf16: the combine step applies the gate weights
     g.c = ws.rows; g.ldc = H;
     g.tile_ctr = ws.pb.gemm_ctr + 8;
-    s.a = ws.hsbuf; s.lda = Is; s.a_rows = T; s.b0 = ws_down; s.b1 = nullptr; s.k_dim = Is; s.n_out = H;
+    s.a = ws.hsbuf; s.lda = ws.hs_pitch; s.a_rows = T; s.b0 = ws_down; s.b1 = nullptr; s.k_dim = Is; s.n_out = H;
     s.c = ws.rows; s.ldc = H; s.c_row_offset = T * K;
     s.tile_ctr = ws.pb.gemm_ctr + 24;
-    st = gemm(1, REMOE_PROF_DOWN, REMOE_PROF_SHARED_DOWN);
+    st = gemm(1, REMOE_PROF_DOWN);
     if (st != REMOE_OK) return st;
     // 5. combine the K (+1) rows of every token
     ProfScope prof(REMOE_PROF_COMBINE, stream);
-    return launch_combine(desc->dtype, ws.rows, ws.pb.pair_slot, f32 ? nullptr : out_w, T, K, H, T * K, Is > 0, x,
+    return launch_combine(desc->dtype, ws.rows, ws.pb.pair_slot, out_w, T, K, H, T * K, Is > 0, x,
                           desc->shared_gate ? ws_scale : nullptr, y, stream);
 }
 

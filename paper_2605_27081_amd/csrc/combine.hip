@@ -2,9 +2,7 @@
 //
 // The routed part is the sum of the token's K rows, each weighted by its gate weight P_t[e]
 // (Sec. 3.1), found through the pair -> slot map of the permute step and taken in routing order
-// (descending logit).  The weights come from pair_w in (token, j) order; where pair_w is NULL the
-// down-projection kernel has already applied them (the fp32 path) and the rows are summed as they
-// are.  The shared
+// (descending logit).  The weights come from pair_w in (token, j) order.  The shared
 // expert's row (always active, outside P_t) is added last, scaled by s_t = sigmoid(ws_scale . x[t])
 // when the layer gates its shared expert.  One workgroup per token; the sum order is fixed, so the
 // result is deterministic.
@@ -85,7 +83,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const ET *__restrict__ row
     for (int j = 0; j < 8; ++j) slot[j] = (j < K) ? pair_slot[t * K + j] : 0;
     float wj[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) wj[j] = (j < K && pair_w) ? pair_w[t * K + j] : 1.0f;
+    for (int j = 0; j < 8; ++j) wj[j] = j < K ? pair_w[t * K + j] : 0.0f;
     for (int c = tid; c < H / V; c += 256) {
         float acc[V];
 #pragma unroll

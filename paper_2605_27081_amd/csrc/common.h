@@ -84,15 +84,14 @@ struct PermuteBuffers {
     int32_t *n_tiles;      // [1]
     int32_t *pair_slot;    // [T*K]        (token, j) -> slot
     int32_t *slot_token;   // [T*K]        slot -> token
-    float *slot_w;         // [T*K]        slot -> gate weight
     uint32_t *gemm_ctr;    // [GEMM_CTR_SETS * 8] tile counters of the layer's GEMM launches, zeroed by the permute step
 };
 constexpr int GEMM_CTR_SETS = 4;
 int permute_tokens_per_block();
-remoe_status launch_permute(const int32_t *idx, const float *w, int64_t T, int K, int N,
+remoe_status launch_permute(const int32_t *idx, int64_t T, int K, int N,
                             int tile_m, int max_tiles, const PermuteBuffers &pb, hipStream_t stream);
 
-// Grouped expert GEMMs.  mode 0: gate/up + SwiGLU, mode 1: down projection scaled per row.
+// Grouped expert GEMMs.  mode 0: gate/up + SwiGLU, mode 1: down projection.
 struct GroupedGemmArgs {
     const void *a;            // activations [a_rows, lda]
     int64_t lda;
@@ -105,7 +104,6 @@ struct GroupedGemmArgs {
     const int32_t *tile_expert, *tile_row0, *tile_rows, *n_tiles;  // NULL => dense, single group
     int64_t dense_rows;       // rows when dense
     int max_tiles;            // m-tiles launched
-    const float *row_scale;   // mode 1: per output row factor, or NULL
     void *c;                  // output [rows, ldc]
     int64_t ldc;
     int64_t c_row_offset;     // added to the output row index
@@ -114,11 +112,11 @@ struct GroupedGemmArgs {
 int gemm_tile_m();
 // bf16, row tiles of gemm_tile_m() slots; the shared expert (or NULL) runs in the same launch.
 remoe_status launch_grouped_gemm_bf16(int mode, const GroupedGemmArgs &routed, const GroupedGemmArgs *shared, hipStream_t stream);
-// The same for row tiles of tile_m = 32, 64 or 128 slots.
-remoe_status launch_stream_gemm(int mode, const GroupedGemmArgs &routed, const GroupedGemmArgs *shared, int tile_m, hipStream_t stream);
-remoe_status launch_grouped_gemm_f32(int mode, const GroupedGemmArgs &g, hipStream_t stream);
+// The same for row tiles of tile_m = 32, 64 or (bf16) 128 slots, both data types.  fp32: row pitches (lda, ldc) are
+// multiples of 32 and the columns of c past n_out are written as zeros in mode 0.
+remoe_status launch_stream_gemm(int dtype, int mode, const GroupedGemmArgs &routed, const GroupedGemmArgs *shared, int tile_m, hipStream_t stream);
 
-// y[t] = sum_j rows[pair_slot[t*K+j]] + s_t * rows[shared_row0 + t]
+// y[t] = sum_j pair_w[t*K+j] * rows[pair_slot[t*K+j]] + s_t * rows[shared_row0 + t]
 remoe_status launch_combine(int dtype, const void *rows, const int32_t *pair_slot, const float *pair_w, int64_t T, int K,
                             int H, int64_t shared_row0, int has_shared, const void *x,
                             const float *ws_scale, void *y, hipStream_t stream);

@@ -584,7 +584,6 @@ remoe_status launch_grouped_gemm_bf16(int mode, const GroupedGemmArgs &routed, c
         if (g.ldc * 2 * CFG_BM >= (int64_t)1 << 32 || g.n_out % 8 != 0)
             return fail(REMOE_E_UNSUPPORTED, "bf16 GEMM output needs n %% 8 == 0 and a row pitch below 8 Mi elements (n=%d ldc=%lld)",
                         g.n_out, (long long)g.ldc);
-        if (g.row_scale) return fail(REMOE_E_INVALID_ARG, "the bf16 GEMM applies no row factors (the combine step does)");
         if (g.max_tiles <= 0) continue;
         KArgs &p = groups.g[groups.n++];
         p.a = static_cast<const bf16_t *>(g.a);

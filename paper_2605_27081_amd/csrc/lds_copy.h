@@ -6,7 +6,7 @@
 namespace remoe {
 
 // 64 lanes x 16 bytes, global -> LDS without passing through registers: lane l's 16 bytes, read from
-// base + off (wave-uniform 64-bit base, per-lane 32-bit byte offset), land at lds_base + 16 l
+// base + off (wave-uniform 64-bit base, per-lane byte offset), land at lds_base + 16 l
 // (lds_base wave-uniform, handed over in M0).  Written as assembly so that the compiler keeps no
 // books on these copies: its own bookkeeping makes every later LDS read wait for all of them,
 // which would undo the overlap.  Every wait for such a copy is therefore explicit.
@@ -20,7 +20,7 @@ namespace remoe {
 //   * M0 is written inside the block and the one wait state the copy needs behind that write is
 //     part of the block.  Nothing else in these kernels touches M0 (the compiler reserves it and has
 //     no use for it there; a host-side test of the grouped GEMM's generated code checks that).
-__device__ __forceinline__ void copy16_to_lds(const char *base, uint32_t off, const void *lds_base)
+template <typename Offset> __device__ __forceinline__ void copy16_to_lds(const char *base, Offset off, const void *lds_base)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     const uint32_t dst = (uint32_t)(uintptr_t)lds_base;   // the low 32 bits of a generic LDS pointer are the LDS offset

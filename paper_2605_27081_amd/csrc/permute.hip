@@ -8,8 +8,8 @@
 //                      workgroup's expert histogram;
 //   2. permute_scan  : one workgroup turns the histograms into per-workgroup offsets, the
 //                      exclusive prefix sum over experts and the list of GEMM row tiles;
-//   3. permute_place : slot = offset[expert] + block offset + rank; writes slot -> token,
-//                      slot -> gate weight and pair -> slot.
+//   3. permute_place : slot = offset[expert] + block offset + rank; writes slot -> token and
+//                      pair -> slot.
 #include "common.h"
 
 namespace remoe {
@@ -114,13 +114,12 @@ __global__ __launch_bounds__(PS_SEG * 128) void permute_scan(const int32_t *__re
 }
 
 __global__ __launch_bounds__(256) void permute_place(const int32_t *__restrict__ idx,
-                                                     const float *__restrict__ w, int64_t n_pairs,
+                                                     int64_t n_pairs,
                                                      int K, int N,
                                                      const int32_t *__restrict__ blk_off,
                                                      const int32_t *__restrict__ offsets,
                                                      int32_t *__restrict__ pair_slot,
-                                                     int32_t *__restrict__ slot_token,
-                                                     float *__restrict__ slot_w)
+                                                     int32_t *__restrict__ slot_token)
 {
     const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (p >= n_pairs) return;
@@ -129,14 +128,13 @@ __global__ __launch_bounds__(256) void permute_place(const int32_t *__restrict__
     const int slot = offsets[e] + blk_off[(t / PM_TOKENS) * N + e] + pair_slot[p];
     pair_slot[p] = slot;
     slot_token[slot] = (int32_t)t;
-    slot_w[slot] = w[p];
 }
 
 }  // namespace
 
 int permute_tokens_per_block() { return PM_TOKENS; }
 
-remoe_status launch_permute(const int32_t *idx, const float *w, int64_t T, int K, int N,
+remoe_status launch_permute(const int32_t *idx, int64_t T, int K, int N,
                             int tile_m, int max_tiles, const PermuteBuffers &pb, hipStream_t stream)
 {
     if (T == 0) return REMOE_OK;
@@ -150,7 +148,7 @@ remoe_status launch_permute(const int32_t *idx, const float *w, int64_t T, int K
                        pb.n_tiles, pb.gemm_ctr);
     const int64_t n_pairs = T * K;
     hipLaunchKernelGGL(permute_place, dim3((unsigned)ceil_div(n_pairs, 256)), dim3(256), 0, stream, idx,
-                       w, n_pairs, K, N, blk_off, pb.offsets, pb.pair_slot, pb.slot_token, pb.slot_w);
+                       n_pairs, K, N, blk_off, pb.offsets, pb.pair_slot, pb.slot_token);
     return check_hip(hipGetLastError(), "permute launch");
 }
 
