@@ -26,7 +26,8 @@
 // weight row and the other entries behind them.
 //
 // 16 traces x 4096 steps, 128 experts, top-8, C = 4: 7.5 ms as one walk of K maxima per step and wavefront,
-// 0.26 ms now (lists 37, walk 207, weights 15 us).
+// 0.19 ms now (lists 37, walk 140, weights 15 us; the
+// walk is bound by the instructions its 16 wavefronts issue: 1.8 us a step before, 0.45 us now with 16 steps at once).
 #include "common.h"
 #include "topk.h"
 
@@ -183,11 +184,20 @@ __device__ __forceinline__ int below(u64 mask)
 #endif
 }
 
+// The n-th expert (from 0) of a set with more than n: in0 says whether expert `lane` is in it, in1 expert `lane` + 64.
+__device__ __forceinline__ int nth(bool in0, bool in1, int n)
+{
+    const u64 g0 = ballot(in0), g1 = ballot(in1);
+    const int n0 = __popcll(g0);
+    if (n < n0) return __ffsll((long long)ballot(in0 & (below(g0) == n))) - 1;
+    return 63 + __ffsll((long long)ballot(in1 & (n0 + below(g1) == n)));
+}
+
 // One stretch [t0, t1) of a trace from the state in (keys, st).  keys[e] = (step of last use + 1) << 7 | e, 0 =
 // never used; slots 128 + lane take the writes of lanes without an expert.  STORE: marks, misses and
-// the ids of steps without a list are written.  Returns the misses.
-template <bool WIDE, bool STORE>
-__device__ __forceinline__ u64 walk(const float *__restrict__ probs, int64_t s, int64_t T, int64_t t0, int64_t t1, int N, int C, float factor,
+// the ids of steps without a list are written.  FULL: K >= C.  Returns the misses that this lane counted.
+template <bool WIDE, bool FULL, bool STORE>
+__device__ __forceinline__ uint32_t walk(const float *__restrict__ probs, int64_t s, int64_t T, int64_t t0, int64_t t1, int N, int C, float factor,
                     const RowLayout lay, int32_t *out_idx, float *out_w, uint8_t *out_miss, uint32_t *keys,
                     uint8_t *lists, WalkState &st)
 {
@@ -195,7 +205,7 @@ __device__ __forceinline__ u64 walk(const float *__restrict__ probs, int64_t s, 
     const bool has = lane < lay.entries;
     uint32_t cut = st.cut;
     int held = st.held;
-    u64 total = 0;
+    uint32_t lane_misses = 0;
     uint32_t next[RR_BATCH];            // the lists of the next batch, a byte per lane and step
     typedef const __attribute__((address_space(1))) uint8_t *global_bytes;
     global_bytes list = (global_bytes)lay.entry(out_idx, out_w, s * T + t0, has ? lane : 0);
@@ -219,25 +229,24 @@ __device__ __forceinline__ u64 walk(const float *__restrict__ probs, int64_t s, 
         asm volatile("" ::: "memory");
         const int n = (int)(t1 - tb < RR_BATCH ? t1 - tb : RR_BATCH);
         fetch();
+        // bit a: step tb + a has no list
+        const uint32_t no_list = (uint32_t)ballot(lane < RR_BATCH && lists[lane * 64] == lists[lane * 64 + 1]);
         uint32_t b = lists[lane];
         uint32_t kr = keys[b & 127u];
         uint32_t o_lo = 0, o_hi = 0, o_miss = 0;              // marks and misses of step tb + lane
         for (int a = 0; a < n; ++a) {
-            const uint32_t t = (uint32_t)(tb + a);
-            const uint32_t b_next = lists[(a + 1 < RR_BATCH ? a + 1 : a) * 64 + lane];
+            const uint32_t t1u = (uint32_t)(tb + a) + 1u, stamp = t1u << 7;
+            const uint32_t b_next = lists[(a + 1) * 64 + lane];        // behind the last step: not used
             const bool boost = b > 127u;
-            const u64 boost_mask = ballot(boost);
-            const bool no_list = (ballot(b == lane_xor<1>(b)) & 1ull) != 0ull;
             const bool live = has & ((kr >= cut) == boost);
             const u64 live_mask = ballot(live);
-            u64 sel = ballot(live & (below(live_mask) < K));
-            const uint32_t stamp = (t + 1u) << 7;
-            uint32_t e = b & 127u;
-            int n_sel = K, miss = __popcll(sel & ~boost_mask);
-            bool mine = ((sel >> lane) & 1ull) != 0ull;
-            if (no_list || __popcll(live_mask) < K) {
+            const bool chosen = live & (below(live_mask) < K);
+            u64 sel = ballot(chosen);
+            uint32_t e = b & 127u, slot = chosen ? e : 128u + (uint32_t)lane;
+            int n_sel = K, miss = __popcll(sel & ~ballot(boost));
+            if (((no_list >> a) & 1u) | (__popcll(live_mask) < K)) {
                 // K rounds of wavefront maximum over the boosted scores
-                const float *pr = probs + (s * T + t) * N;
+                const float *pr = probs + (s * T + tb + a) * N;
                 const float NEG_INF = -__builtin_inff();
                 const float p0 = lane < N ? pr[lane] : 0.f, p1 = lane + 64 < N ? pr[lane + 64] : 0.f;
                 const u64 res_lo = ballot(k0 >= cut), res_hi = WIDE ? ballot(k1 >= cut) : 0ull;
@@ -255,25 +264,23 @@ __device__ __forceinline__ u64 walk(const float *__restrict__ probs, int64_t s, 
                     else sel_hi |= 1ull << (x - 64);
                 }
                 sel = 0ull;
-                mine = lane < K;
+                slot = lane < K ? e : 128u + (uint32_t)lane;
                 n_sel = __popcll(sel_lo) + __popcll(sel_hi);
                 miss = __popcll(sel_lo & ~res_lo) + __popcll(sel_hi & ~res_hi);
                 if (STORE) {
                     // two equal entries, then the ids; a row without marks is one of these
-                    uint8_t *row = lay.entry(out_idx, out_w, s * T + t, 0);
+                    uint8_t *row = lay.entry(out_idx, out_w, s * T + tb + a, 0);
                     if (lane < 2) row[lane] = 0;
-                    if (mine) row[2 + lane] = (uint8_t)e;
+                    if (lane < K) row[2 + lane] = (uint8_t)e;
                 }
             }
             // one wavefront: its LDS accesses are served in program order
-            keys[mine ? e : 128u + (uint32_t)lane] = stamp | e;
+            keys[slot] = stamp | e;
             asm volatile("" ::: "memory");
             kr = keys[b_next & 127u];
             k0 = keys[lane];
             if (WIDE) k1 = keys[lane + 64];
             b = b_next;
-            held += miss;
-            total += (u64)miss;
             if (lane == a) {
                 o_lo = (uint32_t)sel;
                 o_hi = (uint32_t)(sel >> 32);
@@ -281,32 +288,31 @@ __device__ __forceinline__ u64 walk(const float *__restrict__ probs, int64_t s, 
             }
             // The least recent go first, within a step the lower ids: whole steps while they fit, then the
             // lowest ids of one.  Where the step alone fills the cache, everything older goes.
-            int drop = held - C;
-            uint32_t step = cut >> 7;
-            if (n_sel >= C) {
-                drop = n_sel - C;
-                step = t + 1u;
+            if (FULL && n_sel >= C) {
+                held = C;
                 cut = stamp;
-                held = C;
-            } else if (drop > 0) {
-                held = C;
-            }
-            while (drop > 0 && step <= t + 1u) {
-                const bool in0 = (k0 >= cut) & ((k0 >> 7) == step), in1 = WIDE & (k1 >= cut) & ((k1 >> 7) == step);
-                const u64 g0 = ballot(in0), g1 = WIDE ? ballot(in1) : 0ull;
-                const int n0 = __popcll(g0), n_g = n0 + __popcll(g1);
-                if (n_g <= drop) {
-                    drop -= n_g;
-                    cut = ++step << 7;
-                } else {
-                    const u64 h0 = ballot(in0 & (below(g0) == drop));
-                    const u64 h1 = WIDE ? ballot(in1 & (n0 + below(g1) == drop)) : 0ull;
-                    const int x = h0 ? __ffsll((long long)h0) - 1 : 63 + __ffsll((long long)h1);
-                    cut = (step << 7) | (uint32_t)x;
-                    drop = 0;
+                if (n_sel > C) cut |= (uint32_t)nth(k0 >= stamp, WIDE & (k1 >= stamp), n_sel - C);
+            } else {
+                held += miss;
+                int drop = held - C;
+                if (drop > 0) {
+                    held = C;
+                    uint32_t step = cut >> 7;
+                    do {
+                        const bool in0 = (k0 >= cut) & ((k0 >> 7) == step), in1 = WIDE & (k1 >= cut) & ((k1 >> 7) == step);
+                        const int n_g = __popcll(ballot(in0)) + (WIDE ? __popcll(ballot(in1)) : 0);
+                        if (n_g <= drop) {
+                            drop -= n_g;
+                            cut = ++step << 7;
+                        } else {
+                            cut = (step << 7) | (uint32_t)nth(in0, in1, drop);
+                            drop = 0;
+                        }
+                    } while (drop > 0 && step <= t1u);
                 }
             }
         }
+        lane_misses += o_miss;
         if (STORE && lane < n) {
             uint8_t *mk = lay.mark(out_w, s * T + tb + lane);
             const u64 marks = ((u64)o_hi << 32) | o_lo;
@@ -316,20 +322,20 @@ __device__ __forceinline__ u64 walk(const float *__restrict__ probs, int64_t s, 
     }
     st.cut = cut;
     st.held = held;
-    return total;
+    return lane_misses;
 }
 
-template <bool WIDE>
+template <bool WIDE, bool FULL>
 __global__ __launch_bounds__(64 * RR_WAVES) void reroute_walk_kernel(const float *__restrict__ probs, int64_t T, int N, int C, float factor,
                                                                      RowLayout lay, int64_t stretch, int64_t warm, int32_t *out_idx,
                                                                      float *out_w, uint8_t *out_miss, u64 *__restrict__ out_total_miss)
 {
     __shared__ uint32_t keys[RR_WAVES][192];
     __shared__ uint32_t first[RR_WAVES][128];                 // state the stretch was walked from, 0 = not resident
-    __shared__ uint8_t lists[RR_WAVES][RR_BATCH * 64];
+    __shared__ uint8_t lists[RR_WAVES][(RR_BATCH + 1) * 64];
     __shared__ uint32_t cuts[RR_WAVES];
     __shared__ int helds[RR_WAVES];
-    __shared__ u64 misses[RR_WAVES];
+    __shared__ uint32_t misses[RR_WAVES];
     const int64_t s = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6), waves = blockDim.x >> 6;
     const int64_t t0 = wave * stretch < T ? wave * stretch : T, t1 = t0 + stretch < T ? t0 + stretch : T;
@@ -339,7 +345,7 @@ __global__ __launch_bounds__(64 * RR_WAVES) void reroute_walk_kernel(const float
     const int64_t from = t0 > warm ? t0 - warm : 0;
     WalkState st{(uint32_t)(from + 1) << 7, 0};
     if (wave > 0 && t0 < t1) {
-        walk<WIDE, false>(probs, s, T, from, t0, N, C, factor, lay, out_idx, out_w, out_miss, keys[wave], lists[wave], st);
+        walk<WIDE, FULL, false>(probs, s, T, from, t0, N, C, factor, lay, out_idx, out_w, out_miss, keys[wave], lists[wave], st);
     }
     __syncthreads();                    // the walks below may replace the list of a step that has none
     bool again = true;
@@ -350,11 +356,13 @@ __global__ __launch_bounds__(64 * RR_WAVES) void reroute_walk_kernel(const float
                 keys[wave][e] = k;
                 first[wave][e] = k;
             }
-            const u64 m = walk<WIDE, true>(probs, s, T, t0, t1, N, C, factor, lay, out_idx, out_w, out_miss, keys[wave], lists[wave], st);
+            const uint32_t m = walk<WIDE, FULL, true>(probs, s, T, t0, t1, N, C, factor, lay, out_idx, out_w, out_miss, keys[wave], lists[wave], st);
+            uint32_t sum = m;
+            for (int d = 32; d > 0; d >>= 1) sum += (uint32_t)__shfl_xor((int)sum, d, 64);
             if (lane == 0) {
                 cuts[wave] = st.cut;
                 helds[wave] = st.held;
-                misses[wave] = m;
+                misses[wave] = sum;
             }
         }
         __syncthreads();
@@ -432,15 +440,13 @@ remoe_status launch_reroute(const float *probs, int64_t S, int64_t T, int N, int
     int64_t warm = RR_BATCH * ceil_div(16 + 12 * (int64_t)(C < N ? C : N) / K, RR_BATCH);
     if (warm > stretch) warm = stretch;
     u64 *total = reinterpret_cast<u64 *>(total_miss);
-    if (N > 64) {
-        if (rows > 0) hipLaunchKernelGGL(reroute_rank_kernel<true>, dim3((unsigned)row_blocks), dim3(256), 0, stream, probs, rows, N, factor, lay, idx, w);
-        hipLaunchKernelGGL(reroute_walk_kernel<true>, dim3((unsigned)S), dim3(64 * waves), 0, stream, probs, T, N, C, factor, lay, stretch, warm, idx,
-                           w, miss, total);
-    } else {
-        if (rows > 0) hipLaunchKernelGGL(reroute_rank_kernel<false>, dim3((unsigned)row_blocks), dim3(256), 0, stream, probs, rows, N, factor, lay, idx, w);
-        hipLaunchKernelGGL(reroute_walk_kernel<false>, dim3((unsigned)S), dim3(64 * waves), 0, stream, probs, T, N, C, factor, lay, stretch, warm, idx,
-                           w, miss, total);
+    if (rows > 0) {
+        auto rank = N > 64 ? reroute_rank_kernel<true> : reroute_rank_kernel<false>;
+        hipLaunchKernelGGL(rank, dim3((unsigned)row_blocks), dim3(256), 0, stream, probs, rows, N, factor, lay, idx, w);
     }
+    auto walk_kernel = N > 64 ? (K >= C ? reroute_walk_kernel<true, true> : reroute_walk_kernel<true, false>)
+                              : (K >= C ? reroute_walk_kernel<false, true> : reroute_walk_kernel<false, false>);
+    hipLaunchKernelGGL(walk_kernel, dim3((unsigned)S), dim3(64 * waves), 0, stream, probs, T, N, C, factor, lay, stretch, warm, idx, w, miss, total);
     if (rows > 0) hipLaunchKernelGGL(reroute_weights_kernel, dim3((unsigned)row_blocks), dim3(256), 0, stream, probs, rows, N, renorm, lay, idx, w);
     return check_hip(hipGetLastError(), "reroute launch");
 }
