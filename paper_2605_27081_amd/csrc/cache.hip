@@ -9,12 +9,11 @@
 // the last requests alone), so a trace is walked in order: one wavefront per trace, the resident set
 // a 128-bit mask in wave-uniform registers, lane l holding the retention keys of experts l and
 // l + 64.  After a step every requested expert is held; while more than C are held, the one with the
-// smallest key among those the step did not request is dropped (a wavefront-wide minimum of the
-// secondary key, which ends in the expert id and therefore names the victim; LFU takes the minimum
-// of its primary key first).  Keys (larger = kept longer):
-//   LRU    (step of last use, id)                 FIFO  (step of last fetch, id)
-//   LFU    requests so far, then (step of last use, id)
-//   Belady (steps_total - step of next request, 127 - id): the next request farthest ahead goes first
+// smallest key among those the step did not request is dropped.  Keys (larger = kept longer), ending in the
+// order of the ids:
+//   LRU    step of last use, id                   FIFO  step of last fetch, id
+//   LFU    requests so far, step of last use, id
+//   Belady steps_total - step of next request, 127 - id: the next request farthest ahead goes first
 // The next-request table of Belady comes from next_use_kernel, a backward walk over the same trace.
 //
 // step_summary_kernel / step_percentile_kernel: per-step sums of a miss table over the MoE layers,
@@ -31,7 +30,6 @@ namespace remoe {
 namespace {
 
 constexpr int CP_BATCH = 64;            // steps staged in LDS at a time
-constexpr int CP_MAX_K = 64;
 constexpr uint32_t CP_NONE = 0xFFFFFFFFu;
 
 // rows [t0, t0 + n) of a [T, K] int32 table -> LDS, coalesced
@@ -49,8 +47,7 @@ __device__ __forceinline__ void stage_rows(const int32_t *__restrict__ table, in
 __global__ __launch_bounds__(64) void next_use_kernel(const int32_t *__restrict__ idx, int64_t T, int K, int N,
                                                       int32_t *__restrict__ nxt)
 {
-    __shared__ int32_t ids[CP_BATCH * CP_MAX_K];
-    __shared__ int32_t outs[CP_BATCH * CP_MAX_K];
+    extern __shared__ int32_t ids[];           // a batch of rows, replaced by their next requests step by step
     __shared__ int32_t seen[128];
     const int64_t s = blockIdx.x;
     const int lane = threadIdx.x;
@@ -67,12 +64,12 @@ __global__ __launch_bounds__(64) void next_use_kernel(const int32_t *__restrict_
             if (lane < K) {
                 const int e = ids[tt * K + lane];
                 const bool valid = e >= 0 && e < N;
-                outs[tt * K + lane] = valid ? seen[e] : (int32_t)T;
+                ids[tt * K + lane] = valid ? seen[e] : (int32_t)T;
                 if (valid) seen[e] = (int32_t)(t0 + tt);
             }
         }
         __syncthreads();
-        for (int q = lane; q < n * K; q += 64) no[t0 * K + q] = outs[q];
+        for (int q = lane; q < n * K; q += 64) no[t0 * K + q] = ids[q];
         __syncthreads();
     }
 }
@@ -92,13 +89,51 @@ __device__ __forceinline__ bool bit_of(unsigned long long lo, unsigned long long
     return (((e < 64 ? lo : hi) >> (e & 63)) & 1ull) != 0ull;
 }
 
-// The walk is sequential per trace and one wavefront has nothing to hide a dependent instruction's
-// latency behind, so the step is kept short: the sets (resident, requested, evictable) are 128-bit
-// masks in wave-uniform registers and all set arithmetic is scalar; only the retention keys are
-// per lane.  A batch of 64 steps is staged in LDS and lane l first builds the request mask of step
-// l (one pass, all steps at once); the walk then fetches a step's mask with four lane reads.  A key
-// ends in the expert id, so the wavefront minimum names its victim without a search.
-template <int POLICY>
+// a wave-uniform mask as a condition per lane
+__device__ __forceinline__ bool mask_lane(unsigned long long m)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_inverse_ballot_w64(m);
+#else
+    return m & 1ull;
+#endif
+}
+
+__device__ __forceinline__ unsigned long long ballot64(bool b)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_ballot_w64(b);
+#else
+    return b;
+#endif
+}
+
+// the n lowest (HIGH: highest) members of a set of more than n
+template <bool HIGH>
+__device__ __forceinline__ void first_members(unsigned long long &lo, unsigned long long &hi, int n)
+{
+    unsigned long long out_lo = 0ull, out_hi = 0ull;
+    for (; n > 0; --n) {
+        unsigned long long &from = HIGH ? (hi ? hi : lo) : (lo ? lo : hi), &to = &from == &lo ? out_lo : out_hi;
+        const unsigned long long one = HIGH ? 1ull << (63 - __clzll((long long)from)) : from & (0ull - from);
+        to |= one;
+        from ^= one;
+    }
+    lo = out_lo;
+    hi = out_hi;
+}
+
+// The walk is sequential per trace and bound by the instructions its wavefronts issue, so the step is
+// kept short: the sets (resident, requested, evictable) are masks in wave-uniform registers and all set
+// arithmetic is scalar; only the retention keys are per lane, and the upper half of both exists only
+// for more than 64 experts (WIDE).  A batch of 64 steps is staged in LDS (as much of it as K asks for: with room
+// for 64 ids a step, 10 wavefronts fitted a compute unit) and lane l first builds the request mask of step
+// l (one pass, all steps at once); the walk then fetches a step's mask with two or four lane reads.
+// Victims leave in groups of equal key, found by one wavefront minimum per group; only the group that is
+// not needed whole is gone through by id.
+// 3328 traces x 64 steps, 64 experts, top-6, capacity 12 (us, before / after): LRU 73 / 30, FIFO 78 / 31, LFU 90 / 32,
+// Belady 156 / 43 with its table of next requests.
+template <int POLICY, bool WIDE>
 __global__ __launch_bounds__(64) void cache_policy_kernel(const int32_t *__restrict__ idx, int64_t T, int K, int N, int C,
                                                           unsigned long long expert_bytes,
                                                           const int32_t *__restrict__ nxt,
@@ -108,15 +143,17 @@ __global__ __launch_bounds__(64) void cache_policy_kernel(const int32_t *__restr
                                                           unsigned long long *__restrict__ out_total_uniq,
                                                           unsigned long long *__restrict__ out_bytes)
 {
-    __shared__ int32_t ids[CP_BATCH * CP_MAX_K];
-    __shared__ int32_t nus[(POLICY == REMOE_CACHE_BELADY) ? CP_BATCH * CP_MAX_K : 1];
+    extern __shared__ int32_t stage[];
+    int32_t *ids = stage, *nus = stage + CP_BATCH * K;
     __shared__ uint32_t kb[(POLICY == REMOE_CACHE_BELADY) ? 128 : 1];
     const int64_t s = blockIdx.x;
     const int lane = threadIdx.x;
     const int32_t *tr = idx + s * T * K;
     unsigned long long res_lo = 0ull, res_hi = 0ull;          // resident experts 0..63, 64..127 (wave-uniform)
-    uint32_t khi0 = 0, khi1 = 0, klo0 = 0, klo1 = 0;          // keys of experts lane, lane + 64
-    unsigned long long total = 0, total_u = 0;
+    int held = 0;                                             // how many
+    uint32_t key0 = 0, key1 = 0;                              // keys of experts lane, lane + 64
+    uint32_t age0 = 0, age1 = 0;                              // LFU: step of last use, among equal keys
+    unsigned long long lane_miss = 0, lane_uniq = 0;
     for (int64_t t0 = 0; t0 < T; t0 += CP_BATCH) {
         const int n = (int)((T - t0 < CP_BATCH) ? T - t0 : CP_BATCH);
         stage_rows(tr, t0, n, K, ids);
@@ -124,95 +161,109 @@ __global__ __launch_bounds__(64) void cache_policy_kernel(const int32_t *__restr
         __syncthreads();
         // request mask of step t0 + lane
         unsigned long long m_lo = 0ull, m_hi = 0ull;
+        int valid = 0;
         if (lane < n) {
             for (int j = 0; j < K; ++j) {
                 const int e = ids[lane * K + j];
                 if (e >= 0 && e < N) {
-                    if (e < 64) m_lo |= 1ull << e;
+                    ++valid;
+                    if (!WIDE || e < 64) m_lo |= 1ull << (e & 63);
                     else m_hi |= 1ull << (e - 64);
                 }
             }
         }
         const uint32_t m0 = (uint32_t)m_lo, m1 = (uint32_t)(m_lo >> 32), m2 = (uint32_t)m_hi, m3 = (uint32_t)(m_hi >> 32);
-        uint32_t o_miss = 0, o_uniq = 0, o_hit = 0;           // results of step t0 + lane
+        const uint32_t uniq = (uint32_t)(__popcll(m_lo) + (WIDE ? __popcll(m_hi) : 0));
+        const unsigned long long repeats = ballot64((int)uniq != valid);      // steps that name an expert twice
+        uint32_t o_miss = 0, o_hit = 0;                       // results of step t0 + lane
         for (int tt = 0; tt < n; ++tt) {
-            const uint32_t t = (uint32_t)(t0 + tt);
+            const uint32_t stamp = (uint32_t)(t0 + tt) + 1u;
             const unsigned long long req_lo = ((unsigned long long)get_lane(m1, tt) << 32) | get_lane(m0, tt);
-            const unsigned long long req_hi = ((unsigned long long)get_lane(m3, tt) << 32) | get_lane(m2, tt);
+            const unsigned long long req_hi = WIDE ? ((unsigned long long)get_lane(m3, tt) << 32) | get_lane(m2, tt) : 0ull;
+            int miss = __popcll(req_lo & ~res_lo);
+            if (WIDE) miss += __popcll(req_hi & ~res_hi);
             // token hits count a repeated id every time: lane j looks at slot j
-            const int ej = lane < K ? ids[tt * K + lane] : -1;
-            const int hit_tok = __popcll(__ballot(ej >= 0 && ej < N && bit_of(res_lo, res_hi, ej)));
-            const int n_u = __popcll(req_lo) + __popcll(req_hi);
-            const int miss = __popcll(req_lo & ~res_lo) + __popcll(req_hi & ~res_hi);
+            if ((repeats >> tt) & 1ull) {
+                const int ej = lane < K ? ids[tt * K + lane] : -1;
+                const int hits = __popcll(ballot64(ej >= 0 && ej < N && bit_of(res_lo, res_hi, ej)));
+                if (lane == tt) o_hit = (uint32_t)hits;
+            }
+            if (lane == tt) o_miss = (uint32_t)miss;
             // serve the step: every requested expert is held now; refresh its key
-            const bool req0 = ((req_lo >> lane) & 1ull) != 0ull, req1 = ((req_hi >> lane) & 1ull) != 0ull;
-            const uint32_t stamp = ((t + 1u) << 7);
-            if (POLICY == REMOE_CACHE_LRU || POLICY == REMOE_CACHE_LFU) {
-                if (req0) klo0 = stamp | (uint32_t)lane;
-                if (req1) klo1 = stamp | (uint32_t)(lane + 64);
+            if (POLICY == REMOE_CACHE_LRU) {
+                if (mask_lane(req_lo)) key0 = stamp;
+                if (WIDE && mask_lane(req_hi)) key1 = stamp;
             }
             if (POLICY == REMOE_CACHE_FIFO) {
-                const bool res0 = ((res_lo >> lane) & 1ull) != 0ull, res1 = ((res_hi >> lane) & 1ull) != 0ull;
-                if (req0 && !res0) klo0 = stamp | (uint32_t)lane;
-                if (req1 && !res1) klo1 = stamp | (uint32_t)(lane + 64);
+                if (mask_lane(req_lo & ~res_lo)) key0 = stamp;
+                if (WIDE && mask_lane(req_hi & ~res_hi)) key1 = stamp;
             }
             if (POLICY == REMOE_CACHE_LFU) {
-                khi0 += req0 ? 1u : 0u;
-                khi1 += req1 ? 1u : 0u;
+                if (mask_lane(req_lo)) { ++key0; age0 = stamp; }
+                if (WIDE && mask_lane(req_hi)) { ++key1; age1 = stamp; }
             }
             if (POLICY == REMOE_CACHE_BELADY) {
                 // lane j posts the key of slot j's expert, the lanes that own a requested expert pick theirs
                 // up (one wavefront: its LDS accesses are served in program order; a repeated id posts the
                 // same key twice)
-                if (ej >= 0 && ej < N) kb[ej] = (((uint32_t)T - (uint32_t)nus[tt * K + lane]) << 7) | (uint32_t)(127 - ej);
-                if (req0) klo0 = kb[lane];
-                if (req1) klo1 = kb[lane + 64];
+                const int ej = lane < K ? ids[tt * K + lane] : -1;
+                if (ej >= 0 && ej < N) kb[ej] = (uint32_t)T - (uint32_t)nus[tt * K + lane];
+                if (mask_lane(req_lo)) key0 = kb[lane];
+                if (WIDE && mask_lane(req_hi)) key1 = kb[lane + 64];
             }
-            res_lo |= req_lo;
-            res_hi |= req_hi;
-            int held = __popcll(res_lo) + __popcll(res_hi);
             // Victims come from the held experts this step did not request: an expert served in a step
             // stays until the step is over (App. A, step atomicity and admission: E_t is part of the
             // next resident set whenever C >= K).  Only a step with more distinct requests than C
             // leaves none of those, and then the ranking runs over the requested ones.
             unsigned long long free_lo = res_lo & ~req_lo, free_hi = res_hi & ~req_hi;
+            res_lo |= req_lo;
+            res_hi |= req_hi;
+            held += miss;
             while (held > C) {
-                const bool any_free = (free_lo | free_hi) != 0ull;
-                const unsigned long long c_lo = any_free ? free_lo : res_lo, c_hi = any_free ? free_hi : res_hi;
-                bool c0 = ((c_lo >> lane) & 1ull) != 0ull, c1 = ((c_hi >> lane) & 1ull) != 0ull;
-                if (POLICY == REMOE_CACHE_LFU) {
-                    const uint32_t a0 = c0 ? khi0 : CP_NONE, a1 = c1 ? khi1 : CP_NONE;
-                    const uint32_t mhi = wave_min_u32(a0 < a1 ? a0 : a1);
-                    c0 = c0 && khi0 == mhi;
-                    c1 = c1 && khi1 == mhi;
+                if ((free_lo | free_hi) == 0ull) {
+                    free_lo = res_lo;
+                    free_hi = res_hi;
                 }
-                const uint32_t b0 = c0 ? klo0 : CP_NONE, b1 = c1 ? klo1 : CP_NONE;
-                const uint32_t mlo = wave_min_u32(b0 < b1 ? b0 : b1);
-                const int victim = (POLICY == REMOE_CACHE_BELADY) ? 127 - (int)(mlo & 127u) : (int)(mlo & 127u);
-                const unsigned long long keep = ~(1ull << (victim & 63));
-                if (victim < 64) { res_lo &= keep; free_lo &= keep; }
-                else { res_hi &= keep; free_hi &= keep; }
-                --held;
+                const uint32_t b0 = mask_lane(free_lo) ? key0 : CP_NONE, b1 = WIDE && mask_lane(free_hi) ? key1 : CP_NONE;
+                const uint32_t least = wave_min_u32(WIDE && b1 < b0 ? b1 : b0);
+                unsigned long long g_lo = ballot64(key0 == least) & free_lo, g_hi = WIDE ? ballot64(key1 == least) & free_hi : 0ull;
+                int n_g = __popcll(g_lo) + (WIDE ? __popcll(g_hi) : 0);
+                const int drop = held - C;
+                if (POLICY == REMOE_CACHE_LFU && n_g > drop) {
+                    const uint32_t a0 = mask_lane(g_lo) ? age0 : CP_NONE, a1 = WIDE && mask_lane(g_hi) ? age1 : CP_NONE;
+                    const uint32_t oldest = wave_min_u32(WIDE && a1 < a0 ? a1 : a0);
+                    g_lo &= ballot64(age0 == oldest);
+                    if (WIDE) g_hi &= ballot64(age1 == oldest);
+                    n_g = __popcll(g_lo) + (WIDE ? __popcll(g_hi) : 0);
+                }
+                if (n_g > drop) {
+                    first_members<POLICY == REMOE_CACHE_BELADY>(g_lo, g_hi, drop);
+                    n_g = drop;
+                }
+                res_lo &= ~g_lo;
+                free_lo &= ~g_lo;
+                res_hi &= ~g_hi;
+                free_hi &= ~g_hi;
+                held -= n_g;
             }
-            if (lane == tt) {
-                o_miss = (uint32_t)miss;
-                o_uniq = (uint32_t)n_u;
-                o_hit = (uint32_t)hit_tok;
-            }
-            total += (unsigned long long)miss;
-            total_u += (unsigned long long)n_u;
         }
         if (lane < n) {
             out_miss[s * T + t0 + lane] = (uint8_t)o_miss;
-            out_uniq[s * T + t0 + lane] = (uint8_t)o_uniq;
-            out_hit_tok[s * T + t0 + lane] = (uint8_t)o_hit;
+            out_uniq[s * T + t0 + lane] = (uint8_t)uniq;
+            out_hit_tok[s * T + t0 + lane] = (uint8_t)((repeats >> lane) & 1ull ? o_hit : uniq - o_miss);
+            lane_miss += o_miss;
+            lane_uniq += uniq;
         }
         __syncthreads();       // the staged rows are replaced next
     }
+    for (int d = 32; d > 0; d >>= 1) {
+        lane_miss += __shfl_xor(lane_miss, d, 64);
+        lane_uniq += __shfl_xor(lane_uniq, d, 64);
+    }
     if (lane == 0) {
-        out_total_miss[s] = total;
-        out_total_uniq[s] = total_u;
-        out_bytes[s] = total * expert_bytes;
+        out_total_miss[s] = lane_miss;
+        out_total_uniq[s] = lane_uniq;
+        out_bytes[s] = lane_miss * expert_bytes;
     }
 }
 
@@ -368,23 +419,24 @@ remoe_status launch_cache_policy(const int32_t *idx, int64_t S, int64_t T, int K
     unsigned long long *tu = reinterpret_cast<unsigned long long *>(total_uniq);
     unsigned long long *tb = reinterpret_cast<unsigned long long *>(bytes);
     int32_t *nxt = static_cast<int32_t *>(workspace);
+    const size_t rows = sizeof(int32_t) * CP_BATCH * K;
+    auto run = [&](auto kernel, size_t lds) {
+        hipLaunchKernelGGL(kernel, grid, block, lds, stream, idx, T, K, N, C, expert_bytes, nxt, miss, uniq, hit_tok, tm, tu, tb);
+    };
+    const bool wide = N > 64;
     switch (policy) {
     case REMOE_CACHE_LRU:
-        hipLaunchKernelGGL(cache_policy_kernel<REMOE_CACHE_LRU>, grid, block, 0, stream, idx, T, K, N, C, expert_bytes, nxt, miss,
-                           uniq, hit_tok, tm, tu, tb);
+        run(wide ? cache_policy_kernel<REMOE_CACHE_LRU, true> : cache_policy_kernel<REMOE_CACHE_LRU, false>, rows);
         break;
     case REMOE_CACHE_FIFO:
-        hipLaunchKernelGGL(cache_policy_kernel<REMOE_CACHE_FIFO>, grid, block, 0, stream, idx, T, K, N, C, expert_bytes, nxt, miss,
-                           uniq, hit_tok, tm, tu, tb);
+        run(wide ? cache_policy_kernel<REMOE_CACHE_FIFO, true> : cache_policy_kernel<REMOE_CACHE_FIFO, false>, rows);
         break;
     case REMOE_CACHE_LFU:
-        hipLaunchKernelGGL(cache_policy_kernel<REMOE_CACHE_LFU>, grid, block, 0, stream, idx, T, K, N, C, expert_bytes, nxt, miss,
-                           uniq, hit_tok, tm, tu, tb);
+        run(wide ? cache_policy_kernel<REMOE_CACHE_LFU, true> : cache_policy_kernel<REMOE_CACHE_LFU, false>, rows);
         break;
     case REMOE_CACHE_BELADY:
-        hipLaunchKernelGGL(next_use_kernel, grid, block, 0, stream, idx, T, K, N, nxt);
-        hipLaunchKernelGGL(cache_policy_kernel<REMOE_CACHE_BELADY>, grid, block, 0, stream, idx, T, K, N, C, expert_bytes, nxt,
-                           miss, uniq, hit_tok, tm, tu, tb);
+        hipLaunchKernelGGL(next_use_kernel, grid, block, rows, stream, idx, T, K, N, nxt);
+        run(wide ? cache_policy_kernel<REMOE_CACHE_BELADY, true> : cache_policy_kernel<REMOE_CACHE_BELADY, false>, 2 * rows);
         break;
     default:
         return fail(REMOE_E_INVALID_ARG, "unknown cache policy %d", policy);
