@@ -144,6 +144,7 @@ struct Workspace {
     void *hbuf = nullptr;     // [T*K, I]            SwiGLU activations of the routed experts
     void *hsbuf = nullptr;    // [T, I_s]            SwiGLU activations of the shared expert
     void *rows = nullptr;     // [T*K (+T), H]       weighted per-(token, expert) outputs, then shared rows
+    float *logits = nullptr;  // the router's shares of the logits, where it takes any
     int tile_m = 0;           // rows of a GEMM row tile
     int h_pitch = 0, hs_pitch = 0;   // row pitches of hbuf, hsbuf
     int max_tiles = 0;
@@ -206,6 +207,7 @@ Workspace layout(const remoe_layer_desc *d, int64_t T, void *base_v)
     carve(base, off, w.hbuf, es * pairs * w.h_pitch);
     carve(base, off, w.hsbuf, es * T * w.hs_pitch);
     carve(base, off, w.rows, es * (pairs + (d->shared_inter ? T : 0)) * d->hidden);
+    carve(base, off, w.logits, route_scratch_bytes(T, d->hidden, d->n_experts));
     w.total = align_up(off, 256);
     return w;
 }
@@ -336,7 +338,7 @@ remoe_status moe_route(const remoe_layer_desc *desc, const void *x, int64_t n_to
         return fail(REMOE_E_INVALID_ARG, "x and w_router must be 16-byte aligned");
     ProfScope prof(REMOE_PROF_ROUTE, static_cast<hipStream_t>(stream));
     return launch_route(x, desc->dtype, n_tokens, desc->hidden, w_router, desc->n_experts, desc->top_k,
-                        desc->renorm, out_idx, out_w, out_margin, out_probs, static_cast<hipStream_t>(stream));
+                        desc->renorm, out_idx, out_w, out_margin, out_probs, nullptr, static_cast<hipStream_t>(stream));
 }
 
 remoe_status moe_forward(const remoe_layer_desc *desc, const void *x, int64_t n_tokens,
@@ -372,7 +374,7 @@ remoe_status moe_forward(const remoe_layer_desc *desc, const void *x, int64_t n_
     // 1. router: logits, top-k, softmax weights
     {
         ProfScope prof(REMOE_PROF_ROUTE, stream);
-        st = launch_route(x, desc->dtype, T, H, w_router, N, K, desc->renorm, out_idx, out_w, nullptr, nullptr, stream);
+        st = launch_route(x, desc->dtype, T, H, w_router, N, K, desc->renorm, out_idx, out_w, nullptr, nullptr, ws.logits, stream);
     }
     if (st != REMOE_OK) return st;
     // 2. sort (token, j) pairs by expert; build the GEMM tile list

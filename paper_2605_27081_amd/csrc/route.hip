@@ -36,6 +36,7 @@ namespace {
 constexpr int RT_BLOCK = 256;          // threads
 constexpr int RT_BK = 32;              // k-values per slice
 constexpr int RT_LANES = 8;            // lanes per token in the top-k
+constexpr int RT_PARTS = 8;            // shares of the reduction at most
 
 // 128-byte rows (fp32 values) are 8 chunks of 16 bytes; chunk c of row r lives in row slot r ^ ((r >> 3) & 1)
 // at chunk position c ^ (r & 7): 16 consecutive rows of one logical chunk cover all banks once.
@@ -233,11 +234,14 @@ __device__ __forceinline__ void route_topk(const float *row, int sub, int64_t t,
     }
 }
 
-template <int NE, int MT, typename XT>
+// PART: workgroup (b, s) takes share s of the reduction only (`per_part` slices) and stores its products, a row of
+// NE * 32 sums per token, to partial[s]; route_parts_kernel adds the shares up and ranks them.
+template <int NE, int MT, bool PART, typename XT>
 __global__ __launch_bounds__(RT_BLOCK, 2) void route_kernel(const XT *__restrict__ x, int64_t T, int H,
                                                             const float *__restrict__ wr, int N, int K, int renorm,
                                                             int32_t *__restrict__ out_idx, float *__restrict__ out_w,
-                                                            float *__restrict__ out_margin, float *__restrict__ out_probs)
+                                                            float *__restrict__ out_margin, float *__restrict__ out_probs,
+                                                            float *__restrict__ partial, int per_part)
 {
     typedef LogitLayout<NE> LL;
     constexpr bool BF16 = sizeof(XT) == 2;
@@ -283,12 +287,13 @@ __global__ __launch_bounds__(RT_BLOCK, 2) void route_kernel(const XT *__restrict
         x_off[i] = (uint32_t)((r < left ? r : (int)left - 1) * H * (int)sizeof(XT) + c * 16);
     }
     const char *w_base = reinterpret_cast<const char *>(wr), *x_base = reinterpret_cast<const char *>(x + t0 * H);
-    const int nk = H / RT_BK;
-    // slice j of the reduction -> stage `st` (past the end: the last slice again, so that the count of
+    const int slices = H / RT_BK, first = PART ? (int)blockIdx.y * per_part : 0;
+    const int nk = PART ? (slices - first < per_part ? slices - first : per_part) : slices;
+    // slice j of the share -> stage `st` (past the end: the last slice again, so that the count of
     // outstanding copies never varies)
 #define RT_COPY(j, st)                                                                                            \
     {                                                                                                             \
-        const int j_ = (j) < nk ? (j) : nk - 1;                                                                   \
+        const int j_ = first + ((j) < nk ? (j) : nk - 1);                                                         \
         const char *wb_ = w_base + (int64_t)j_ * RT_BK * 4, *xb_ = x_base + (int64_t)j_ * RT_BK * (int)sizeof(XT); \
         _Pragma("unroll") for (int i = 0; i < W_COPIES; ++i)                                                      \
             copy16_to_lds(wb_, w_off[i], (st) + (wave * W_COPIES + i) * 64);                                      \
@@ -337,6 +342,17 @@ __global__ __launch_bounds__(RT_BLOCK, 2) void route_kernel(const XT *__restrict
 #undef RT_NEXT
 #undef RT_COPY
     wait_vmem<0>();
+    if constexpr (PART) {
+        float *out = partial + ((int64_t)blockIdx.y * T + t0) * (NE * 32) + et * 32 + li;
+#pragma unroll
+        for (int n = 0; n < MT; ++n)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int tl = row0 + n * 32 + (r >> 2) * 8 + lh * 4 + (r & 3);
+                if (tl < left) out[tl * (NE * 32)] = acc[n][r];
+            }
+        return;
+    }
     lds_barrier();
 
     // park the logits (every copy has landed, every stage has been read)
@@ -354,23 +370,80 @@ __global__ __launch_bounds__(RT_BLOCK, 2) void route_kernel(const XT *__restrict
     }
 }
 
+// 32 tokens per workgroup: their logits are the sums of the shares, taken in order
+template <int NE>
+__global__ __launch_bounds__(RT_BLOCK) void route_parts_kernel(const float *__restrict__ partial, int parts, int64_t T, int N, int K, int renorm,
+                                                               int32_t *__restrict__ out_idx, float *__restrict__ out_w,
+                                                               float *__restrict__ out_margin, float *__restrict__ out_probs)
+{
+    typedef LogitLayout<NE> LL;
+    constexpr int TOKENS = RT_BLOCK / RT_LANES, ROW4 = NE * 8;        // 16-byte pieces of a row
+    __shared__ floatx4_t smem[TOKENS * LL::STRIDE / 4];
+    float *Ls = reinterpret_cast<float *>(smem);
+    const int64_t t0 = (int64_t)blockIdx.x * TOKENS, left = T - t0;
+#pragma unroll
+    for (int q = (int)threadIdx.x; q < TOKENS * ROW4; q += RT_BLOCK) {
+        const int tl = q / ROW4, c = q % ROW4;
+        const int64_t t = t0 + (tl < left ? tl : left - 1);
+        const floatx4_t *p = reinterpret_cast<const floatx4_t *>(partial) + t * ROW4 + c;
+        floatx4_t v[RT_PARTS], sum;
+#pragma unroll
+        for (int s = 0; s < RT_PARTS; ++s) v[s] = p[(s < parts ? s : 0) * T * ROW4];
+        sum = v[0];
+#pragma unroll
+        for (int s = 1; s < RT_PARTS; ++s)
+            if (s < parts) sum += v[s];
+        *reinterpret_cast<floatx4_t *>(&Ls[LL::at(tl, 4 * c)]) = sum;
+    }
+    __syncthreads();
+    const int tl = threadIdx.x / RT_LANES;
+    route_topk<NE>(Ls + tl * LL::STRIDE, threadIdx.x % RT_LANES, t0 + tl, tl < left, N, K, renorm, out_idx, out_w, out_margin, out_probs);
+}
+
 // Tokens per workgroup.  A workgroup's time is one serial chain over the reduction whatever its width, and one
 // wavefront per SIMD issues a vector instruction every 8 cycles at best, so as long as the blocks do not fill
 // the chip the narrowest block is the fastest; beyond that a wider block splits the weights for more
 // tokens at a time.  Hence the fewest token tiles that still give one workgroup per compute unit, up to what the
 // LDS holds twice.  H = 2048, bf16, 1 / 2 / 4 token tiles: 128 experts, 4096 tokens 27 / 31 / 46 us, 16384 tokens
 // 45 / 35 / 47, 65536 tokens 169 / 119 / 101; 64 experts, 16384 tokens 26 / 30 / 47, 65536 tokens 80 / 63 / 62.
+// Shares of the reduction: with few tokens a handful of workgroups fetch the whole gate matrix, each through one
+// compute unit, one slice after the other.  Given scratch memory for the shares (launch_route's `partial`), up to
+// RT_PARTS workgroups take at least 8 slices each, while the blocks leave room for them on the chip (256 compute units; the
+// constant, so that the size of the scratch is a function of its arguments alone).  Layer with the router as its
+// largest part, caches flushed before each call, 1 / 2 / 4 / 8 shares (us): H = 2048, 128 experts, 16 tokens 75 / 67 / 62 /
+// 59, 1021 tokens 114 / 107 / 102 / 100, 2048 tokens 144 / 139 / 134 / 135, 4096 tokens 187 / 182 / 183 / 188; 64 experts,
+// 4096 tokens 157 / 150 / 146 / 148; H = 1024, 32 experts, 1021 tokens 52 / 48 / 45 / 44; H = 512, 128 experts, 1021
+// tokens 40 / 43 / 41 / 41: below H = 1024 the second launch costs what the shares save.
+int route_parts(int64_t T, int H, int N)
+{
+    const int ne = N <= 32 ? 1 : N <= 64 ? 2 : 4;
+    const int64_t room = 256 / ceil_div(T, 32 * (4 / ne));
+    int parts = H < 1024 ? 1 : H / (8 * RT_BK);
+    if (parts > RT_PARTS) parts = RT_PARTS;
+    if (parts > room) parts = (int)room;
+    return parts > 1 ? parts : 1;
+}
+
 template <int NE, typename XT>
 remoe_status launch_tiles(const XT *x, int64_t T, int H, const float *wr, int N, int K, int renorm, int32_t *out_idx,
-                          float *out_w, float *out_margin, float *out_probs, hipStream_t stream)
+                          float *out_w, float *out_margin, float *out_probs, float *partial, hipStream_t stream)
 {
     constexpr int UNIT = 32 * (4 / NE);    // tokens of a workgroup per token tile of a wavefront
     const dim3 block(RT_BLOCK);
 #define RT_LAUNCH(MT)                                                                                              \
-    hipLaunchKernelGGL((route_kernel<NE, MT, XT>), dim3((unsigned)ceil_div(T, UNIT * MT)), block, 0, stream, x, T, H, wr, N, K, \
-                       renorm, out_idx, out_w, out_margin, out_probs)
+    hipLaunchKernelGGL((route_kernel<NE, MT, false, XT>), dim3((unsigned)ceil_div(T, UNIT * MT)), block, 0, stream, x, T, H, wr, N, K, \
+                       renorm, out_idx, out_w, out_margin, out_probs, nullptr, 0)
     constexpr bool BF16 = sizeof(XT) == 2;
     constexpr int MAX_MT = NE == 1 ? (BF16 ? 2 : 1) : (BF16 ? 4 : 2);
+    const int parts = partial ? route_parts(T, H, N) : 1;
+    if (parts > 1) {
+        const int per_part = (int)ceil_div(H / RT_BK, parts);
+        hipLaunchKernelGGL((route_kernel<NE, 1, true, XT>), dim3((unsigned)ceil_div(T, UNIT), (unsigned)ceil_div(H / RT_BK, per_part)), block, 0,
+                           stream, x, T, H, wr, N, K, renorm, nullptr, nullptr, nullptr, nullptr, partial, per_part);
+        hipLaunchKernelGGL(route_parts_kernel<NE>, dim3((unsigned)ceil_div(T, RT_BLOCK / RT_LANES)), block, 0, stream, partial,
+                           (int)ceil_div(H / RT_BK, per_part), T, N, K, renorm, out_idx, out_w, out_margin, out_probs);
+        return check_hip(hipGetLastError(), "route_parts_kernel launch");
+    }
     int cus = 0;
     const remoe_status st = compute_units(&cus);
     if (st != REMOE_OK) return st;
@@ -385,25 +458,31 @@ remoe_status launch_tiles(const XT *x, int64_t T, int H, const float *wr, int N,
 template <typename XT>
 remoe_status launch_typed(const XT *x, int64_t T, int H, const float *wr, int N, int K, int renorm,
                           int32_t *out_idx, float *out_w, float *out_margin, float *out_probs,
-                          hipStream_t stream)
+                          float *partial, hipStream_t stream)
 {
-    if (N <= 32) return launch_tiles<1, XT>(x, T, H, wr, N, K, renorm, out_idx, out_w, out_margin, out_probs, stream);
-    if (N <= 64) return launch_tiles<2, XT>(x, T, H, wr, N, K, renorm, out_idx, out_w, out_margin, out_probs, stream);
-    return launch_tiles<4, XT>(x, T, H, wr, N, K, renorm, out_idx, out_w, out_margin, out_probs, stream);
+    if (N <= 32) return launch_tiles<1, XT>(x, T, H, wr, N, K, renorm, out_idx, out_w, out_margin, out_probs, partial, stream);
+    if (N <= 64) return launch_tiles<2, XT>(x, T, H, wr, N, K, renorm, out_idx, out_w, out_margin, out_probs, partial, stream);
+    return launch_tiles<4, XT>(x, T, H, wr, N, K, renorm, out_idx, out_w, out_margin, out_probs, partial, stream);
 }
 
 }  // namespace
 
+size_t route_scratch_bytes(int64_t T, int H, int N)
+{
+    const int parts = T > 0 ? route_parts(T, H, N) : 1;
+    return parts > 1 ? sizeof(float) * parts * T * (N <= 32 ? 32 : N <= 64 ? 64 : 128) : 0;
+}
+
 remoe_status launch_route(const void *x, int x_dtype, int64_t T, int H, const float *w_router,
                           int N, int K, int renorm, int32_t *out_idx, float *out_w,
-                          float *out_margin, float *out_probs, hipStream_t stream)
+                          float *out_margin, float *out_probs, float *partial, hipStream_t stream)
 {
     if (T == 0) return REMOE_OK;
     if (x_dtype == REMOE_F32)
         return launch_typed<float>(static_cast<const float *>(x), T, H, w_router, N, K, renorm,
-                                   out_idx, out_w, out_margin, out_probs, stream);
+                                   out_idx, out_w, out_margin, out_probs, partial, stream);
     return launch_typed<bf16_t>(static_cast<const bf16_t *>(x), T, H, w_router, N, K, renorm,
-                                out_idx, out_w, out_margin, out_probs, stream);
+                                out_idx, out_w, out_margin, out_probs, partial, stream);
 }
 
 }  // namespace remoe
