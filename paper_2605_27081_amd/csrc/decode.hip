@@ -589,10 +589,10 @@ __global__ __launch_bounds__(CH_THREADS) void decode_chain_kernel(const ChainArg
     }
 }
 
-__global__ void decode_chain_clear(uint32_t *abort_flag, unsigned long long *tagged, int n_tagged)
+__global__ __launch_bounds__(DEC_CLEAR_THREADS) void decode_chain_clear(uint32_t *abort_flag, unsigned long long *tagged, int n_tagged)
 {
-    for (int q = threadIdx.x; q < n_tagged; q += blockDim.x) tagged[q] = 0ull;   // tag 0 = no layer-step
-    if (threadIdx.x == 0) *abort_flag = 0u;
+    decode_clear_words(tagged, n_tagged);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *abort_flag = 0u;
 }
 
 }  // namespace
@@ -673,8 +673,8 @@ remoe_status launch_decode(const DecodeLaunch &d, hipStream_t stream)
     a.spin_limit = d.spin_limit_ticks;
 
     // both regions are contiguous from logit_off to the end of the workspace
-    hipLaunchKernelGGL(decode_chain_clear, dim3(1), dim3(1024), 0, stream, a.abort_flag, a.logit_x,
-                       (int)((wl.total - wl.logit_off) / sizeof(unsigned long long)));
+    const int words = (int)((wl.total - wl.logit_off) / sizeof(unsigned long long));
+    hipLaunchKernelGGL(decode_chain_clear, dim3(decode_clear_blocks(words)), dim3(DEC_CLEAR_THREADS), 0, stream, a.abort_flag, a.logit_x, words);
     void *params[] = {&a};
     const void *fn = nullptr;
     const bool few = KI <= 4 * 512;                  // down-row chunks per lane: 4 or 12

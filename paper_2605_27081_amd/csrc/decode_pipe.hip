@@ -583,10 +583,12 @@ __global__ __launch_bounds__(DP_THREADS) void decode_pipe_kernel(const PipeArgs 
     }
 }
 
-__global__ void decode_pipe_clear(uint32_t *bar, int n, uint32_t *abort_flag, unsigned long long *tagged, int n_tagged)
+__global__ __launch_bounds__(DEC_CLEAR_THREADS) void decode_pipe_clear(uint32_t *bar, int n, uint32_t *abort_flag, unsigned long long *tagged,
+                                                                       int n_tagged)
 {
-    for (int q = threadIdx.x; q < n; q += blockDim.x) bar[q] = 0u;
-    for (int q = threadIdx.x; q < n_tagged; q += blockDim.x) tagged[q] = 0ull;   // tag 0 = no layer-step
+    decode_clear_words(tagged, n_tagged);
+    if (blockIdx.x != 0) return;
+    for (int q = threadIdx.x; q < n; q += DEC_CLEAR_THREADS) bar[q] = 0u;
     if (threadIdx.x == 0) *abort_flag = 0u;
 }
 
@@ -654,8 +656,9 @@ remoe_status launch_decode_pipelined(const DecodeLaunch &d, hipStream_t stream)
     a.spin_limit = d.spin_limit_ticks;
 
     // both ring regions are contiguous from logit_off to the end of the workspace
-    hipLaunchKernelGGL(decode_pipe_clear, dim3(1), dim3(1024), 0, stream, a.bar, G, a.abort_flag, a.logit_ring,
-                       (int)((wl.total - wl.logit_off) / sizeof(unsigned long long)));
+    const int words = (int)((wl.total - wl.logit_off) / sizeof(unsigned long long));
+    hipLaunchKernelGGL(decode_pipe_clear, dim3(decode_clear_blocks(words)), dim3(DEC_CLEAR_THREADS), 0, stream, a.bar, G, a.abort_flag,
+                       a.logit_ring, words);
     void *params[] = {&a};
     const void *fn = nullptr;
     const bool few = d.K * d.I <= 4 * 512;               // down-row chunks per lane: 4 or DP_MAX_DCH
