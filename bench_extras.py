@@ -66,7 +66,7 @@ def main():
         ws = torch.empty(max(nb, 16), dtype=torch.uint8, device=DEV) if nb else None
         ms = timed(lambda: remoe.cache_simulate(idx, N, C, pol, expert_bytes, miss, uniq, hit, tot, totu, byt, ws), args.repeat)
         line(f"cache_simulate[{name}]", ms, traces=S_tr, steps=T, capacity=C,
-             trace_steps_per_s=round(S_tr * T / ms * 1e3), note="sequential in t per trace: latency-bound, one wavefront per trace")
+             trace_steps_per_s=round(S_tr * T / ms * 1e3), note="sequential in t per trace, one wavefront per trace: bound by the instructions it issues")
 
     L, S = 48, 16
     out_all = torch.empty(S, T, dtype=torch.int16, device=DEV)
@@ -99,7 +99,7 @@ def main():
     rtot = torch.empty(S, dtype=torch.int64, device=DEV)
     ms = timed(lambda: remoe.reroute_lru(P, K, 4, 1.5, False, ridx, rw, rmiss, rtot), args.repeat)
     line("reroute_lru", ms, traces=S, steps=T, capacity=4, trace_steps_per_s=round(S * T / ms * 1e3),
-         note="sequential in t per trace; 16 traces use 16 wavefronts")
+         note="16 wavefronts per trace, each on its own verified stretch")
 
     lags = [1, 2, 4, 8, 16]
     vals = torch.zeros(S, 6, dtype=torch.float64, device=DEV)
