@@ -58,7 +58,8 @@ int32_t remoe_version(void);
 const char *remoe_last_error(void);
 
 /* Bytes of workspace moe_forward needs for `n_tokens` tokens of this layer shape (0 on invalid
- * arguments, with remoe_last_error set).  Host call, no GPU work. */
+ * arguments, with remoe_last_error set); never less for more tokens, so a buffer sized for the
+ * largest batch serves every smaller one.  Host call, no GPU work. */
 size_t remoe_workspace_bytes(const remoe_layer_desc *desc, int64_t n_tokens);
 
 /*

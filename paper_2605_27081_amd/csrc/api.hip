@@ -168,6 +168,7 @@ template <typename P> void carve(char *base, size_t &off, P *&ptr, size_t bytes)
 // so that the workspace size is a function of its arguments alone):
 //   64 / 128 rows   2048 tokens, 10 experts top-1 (128-row tiles: 126) 136 / 142; 3000 tokens (170) 168 / 151
 //   128 / 256 rows  4096 tokens, 10 experts top-1 (256-row tiles: 126) 168 / 178; 6000 tokens (170) 236 / 191
+constexpr int MIN_TILE_M = 32;
 int forward_tile_m(const remoe_layer_desc *d, int64_t T)
 {
     const double rows = (double)T * d->top_k / d->n_experts;
@@ -177,10 +178,10 @@ int forward_tile_m(const remoe_layer_desc *d, int64_t T)
                (double)(ceil_div(T, m) * ceil_div(d->shared_inter, 128));
     };
     constexpr double ENOUGH = 256 * 5 / 8;
-    if (d->dtype == REMOE_F32) return rows >= 24.0 && tiles(64) >= 2 * ENOUGH ? 64 : 32;
+    if (d->dtype == REMOE_F32) return rows >= 24.0 && tiles(64) >= 2 * ENOUGH ? 64 : MIN_TILE_M;
     if (rows >= 120.0 && tiles(256) >= ENOUGH) return gemm_tile_m();
     if (rows >= 40.0 && tiles(128) >= ENOUGH) return 128;
-    return rows > 6.0 ? 64 : 32;
+    return rows > 6.0 ? 64 : MIN_TILE_M;
 }
 
 Workspace layout(const remoe_layer_desc *d, int64_t T, void *base_v)
@@ -193,13 +194,17 @@ Workspace layout(const remoe_layer_desc *d, int64_t T, void *base_v)
     const int64_t pairs = T * d->top_k;
     const int64_t n_blk = ceil_div(T, permute_tokens_per_block());
     w.tile_m = forward_tile_m(d, T);
-    w.max_tiles = (int)(pairs / w.tile_m + (pairs < d->n_experts ? pairs : d->n_experts));   // full tiles + a ragged one per expert
+    const int64_t ragged = pairs < d->n_experts ? pairs : d->n_experts;
+    w.max_tiles = (int)(pairs / w.tile_m + ragged);   // full tiles + a ragged one per expert
+    // A buffer sized for the largest batch has to serve every smaller one, so no part may shrink as T grows: the tile
+    // lists are sized for the lowest tiles whatever tile_m is.
+    const size_t list_tiles = (size_t)(pairs / MIN_TILE_M + ragged);
     size_t off = 0;
     carve(base, off, w.pb.blk_hist, sizeof(int32_t) * 2 * n_blk * d->n_experts);
     carve(base, off, w.pb.offsets, sizeof(int32_t) * (d->n_experts + 1));
-    carve(base, off, w.pb.tile_expert, sizeof(int32_t) * w.max_tiles);
-    carve(base, off, w.pb.tile_row0, sizeof(int32_t) * w.max_tiles);
-    carve(base, off, w.pb.tile_rows, sizeof(int32_t) * w.max_tiles);
+    carve(base, off, w.pb.tile_expert, sizeof(int32_t) * list_tiles);
+    carve(base, off, w.pb.tile_row0, sizeof(int32_t) * list_tiles);
+    carve(base, off, w.pb.tile_rows, sizeof(int32_t) * list_tiles);
     carve(base, off, w.pb.n_tiles, sizeof(int32_t));
     carve(base, off, w.pb.gemm_ctr, sizeof(uint32_t) * GEMM_CTR_SETS * 8);
     carve(base, off, w.pb.pair_slot, sizeof(int32_t) * pairs);

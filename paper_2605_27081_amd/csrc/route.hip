@@ -414,14 +414,20 @@ __global__ __launch_bounds__(RT_BLOCK) void route_parts_kernel(const float *__re
 // 59, 1021 tokens 114 / 107 / 102 / 100, 2048 tokens 144 / 139 / 134 / 135, 4096 tokens 187 / 182 / 183 / 188; 64 experts,
 // 4096 tokens 157 / 150 / 146 / 148; H = 1024, 32 experts, 1021 tokens 52 / 48 / 45 / 44; H = 512, 128 experts, 1021
 // tokens 40 / 43 / 41 / 41: below H = 1024 the second launch costs what the shares save.
+constexpr int RT_PART_BLOCKS = 256;
+int most_parts(int H)
+{
+    const int parts = H < 1024 ? 1 : H / (8 * RT_BK);
+    return parts < RT_PARTS ? parts : RT_PARTS;
+}
+int expert_tiles(int N) { return N <= 32 ? 1 : N <= 64 ? 2 : 4; }
+int block_tokens(int N) { return 32 * (4 / expert_tiles(N)); }      // of a workgroup with one token tile per wavefront
+
 int route_parts(int64_t T, int H, int N)
 {
-    const int ne = N <= 32 ? 1 : N <= 64 ? 2 : 4;
-    const int64_t room = 256 / ceil_div(T, 32 * (4 / ne));
-    int parts = H < 1024 ? 1 : H / (8 * RT_BK);
-    if (parts > RT_PARTS) parts = RT_PARTS;
-    if (parts > room) parts = (int)room;
-    return parts > 1 ? parts : 1;
+    const int64_t room = RT_PART_BLOCKS / ceil_div(T, block_tokens(N));
+    const int parts = most_parts(H);
+    return parts <= room ? parts : room > 1 ? (int)room : 1;
 }
 
 template <int NE, typename XT>
@@ -467,10 +473,12 @@ remoe_status launch_typed(const XT *x, int64_t T, int H, const float *wr, int N,
 
 }  // namespace
 
+// What any batch of up to T tokens takes (so that more tokens never need less): rows of one share for at most
+// RT_PART_BLOCKS blocks of tokens, 4 MB.
 size_t route_scratch_bytes(int64_t T, int H, int N)
 {
-    const int parts = T > 0 ? route_parts(T, H, N) : 1;
-    return parts > 1 ? sizeof(float) * parts * T * (N <= 32 ? 32 : N <= 64 ? 64 : 128) : 0;
+    const int64_t rows = most_parts(H) * T, most = (int64_t)RT_PART_BLOCKS * block_tokens(N);
+    return most_parts(H) > 1 ? sizeof(float) * (size_t)(rows < most ? rows : most) * 32 * expert_tiles(N) : 0;
 }
 
 remoe_status launch_route(const void *x, int x_dtype, int64_t T, int H, const float *w_router,
