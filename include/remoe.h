@@ -98,7 +98,8 @@ remoe_status moe_route(const remoe_layer_desc *desc, const void *x, int64_t n_to
  *                            (NULL when shared_inter == 0)
  *   ws_scale [H]             fp32 (NULL unless shared_gate)
  *   y        [T, H]          desc->dtype
- *   out_idx  [T, K] int32,   out_w [T, K] fp32  — the routing, as moe_route returns it
+ *   out_idx  [T, K] int32,   out_w [T, K] fp32  — the routing, as moe_route returns it (bit for bit;
+ *                            a token's routing does not depend on the other tokens of the call)
  *   workspace                at least remoe_workspace_bytes(desc, T) bytes, 256-byte aligned;
  *                            contents are scratch and meaningless afterwards
  *

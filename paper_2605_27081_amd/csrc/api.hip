@@ -144,7 +144,7 @@ struct Workspace {
     void *hbuf = nullptr;     // [T*K, I]            SwiGLU activations of the routed experts
     void *hsbuf = nullptr;    // [T, I_s]            SwiGLU activations of the shared expert
     void *rows = nullptr;     // [T*K (+T), H]       weighted per-(token, expert) outputs, then shared rows
-    float *logits = nullptr;  // the router's shares of the logits, where it takes any
+    float *logits = nullptr;  // the router's logits, where it takes them through memory
     int tile_m = 0;           // rows of a GEMM row tile
     int h_pitch = 0, hs_pitch = 0;   // row pitches of hbuf, hsbuf
     int max_tiles = 0;
@@ -212,7 +212,7 @@ Workspace layout(const remoe_layer_desc *d, int64_t T, void *base_v)
     carve(base, off, w.hbuf, es * pairs * w.h_pitch);
     carve(base, off, w.hsbuf, es * T * w.hs_pitch);
     carve(base, off, w.rows, es * (pairs + (d->shared_inter ? T : 0)) * d->hidden);
-    carve(base, off, w.logits, route_scratch_bytes(T, d->hidden, d->n_experts));
+    carve(base, off, w.logits, route_scratch_bytes(d->dtype, T, d->hidden, d->n_experts));
     w.total = align_up(off, 256);
     return w;
 }

@@ -69,12 +69,12 @@ __device__ __forceinline__ float swap_with_neighbour(float v)
 }
 
 // ---- kernel launchers (one per source file) -------------------------------------------------
-// Router: logits, top-k, softmax weights.  x_dtype as remoe_dtype.  partial: 16-byte aligned scratch of
-// route_scratch_bytes (0: none is used), or NULL.
-size_t route_scratch_bytes(int64_t T, int H, int N);
+// Router: logits, top-k, softmax weights.  x_dtype as remoe_dtype.  logits: 16-byte aligned scratch of
+// route_scratch_bytes (0: none is used), or NULL; the results are the same bits with and without.
+size_t route_scratch_bytes(int x_dtype, int64_t T, int H, int N);
 remoe_status launch_route(const void *x, int x_dtype, int64_t T, int H, const float *w_router,
                           int N, int K, int renorm, int32_t *out_idx, float *out_w,
-                          float *out_margin, float *out_probs, float *partial, hipStream_t stream);
+                          float *out_margin, float *out_probs, float *logits, hipStream_t stream);
 
 // Token -> expert counting sort and tile map.
 struct PermuteBuffers {

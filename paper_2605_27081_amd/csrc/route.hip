@@ -4,7 +4,8 @@
 // One workgroup of 4 wavefronts owns a block of tokens and all N_r <= 128 experts.  The experts are cut
 // into NE tiles of 32 (NE = 1, 2 or 4); wavefront w computes expert tile w % NE for MT tiles of 32
 // tokens, the 4 / NE wavefronts of one expert tile taking different tokens, so a workgroup owns
-// 32 * MT * 4 / NE tokens and every token's full logit row ends in one workgroup.
+// 32 * MT * 4 / NE tokens and every token's full logit row ends in one workgroup.  (Layers of few tokens spread the work
+// further: route_few_kernel below.)
 //
 // Logits.  The gate weights are fp32 and the logits must carry fp32 accuracy (near ties decide
 // which experts run).  For fp32 hidden states the products run on v_mfma_f32_32x32x2_f32.  For bf16
@@ -36,7 +37,7 @@ namespace {
 constexpr int RT_BLOCK = 256;          // threads
 constexpr int RT_BK = 32;              // k-values per slice
 constexpr int RT_LANES = 8;            // lanes per token in the top-k
-constexpr int RT_PARTS = 8;            // shares of the reduction at most
+constexpr int RT_PARTS = 8;            // shares of an fp32 reduction at most
 
 // 128-byte rows (fp32 values) are 8 chunks of 16 bytes; chunk c of row r lives in row slot r ^ ((r >> 3) & 1)
 // at chunk position c ^ (r & 7): 16 consecutive rows of one logical chunk cover all banks once.
@@ -234,8 +235,9 @@ __device__ __forceinline__ void route_topk(const float *row, int sub, int64_t t,
     }
 }
 
-// PART: workgroup (b, s) takes share s of the reduction only (`per_part` slices) and stores its products, a row of
-// NE * 32 sums per token, to partial[s]; route_parts_kernel adds the shares up and ranks them.
+// fp32 hidden states: a logit is the sum of shares of per_part slices each (an even number), added in order, which
+// keeps the sums' rounding small at large H.  PART: workgroup (b, s) takes share s only and stores its sums, a row of
+// NE * 32 per token, to partial[s]; route_rank_kernel adds the shares and ranks them.
 template <int NE, int MT, bool PART, typename XT>
 __global__ __launch_bounds__(RT_BLOCK, 2) void route_kernel(const XT *__restrict__ x, int64_t T, int H,
                                                             const float *__restrict__ wr, int N, int K, int renorm,
@@ -301,11 +303,15 @@ __global__ __launch_bounds__(RT_BLOCK, 2) void route_kernel(const XT *__restrict
             copy16_to_lds(xb_, x_off[i], (st) + W_U4 + (X_TOTAL >= 4 ? wave * X_COPIES + i : wave % X_TOTAL) * 64); \
     }
 
-    floatx16_t acc[MT];
+    constexpr bool SUMS = !PART && !BF16;      // several shares in this workgroup
+    floatx16_t acc[MT], sum[SUMS ? MT : 1];
 #pragma unroll
     for (int n = 0; n < MT; ++n)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[n][r] = 0.f;
+        for (int r = 0; r < 16; ++r) {
+            acc[n][r] = 0.f;
+            if (SUMS) sum[n][r] = 0.f;
+        }
 
 #pragma unroll
     for (int j = 0; j < STAGES - 1; ++j) RT_COPY(j, smem + j * STAGE)
@@ -326,11 +332,26 @@ __global__ __launch_bounds__(RT_BLOCK, 2) void route_kernel(const XT *__restrict
     Frags<MT, XT> fa, fb;
     RT_NEXT(0, fa)
     int kt = 1;
-    for (; kt + 1 < nk; kt += 2) {
-        RT_NEXT(kt, fb)
-        fa.mfma(acc);
-        RT_NEXT(kt + 1, fa)
-        fb.mfma(acc);
+    for (int end = SUMS ? per_part : nk;; end += per_part) {       // slices [.., end) are the current share
+        const int stop = end < nk - 1 ? end : nk - 1;
+        for (; kt < stop; kt += 2) {
+            RT_NEXT(kt, fb)
+            fa.mfma(acc);
+            RT_NEXT(kt + 1, fa)
+            fb.mfma(acc);
+        }
+        if constexpr (SUMS) {
+            if (kt > end) {
+#pragma unroll
+                for (int n = 0; n < MT; ++n)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        sum[n][r] += acc[n][r];
+                        acc[n][r] = 0.f;
+                    }
+            }
+        }
+        if (!SUMS || kt >= nk - 1) break;
     }
     if (kt < nk) {
         RT_NEXT(kt, fb)
@@ -361,7 +382,7 @@ __global__ __launch_bounds__(RT_BLOCK, 2) void route_kernel(const XT *__restrict
     for (int n = 0; n < MT; ++n)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-            Ls[LL::at(row0 + n * 32 + (r >> 2) * 8 + lh * 4 + (r & 3), et * 32 + li)] = acc[n][r];
+            Ls[LL::at(row0 + n * 32 + (r >> 2) * 8 + lh * 4 + (r & 3), et * 32 + li)] = SUMS ? sum[n][r] + acc[n][r] : acc[n][r];
     __syncthreads();
 #pragma unroll 1
     for (int g = 0; g < TOKENS; g += RT_BLOCK / RT_LANES) {
@@ -370,11 +391,159 @@ __global__ __launch_bounds__(RT_BLOCK, 2) void route_kernel(const XT *__restrict
     }
 }
 
-// 32 tokens per workgroup: their logits are the sums of the shares, taken in order
+// ---- few tokens ----------------------------------------------------------------------------------------
+// route_kernel leaves most of the chip idle for a few hundred tokens: a workgroup fetches the whole gate matrix through
+// its one compute unit, and each of its wavefronts splits the weights of its expert tile in front of the MFMAs that
+// need them, 1000 cycles a slice of which the MFMAs are 200.  Here a workgroup owns 32 tokens and one tile of 32
+// experts: eight wavefronts split the weights, four rows each, into LDS, one copies the tokens, and one does nothing
+// but read operands and multiply, in steps of 64 k-values, two to a barrier.  It issues the MFMAs that route_kernel
+// issues for this token and expert tile, in the same order on the same operands, so the logits are the same bits from
+// either kernel: moe_forward routes as moe_route does, and a token the same way in a batch of any size.
+// (Cutting the reduction itself into shares is 3 us faster and changes the sums.)  The logits go to memory;
+// route_rank_kernel ranks them.
+// What bounds it: the chain of 3 H / 16 dependent MFMAs, 36 cycles each (5.7 us at H = 2048).  Wavefronts w, w + 4 and w + 8
+// share a SIMD: the multiplying one has its SIMD to itself but for the copies (beside two splitters it took 2 us
+// more), and 8 and 11 end at once.  16 tokens, 128 experts, H = 2048, caches flushed: 27 us for route_kernel, 11 here
+// and 5 for the ranking.
+constexpr int RF_BK = 64;
+constexpr int RF_THREADS = 12 * 64;
+constexpr int RF_AHEAD = 8;            // steps of weights on their way (64 KB), stages of the tokens
+constexpr int RF_X = 32 * 8, RF_PIECE = 32 * 8;                      // 16-byte units of a step's tokens, of one piece of its weights
+
+// the operands of a step
+struct StepFrags {
+    u32x4_t x[4], piece[4][3];
+    __device__ __forceinline__ void read(const u32x4_t *xs, const u32x4_t *ps, int i, int li, int lh)
+    {
+        const int ks = i / 3, pc = i % 3;
+        if (pc == 0) x[ks] = xs[slot_f32(li, 2 * ks + lh)];        // 128-byte rows, whatever they hold
+        piece[ks][pc] = ps[pc * RF_PIECE + slot_f32(li, 2 * ks + lh)];
+    }
+    __device__ __forceinline__ void mfma(floatx16_t &acc, int i) const
+    {
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, x[i / 3]), __builtin_bit_cast(bf16x8_t, piece[i / 3][i % 3]), acc,
+                                                      0, 0, 0);
+    }
+};
+
+// logits[t, pitch]: workgroup (b, e) writes columns 32 e .. 32 e + 31 of tokens 32 b ..; H is a multiple of 2 RF_BK
+__global__ __launch_bounds__(RF_THREADS) void route_few_kernel(const bf16_t *__restrict__ x, int64_t T, int H, const float *__restrict__ wr, int N,
+                                                               float *__restrict__ logits, int pitch)
+{
+    __shared__ u32x4_t ring[RF_AHEAD][RF_X];
+    __shared__ u32x4_t pieces[4][3 * RF_PIECE];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int64_t t0 = (int64_t)blockIdx.x * 32, left = T - t0;
+    const int e0 = blockIdx.y * 32, n = H / RF_BK;
+    if (wave == 8 || wave == 11) return;       // (a barrier waits for the wavefronts that have not ended)
+    if (wave == 4) {
+        // tokens past the end repeat the last one (not stored)
+        uint32_t x_off[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int rs = i * 8 + (lane >> 3), r = rs ^ ((rs >> 3) & 1), c = (lane & 7) ^ (r & 7);
+            x_off[i] = (uint32_t)((r < left ? r : (int)left - 1) * H * 2 + c * 16);
+        }
+        const char *x_base = reinterpret_cast<const char *>(x + t0 * H);
+        // steps j and j + 1 -> their stages (past the end the last step again, to a stage that is not read any more)
+        auto copy = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+            for (int d = 0; d < 2; ++d)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    copy16_to_lds(x_base + (int64_t)(j + d < n ? j + d : n - 1) * RF_BK * 2, x_off[i], ring[(j + d) & (RF_AHEAD - 1)] + i * 64);
+        };
+#pragma unroll
+        for (int j = 0; j < RF_AHEAD - 4; j += 2) copy(j);
+        for (int j = 0; j < n; j += 2) {
+            copy(j + RF_AHEAD - 4);            // stages of steps j - 4 and j - 3, which have been read
+            wait_vmem<(RF_AHEAD - 4) * 4>();
+            lds_barrier();                     // the tokens of steps j and j + 1 are there
+        }
+        wait_vmem<0>();
+        return;
+    }
+    if (wave != 0) {
+        // this lane splits four weights of row r a step: half a chunk.  Rows past the end repeat the last expert (masked in
+        // the ranking).  (Through LDS instead of straight into registers the weights took a third of its bandwidth.)
+        const int r = (wave < 4 ? wave - 1 : wave < 8 ? wave - 2 : wave - 3) * 4 + (lane >> 4), place = slot_f32(r, (lane & 15) >> 1) * 2 + (lane & 1);
+        const floatx4_t *src = reinterpret_cast<const floatx4_t *>(wr + (int64_t)(e0 + r < N ? e0 + r : N - 1) * H) + (lane & 15);
+        floatx4_t w[RF_AHEAD];
+        auto split = [&](int u) __attribute__((always_inline)) {
+            uint32_t p0[3], p1[3];
+            split3_pair(w[u][0], w[u][1], p0[0], p0[1], p0[2]);
+            split3_pair(w[u][2], w[u][3], p1[0], p1[1], p1[2]);
+#pragma unroll
+            for (int pc = 0; pc < 3; ++pc)
+                reinterpret_cast<uint2 *>(&pieces[u & 3][pc * RF_PIECE])[place] = make_uint2(p0[pc], p1[pc]);
+        };
+#pragma unroll
+        for (int u = 0; u < RF_AHEAD; ++u) w[u] = src[(u < n ? u : n - 1) * (RF_BK / 4)];
+        int j = 0;
+        for (; j + RF_AHEAD <= n; j += RF_AHEAD) {
+#pragma unroll
+            for (int u = 0; u < RF_AHEAD; ++u) {
+                split(u);
+                const int next = j + u + RF_AHEAD;
+                w[u] = src[(next < n ? next : n - 1) * (RF_BK / 4)];
+                if (u & 1) {
+                    lds_barrier();                     // steps j + u - 1 and j + u are ready, the two before them have been read
+                    __builtin_amdgcn_sched_barrier(0); // (later steps' splits in front of it would wait for their loads)
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < RF_AHEAD - 1; ++u) {
+            if (j + u < n) {
+                split(u);
+                if (u & 1) lds_barrier();
+            }
+        }
+        return;
+    }
+    __builtin_amdgcn_s_setprio(3);
+    const int li = lane & 31, lh = lane >> 5;
+    floatx16_t acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    StepFrags fa, fb;
+    // step j is read while the step before it is multiplied: the reads behind the first MFMAs (in front of them they
+    // would keep them waiting), so that they have landed when the last one is issued
+    auto step = [&](int j, bool barrier, const StepFrags &prev, StepFrags &next) __attribute__((always_inline)) {
+        if (barrier) lds_barrier();            // this step and the next are there
+        const u32x4_t *xs = ring[j & (RF_AHEAD - 1)], *ps = pieces[j & 3];
+#pragma unroll
+        for (int i = 0; i < 12; ++i) {
+            if (j > 0) prev.mfma(acc, i);
+            if (i < 6) {
+                next.read(xs, ps, 2 * i, li, lh);
+                next.read(xs, ps, 2 * i + 1, li, lh);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    step(0, true, fb, fa);
+    for (int j = 1; j + 1 < n; j += 2) {                           // n is even
+        step(j, false, fa, fb);
+        step(j + 1, true, fb, fa);
+    }
+    step(n - 1, false, fa, fb);
+#pragma unroll
+    for (int i = 0; i < 12; ++i) fb.mfma(acc, i);
+    float *out = logits + t0 * pitch + e0 + li;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int tl = (r >> 2) * 8 + lh * 4 + (r & 3);
+        if (tl < left) out[tl * pitch] = acc[r];
+    }
+}
+
+// 32 tokens per workgroup, a row of NE * 32 logits each (columns past N hold anything), or `parts` shares of them, added
+// in order
 template <int NE>
-__global__ __launch_bounds__(RT_BLOCK) void route_parts_kernel(const float *__restrict__ partial, int parts, int64_t T, int N, int K, int renorm,
-                                                               int32_t *__restrict__ out_idx, float *__restrict__ out_w,
-                                                               float *__restrict__ out_margin, float *__restrict__ out_probs)
+__global__ __launch_bounds__(RT_BLOCK) void route_rank_kernel(const float *__restrict__ logits, int parts, int64_t T, int N, int K, int renorm,
+                                                              int32_t *__restrict__ out_idx, float *__restrict__ out_w,
+                                                              float *__restrict__ out_margin, float *__restrict__ out_probs)
 {
     typedef LogitLayout<NE> LL;
     constexpr int TOKENS = RT_BLOCK / RT_LANES, ROW4 = NE * 8;        // 16-byte pieces of a row
@@ -385,14 +554,16 @@ __global__ __launch_bounds__(RT_BLOCK) void route_parts_kernel(const float *__re
     for (int q = (int)threadIdx.x; q < TOKENS * ROW4; q += RT_BLOCK) {
         const int tl = q / ROW4, c = q % ROW4;
         const int64_t t = t0 + (tl < left ? tl : left - 1);
-        const floatx4_t *p = reinterpret_cast<const floatx4_t *>(partial) + t * ROW4 + c;
-        floatx4_t v[RT_PARTS], sum;
+        const floatx4_t *p = reinterpret_cast<const floatx4_t *>(logits) + t * ROW4 + c;
+        floatx4_t sum = p[0];
+        if (parts > 1) {
+            floatx4_t v[RT_PARTS];
 #pragma unroll
-        for (int s = 0; s < RT_PARTS; ++s) v[s] = p[(s < parts ? s : 0) * T * ROW4];
-        sum = v[0];
+            for (int s = 1; s < RT_PARTS; ++s) v[s] = p[(s < parts ? s : 0) * T * ROW4];
 #pragma unroll
-        for (int s = 1; s < RT_PARTS; ++s)
-            if (s < parts) sum += v[s];
+            for (int s = 1; s < RT_PARTS; ++s)
+                if (s < parts) sum += v[s];
+        }
         *reinterpret_cast<floatx4_t *>(&Ls[LL::at(tl, 4 * c)]) = sum;
     }
     __syncthreads();
@@ -406,49 +577,60 @@ __global__ __launch_bounds__(RT_BLOCK) void route_parts_kernel(const float *__re
 // tokens at a time.  Hence the fewest token tiles that still give one workgroup per compute unit, up to what the
 // LDS holds twice.  H = 2048, bf16, 1 / 2 / 4 token tiles: 128 experts, 4096 tokens 27 / 31 / 46 us, 16384 tokens
 // 45 / 35 / 47, 65536 tokens 169 / 119 / 101; 64 experts, 16384 tokens 26 / 30 / 47, 65536 tokens 80 / 63 / 62.
-// Shares of the reduction: with few tokens a handful of workgroups fetch the whole gate matrix, each through one
-// compute unit, one slice after the other.  Given scratch memory for the shares (launch_route's `partial`), up to
-// RT_PARTS workgroups take at least 8 slices each, while the blocks leave room for them on the chip (256 compute units; the
-// constant, so that the size of the scratch is a function of its arguments alone).  Layer with the router as its
-// largest part, caches flushed before each call, 1 / 2 / 4 / 8 shares (us): H = 2048, 128 experts, 16 tokens 75 / 67 / 62 /
-// 59, 1021 tokens 114 / 107 / 102 / 100, 2048 tokens 144 / 139 / 134 / 135, 4096 tokens 187 / 182 / 183 / 188; 64 experts,
-// 4096 tokens 157 / 150 / 146 / 148; H = 1024, 32 experts, 1021 tokens 52 / 48 / 45 / 44; H = 512, 128 experts, 1021
-// tokens 40 / 43 / 41 / 41: below H = 1024 the second launch costs what the shares save.
-constexpr int RT_PART_BLOCKS = 256;
-int most_parts(int H)
-{
-    const int parts = H < 1024 ? 1 : H / (8 * RT_BK);
-    return parts < RT_PARTS ? parts : RT_PARTS;
-}
-int expert_tiles(int N) { return N <= 32 ? 1 : N <= 64 ? 2 : 4; }
-int block_tokens(int N) { return 32 * (4 / expert_tiles(N)); }      // of a workgroup with one token tile per wavefront
+// Few tokens (bf16, given scratch memory for the logits: launch_route's `logits`): one workgroup of route_few_kernel per
+// compute unit (its registers hold no second one; 256, the constant, so that the size of the scratch is a function of its
+// arguments alone).  Layer with the router as its largest part, caches flushed before each call, route_kernel / this
+// (us): H = 2048, 128 experts, 16 tokens 75 / 62, 1021 tokens 114 / 105, 2048 tokens 144 / 142.  Below H = 1024 the second
+// launch costs what the first one saves.
+constexpr int RF_BLOCKS = 256;
+int logit_pitch(int N) { return N <= 32 ? 32 : N <= 64 ? 64 : 128; }
+int expert_tiles(int N) { return (int)ceil_div(N, 32); }
+bool few_tokens(int64_t T, int H, int N) { return H >= 1024 && H % (2 * RF_BK) == 0 && ceil_div(T, 32) * expert_tiles(N) <= RF_BLOCKS; }
 
-int route_parts(int64_t T, int H, int N)
+// fp32: where the reduction is cut depends on H alone, so the logits are the same bits for any batch and entry point.
+// With scratch memory every share is a workgroup's of its own, up to two for each of the two that a compute unit
+// holds; otherwise a workgroup takes the shares one after the other.  H = 2048, 128 experts, one after the other / each its
+// own (us): 3000 tokens 356 / 338, 4096 tokens 503 / 494.
+constexpr int RT_PART_BLOCKS = 1024;
+int part_slices(int H)
 {
-    const int64_t room = RT_PART_BLOCKS / ceil_div(T, block_tokens(N));
-    const int parts = most_parts(H);
-    return parts <= room ? parts : room > 1 ? (int)room : 1;
+    const int slices = H / RT_BK, most = H < 1024 ? 1 : slices / 8;
+    return (int)ceil_div(slices, 2 * (most < RT_PARTS ? most : RT_PARTS)) * 2;
+}
+int part_count(int H) { return (int)ceil_div(H / RT_BK, part_slices(H)); }
+bool one_share_each(int64_t T, int H, int N)
+{
+    return part_count(H) > 1 && ceil_div(T, 4096 / logit_pitch(N)) * part_count(H) <= RT_PART_BLOCKS;
 }
 
 template <int NE, typename XT>
 remoe_status launch_tiles(const XT *x, int64_t T, int H, const float *wr, int N, int K, int renorm, int32_t *out_idx,
-                          float *out_w, float *out_margin, float *out_probs, float *partial, hipStream_t stream)
+                          float *out_w, float *out_margin, float *out_probs, float *logits, hipStream_t stream)
 {
     constexpr int UNIT = 32 * (4 / NE);    // tokens of a workgroup per token tile of a wavefront
     const dim3 block(RT_BLOCK);
 #define RT_LAUNCH(MT)                                                                                              \
     hipLaunchKernelGGL((route_kernel<NE, MT, false, XT>), dim3((unsigned)ceil_div(T, UNIT * MT)), block, 0, stream, x, T, H, wr, N, K, \
-                       renorm, out_idx, out_w, out_margin, out_probs, nullptr, 0)
+                       renorm, out_idx, out_w, out_margin, out_probs, nullptr, per_part)
     constexpr bool BF16 = sizeof(XT) == 2;
     constexpr int MAX_MT = NE == 1 ? (BF16 ? 2 : 1) : (BF16 ? 4 : 2);
-    const int parts = partial ? route_parts(T, H, N) : 1;
-    if (parts > 1) {
-        const int per_part = (int)ceil_div(H / RT_BK, parts);
-        hipLaunchKernelGGL((route_kernel<NE, 1, true, XT>), dim3((unsigned)ceil_div(T, UNIT), (unsigned)ceil_div(H / RT_BK, per_part)), block, 0,
-                           stream, x, T, H, wr, N, K, renorm, nullptr, nullptr, nullptr, nullptr, partial, per_part);
-        hipLaunchKernelGGL(route_parts_kernel<NE>, dim3((unsigned)ceil_div(T, RT_BLOCK / RT_LANES)), block, 0, stream, partial,
-                           (int)ceil_div(H / RT_BK, per_part), T, N, K, renorm, out_idx, out_w, out_margin, out_probs);
-        return check_hip(hipGetLastError(), "route_parts_kernel launch");
+    const int parts = BF16 ? 1 : part_count(H), per_part = part_slices(H);
+    bool ranked_apart = false;
+    if constexpr (BF16) {
+        if (logits && few_tokens(T, H, N)) {
+            hipLaunchKernelGGL(route_few_kernel, dim3((unsigned)ceil_div(T, 32), (unsigned)expert_tiles(N)), dim3(RF_THREADS), 0, stream, x, T, H, wr, N,
+                               logits, logit_pitch(N));
+            ranked_apart = true;
+        }
+    } else if (logits && one_share_each(T, H, N)) {
+        hipLaunchKernelGGL((route_kernel<NE, 1, true, XT>), dim3((unsigned)ceil_div(T, UNIT), (unsigned)parts), block, 0, stream, x, T, H, wr, N, K,
+                           renorm, nullptr, nullptr, nullptr, nullptr, logits, per_part);
+        ranked_apart = true;
+    }
+    if (ranked_apart) {
+        hipLaunchKernelGGL(route_rank_kernel<NE>, dim3((unsigned)ceil_div(T, RT_BLOCK / RT_LANES)), block, 0, stream, logits, parts, T, N, K, renorm,
+                           out_idx, out_w, out_margin, out_probs);
+        return check_hip(hipGetLastError(), "route_rank_kernel launch");
     }
     int cus = 0;
     const remoe_status st = compute_units(&cus);
@@ -464,33 +646,40 @@ remoe_status launch_tiles(const XT *x, int64_t T, int H, const float *wr, int N,
 template <typename XT>
 remoe_status launch_typed(const XT *x, int64_t T, int H, const float *wr, int N, int K, int renorm,
                           int32_t *out_idx, float *out_w, float *out_margin, float *out_probs,
-                          float *partial, hipStream_t stream)
+                          float *logits, hipStream_t stream)
 {
-    if (N <= 32) return launch_tiles<1, XT>(x, T, H, wr, N, K, renorm, out_idx, out_w, out_margin, out_probs, partial, stream);
-    if (N <= 64) return launch_tiles<2, XT>(x, T, H, wr, N, K, renorm, out_idx, out_w, out_margin, out_probs, partial, stream);
-    return launch_tiles<4, XT>(x, T, H, wr, N, K, renorm, out_idx, out_w, out_margin, out_probs, partial, stream);
+    if (N <= 32) return launch_tiles<1, XT>(x, T, H, wr, N, K, renorm, out_idx, out_w, out_margin, out_probs, logits, stream);
+    if (N <= 64) return launch_tiles<2, XT>(x, T, H, wr, N, K, renorm, out_idx, out_w, out_margin, out_probs, logits, stream);
+    return launch_tiles<4, XT>(x, T, H, wr, N, K, renorm, out_idx, out_w, out_margin, out_probs, logits, stream);
 }
 
 }  // namespace
 
-// What any batch of up to T tokens takes (so that more tokens never need less): rows of one share for at most
-// RT_PART_BLOCKS blocks of tokens, 4 MB.
-size_t route_scratch_bytes(int64_t T, int H, int N)
+// What any batch of up to T tokens takes (so that more tokens never need less): 1 MB at most, 16 MB for fp32.
+size_t route_scratch_bytes(int x_dtype, int64_t T, int H, int N)
 {
-    const int64_t rows = most_parts(H) * T, most = (int64_t)RT_PART_BLOCKS * block_tokens(N);
-    return most_parts(H) > 1 ? sizeof(float) * (size_t)(rows < most ? rows : most) * 32 * expert_tiles(N) : 0;
+    int64_t rows = 0, most = 0;
+    if (x_dtype == REMOE_BF16 && few_tokens(1, H, N)) {
+        rows = T;
+        most = RF_BLOCKS / expert_tiles(N) * 32;
+    }
+    if (x_dtype == REMOE_F32 && one_share_each(1, H, N)) {
+        rows = part_count(H) * T;
+        most = (int64_t)RT_PART_BLOCKS * (4096 / logit_pitch(N));
+    }
+    return sizeof(float) * (size_t)(rows < most ? rows : most) * logit_pitch(N);
 }
 
 remoe_status launch_route(const void *x, int x_dtype, int64_t T, int H, const float *w_router,
                           int N, int K, int renorm, int32_t *out_idx, float *out_w,
-                          float *out_margin, float *out_probs, float *partial, hipStream_t stream)
+                          float *out_margin, float *out_probs, float *logits, hipStream_t stream)
 {
     if (T == 0) return REMOE_OK;
     if (x_dtype == REMOE_F32)
         return launch_typed<float>(static_cast<const float *>(x), T, H, w_router, N, K, renorm,
-                                   out_idx, out_w, out_margin, out_probs, partial, stream);
+                                   out_idx, out_w, out_margin, out_probs, logits, stream);
     return launch_typed<bf16_t>(static_cast<const bf16_t *>(x), T, H, w_router, N, K, renorm,
-                                out_idx, out_w, out_margin, out_probs, partial, stream);
+                                out_idx, out_w, out_margin, out_probs, logits, stream);
 }
 
 }  // namespace remoe

@@ -1,5 +1,6 @@
-"""Layers whose router takes its reduction in shares: shares of unequal length, one and several expert tiles, ragged token
-blocks, the token counts at which the number of shares changes; the ids and weights against the oracle."""
+"""Layers of few tokens, whose router spreads over expert tiles and producer wavefronts: one and several tiles, ragged
+ones and ragged token blocks, both sides of the token counts at which it gives way; the ids and weights
+against the oracle, and bit for bit against moe_route."""
 import pytest
 import torch
 
@@ -31,3 +32,35 @@ def test_layer_router_in_shares(T, H, N, K, dtype):
                       None, None, None, None, y, idx, w, ws)
     torch.cuda.synchronize()
     compare_routing(idx, w, oracle.route(x.cpu(), wr.cpu(), K, True, want_probs=True), True)
+
+
+@pytest.mark.parametrize("H,N,K,dtype,counts", [
+    (2048, 128, 8, "bf16", (1, 33, 2048, 2049, 8193, 16385)), (1152, 96, 2, "bf16", (2720, 2721)), (1408, 60, 4, "bf16", (129, 4096, 4097, 16385)),
+    (2176, 20, 2, "bf16", (7, 8192, 8193)), (1056, 128, 8, "f32", (70, 4097, 8192, 8193)), (1312, 33, 2, "f32", (65, 13056, 13057, 16385)),
+    (2080, 20, 1, "f32", (130, 18688, 18689))])
+def test_routing_is_the_same_in_any_batch_and_from_either_entry_point(H, N, K, dtype, counts):
+    """Bit for bit: a token's ids and weights from moe_forward and moe_route, on both sides of every change of the
+    router's kernel and of its block width."""
+    tdt, inter, T = (torch.float32 if dtype == "f32" else torch.bfloat16), 64, max(counts)
+    desc = remoe.LayerDesc(H, N, inter, K, 0, 0, 0, 0 if dtype == "f32" else 1)
+    x = wl.ar1_hidden_states(83, 1, T, H, 0.0, tdt, DEV)[0].contiguous()
+    g = lambda name, shape, dt: wl.gaussian(83, name, shape, 0.1, 0, N, dt, DEV)
+    wr = g("w_router", (N, H), torch.float32)
+    w = [g("w_gate", (N, inter, H), tdt), g("w_up", (N, inter, H), tdt), g("w_down", (N, H, inter), tdt)]
+
+    def out(t):
+        return torch.full((t, K), -1, dtype=torch.int32, device=DEV), torch.full((t, K), float("nan"), device=DEV)
+
+    ref_idx, ref_w = out(T)
+    remoe.moe_route(desc, x, wr, ref_idx, ref_w, None, None)
+    for t in counts:
+        print(f"route T={t} H={H} N={N} K={K} {dtype}", flush=True)
+        for entry in ("route", "forward"):
+            idx, gw = out(t)
+            if entry == "route":
+                remoe.moe_route(desc, x[:t], wr, idx, gw, None, None)
+            else:
+                ws = torch.full((remoe.remoe_workspace_bytes(desc, t),), 0xFF, dtype=torch.uint8, device=DEV)
+                remoe.moe_forward(desc, x[:t], wr, *w, None, None, None, None, torch.empty(t, H, dtype=tdt, device=DEV), idx, gw, ws)
+            torch.cuda.synchronize()
+            assert torch.equal(idx, ref_idx[:t]) and torch.equal(gw, ref_w[:t]), f"{entry} of {t} tokens"
