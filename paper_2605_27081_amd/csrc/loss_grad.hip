@@ -128,16 +128,16 @@ __global__ __launch_bounds__(LR_WAVES * 64) void loss_grad_kernel(const GradArgs
                 const int e = E[(t - 1) * K + j];
 #pragma unroll
                 for (int h = 0; h < HALVES; ++h)
-                    if (e == lane + 64 * h) g[h] += c_reuse;
+                    if (e == lane + 64 * h && p[h] > 0.0) g[h] += c_reuse;
             }
         double dot = 0.0;
 #pragma unroll
-        for (int h = 0; h < HALVES; ++h) dot += p[h] > 0.0 ? p[h] * g[h] : 0.0;      // entries with P = 0 get 0
+        for (int h = 0; h < HALVES; ++h) dot += p[h] * g[h];      // g = 0 where P = 0; a NaN goes into every entry of its step
         dot = wsum64(dot);
         float *o = a.dlogits + (s * T + t) * N;
 #pragma unroll
         for (int h = 0; h < HALVES; ++h)
-            if (lane + 64 * h < N) o[lane + 64 * h] = p[h] > 0.0 ? (float)(p[h] * (g[h] - dot)) : 0.f;
+            if (lane + 64 * h < N) o[lane + 64 * h] = (float)(p[h] * (g[h] - dot));
     }
 }
 

@@ -37,7 +37,7 @@ __device__ __forceinline__ void fill_log_table(double2 *table)
     }
 }
 
-// ln p for p > 0, -inf otherwise
+// ln p: -inf for 0, inf for inf, NaN for NaN and for p < 0 (what the hardware's logarithm says of them)
 __device__ __forceinline__ double log_f32(float p, const double2 *table)
 {
     uint32_t u = __float_as_uint(p);
@@ -57,7 +57,7 @@ __device__ __forceinline__ double log_f32(float p, const double2 *table)
     q = fma(r, q, 1.0 / 3.0);
     q = fma(r, q, -0.5);
     const double v = fma((double)k, 0.693147180559945309417, e.y) + fma(r * r, q, r);
-    return p > 0.f ? v : -__builtin_inf();
+    return p > 0.f && p < __builtin_inff() ? v : (double)__builtin_amdgcn_logf(p);
 }
 
 // Every logarithm a step needs belongs to its own row or to the row of a partner step t +- d, and every row is

@@ -36,3 +36,53 @@ def test_losses_across_blocks(S, T, N, K, window, lags):
     grad = oracle.remoe_loss_grad(P, Q, idx, lags, window, coef)
     err = ((dz.cpu().double() - grad).abs().amax() / grad.abs().amax()).item()
     assert err <= 1.5e-7, err                                             # one rounding to fp32
+
+
+def _grad(P, Q, idx, lags, window, coef, vals):
+    S, T, N = P.shape
+    dz = torch.zeros(S, T, N, device=DEV)
+    remoe.remoe_loss_backward(P.to(DEV), Q.to(DEV), idx.to(DEV), lags, window, coef, vals, dz,
+                              torch.empty(remoe.remoe_loss_backward_workspace_bytes(S, T, N, window), dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    return dz.cpu()
+
+
+@pytest.mark.parametrize("N", [60, 128])
+def test_numbers_that_are_not_finite_stay_visible(N):
+    """A NaN probability makes every step that it is a partner of NaN and no other; a diverged sequence has no
+    finite gradient; ln keeps infinities and NaNs of either distribution."""
+    print(f"loss not finite N={N}", flush=True)
+    S, T, K, window, lags, coef = 2, 90, 4, 8, [1, 5, 70], [1.0, 0.4, 0.7, 0.3, 0.2]
+    g = torch.Generator().manual_seed(N)
+    P, Q = (torch.softmax(torch.randn(S, T, N, generator=g), -1) for _ in range(2))
+    P[:, :, 3] = 0.0                                  # 0 gets 0, but not in a row without a finite gradient
+    idx = torch.rand(S, T, N, generator=g).topk(K, -1).indices.int()
+    vals = torch.empty(S, 6, dtype=torch.float64, device=DEV)
+    ws = torch.empty(remoe.remoe_loss_workspace_bytes(S), dtype=torch.uint8, device=DEV)
+    Q[:, :, 3] = 0.0
+    remoe.remoe_loss_forward(P.to(DEV), Q.to(DEV), idx.to(DEV), lags, window, vals, ws)
+    clean = _grad(P, Q, idx, lags, window, coef, vals)
+    assert torch.isfinite(clean).all() and (clean[:, :, 3] == 0).all()
+
+    t, e = 15, N - 2
+    bad = P.clone()
+    bad[0, t, e] = float("nan")
+    hit = {t} | {t + s * d for d in lags for s in (-1, 1)} | set(range(t - t % window, t - t % window + window))
+    hit = torch.tensor([u in hit for u in range(T)])
+    dz = _grad(bad, Q, idx, lags, window, coef, vals)
+    assert torch.isnan(dz[0, hit]).all()
+    assert torch.equal(dz[0, ~hit], clean[0, ~hit]) and torch.equal(dz[1], clean[1])
+    bad[1] = float("nan")
+    assert torch.isnan(_grad(bad, Q, idx, lags, window, coef, vals)[1]).all()
+
+    for value, want in ((float("inf"), float("-inf")), (float("nan"), float("nan"))):
+        ref = Q.clone()
+        ref[0, t, e] = value
+        out = torch.empty_like(vals)
+        remoe.remoe_loss_forward(P.to(DEV), ref.to(DEV), idx.to(DEV), lags, window, out, ws)
+        torch.cuda.synchronize()
+        trust = out[0, 2].item()
+        assert trust == want or (want != want and trust != trust)
+        assert torch.equal(out[1], vals[1])
+        dz = _grad(P, ref, idx, lags, window, coef, vals)
+        assert not torch.isfinite(dz[0, t]).any() and torch.isfinite(dz[0, t + 1]).all()
