@@ -391,6 +391,11 @@ __global__ __launch_bounds__(GG_WAVES * 64) void gate_grad_partial_kernel(const 
     }
 }
 
+// FROM_BF16: an infinite dz, or one that rounds to infinity in bf16 (about 3.4e38 and more), leaves inf - inf in its
+// pieces and so a NaN in its expert's sums.  A sum that is NaN is therefore taken again from the values themselves (in
+// fp64, up to the first NaN).  Looking for such dz while they are split costs 1.6 of 27 us, walking the tokens a second time
+// in the kernel above 10 us (registers).
+template <bool FROM_BF16>
 __global__ void gate_grad_reduce_kernel(const GateArgs a)
 {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -399,6 +404,13 @@ __global__ void gate_grad_reduce_kernel(const GateArgs a)
     float v = 0.f;
 #pragma unroll 8
     for (int c = 0; c < a.chunks; ++c) v += a.partial[(int64_t)c * total + q];
+    if (FROM_BF16 && v != v) {
+        const float *dz = a.dz + q / a.H;
+        const bf16_t *x = static_cast<const bf16_t *>(a.x) + q % a.H;
+        double sum = 0.0;
+        for (int64_t t = 0; t < a.T && sum == sum; ++t) sum += (double)dz[t * a.N] * (double)__uint_as_float((uint32_t)x[t * a.H] << 16);
+        v = (float)sum;
+    }
     a.dw[q] = v;
 }
 
@@ -483,7 +495,8 @@ remoe_status launch_gate_grad(const float *dz, const void *x, int x_dtype, int64
         }
     }
     const int64_t total = (int64_t)N * H;
-    hipLaunchKernelGGL(gate_grad_reduce_kernel, dim3((unsigned)ceil_div(total, 256)), dim3(256), 0, stream, a);
+    auto reduce = x_dtype == REMOE_BF16 ? gate_grad_reduce_kernel<true> : gate_grad_reduce_kernel<false>;
+    hipLaunchKernelGGL(reduce, dim3((unsigned)ceil_div(total, 256)), dim3(256), 0, stream, a);
     return check_hip(hipGetLastError(), "gate gradient kernels launch");
 }
 
