@@ -185,6 +185,11 @@ __device__ __forceinline__ void route_topk(const float *row, int sub, int64_t t,
     for (int j = 0; j < E; ++j) part += __expf(val[j] - zmax);
     const float den = sum8(part);
 
+    // an expert that is out, taken or never there, is a NaN: a maximum passes it over and nothing equals it, not even
+    // where the logits that are left are -inf
+    const float OUT = __builtin_nanf("");
+#pragma unroll
+    for (int j = 0; j < E; ++j) val[j] = e0 + j < N ? val[j] : OUT;
     float my_v = NEG_INF, zk = zmax, zk1 = NEG_INF;
     int my_e = 0;
     const int rounds = (out_margin && K < N) ? K + 1 : K;
@@ -201,7 +206,7 @@ __device__ __forceinline__ void route_topk(const float *row, int sub, int64_t t,
         m = NEG_INF;
 #pragma unroll
         for (int j = 0; j < E; ++j) {
-            val[j] = (j == gone) ? NEG_INF : val[j];
+            val[j] = (j == gone) ? OUT : val[j];
             m = fmaxf(m, val[j]);
         }
         top = max8(m);

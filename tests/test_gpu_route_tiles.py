@@ -36,3 +36,24 @@ def test_route_block_edges(T, H, N, K, dtype):
     # fp32 softmax of logits of a few units: a few 1e-7 from the exponential and the sums (as in the other router tests)
     assert torch.allclose(probs.cpu().double(), orc["probs"], rtol=2e-5, atol=1e-7)
     assert torch.allclose(margin.cpu().double(), orc["margin"], rtol=1e-4, atol=2e-5)
+
+
+@pytest.mark.parametrize("N,dtype", [(20, "f32"), (33, "bf16"), (64, "f32"), (100, "bf16"), (128, "bf16")])
+def test_logits_of_minus_infinity_are_ranked_by_id(N, dtype):
+    """Fewer finite logits than places: the experts whose logit is -inf follow in the order of their ids, none twice."""
+    print(f"route -inf N={N} {dtype}", flush=True)
+    T, H, K, finite = 5, 128, 8, (N - 3, 4)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    x = torch.full((T, H), 2.0 ** 70, dtype=tdt, device=DEV)
+    wr = torch.full((N, H), -2.0 ** 70, device=DEV)                   # products of -2^140
+    wr[finite[0]], wr[finite[1]] = 2.0 ** -77, 0.0                    # logits 1 and 0
+    desc = remoe.LayerDesc(H, N, 64, K, 0, 0, 0, 0 if dtype == "f32" else 1)
+    idx = torch.full((T, K), -1, dtype=torch.int32, device=DEV)
+    w, margin, probs = (torch.full(s, 7.0, device=DEV) for s in ((T, K), (T,), (T, N)))
+    remoe.moe_route(desc, x, wr, idx, w, margin, probs)
+    torch.cuda.synchronize()
+    want = list(finite) + [e for e in range(N) if e not in finite][:K - 2]
+    assert idx.cpu().tolist() == [want] * T
+    p1 = torch.sigmoid(torch.tensor(1.0))
+    assert torch.allclose(w.cpu()[:, 0], p1, rtol=1e-6) and torch.allclose(w.cpu()[:, 1], 1 - p1, rtol=1e-6) and (w.cpu()[:, 2:] == 0).all()
+    assert ((probs.cpu() > 0).sum(1) == 2).all()
