@@ -121,9 +121,9 @@ __device__ __forceinline__ u64 sort64(u64 v, int lane, bool down)
 }
 
 // Entry of the list: expert in the low seven bits, bit 7 = the score it has as a resident.  Two equal first
-// entries say that the row has no list: probabilities that are negative or no numbers, or bonuses that
-// rounding makes equal in an order other than that of the ids (the boosted list is taken to be in the order
-// of the plain one).  The last of the 64 boosted scores kept could tie with one that was not, hence 63 entries.
+// entries say that the row has no list: probabilities that are negative or no numbers, bonuses that
+// overflow (more of those tie than the 64 kept), or bonuses that rounding makes equal in an order other than that
+// of the ids (the boosted list is taken to be in the order of the plain one).  The last of the 64 boosted scores kept could tie with one that was not, hence 63 entries.
 template <bool WIDE>
 __global__ __launch_bounds__(256) void reroute_rank_kernel(const float *__restrict__ probs, int64_t rows, int N, float factor, RowLayout lay,
                                                            int32_t *out_idx, float *out_w)
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void reroute_rank_kernel(const float *__restri
         const u64 b = a ? ((u64)__float_as_uint(boosted) << 32) | (uint32_t)a | 1u : 0ull;
         const u64 after = ((u64)(uint32_t)__shfl_down((int)(uint32_t)(b >> 32), 1, 64) << 32) |
                           (uint32_t)__shfl_down((int)(uint32_t)b, 1, 64);
-        bad = bad || (lane < 63 && after > b) || __float_as_uint(boosted) > 0x7F800000u;
+        bad = bad || (lane < 63 && after > b) || __float_as_uint(boosted) >= 0x7F800000u;
         const u64 rev = ((u64)(uint32_t)__shfl_xor((int)(uint32_t)(b >> 32), 63, 64) << 32) |
                         (uint32_t)__shfl_xor((int)(uint32_t)b, 63, 64);
         const u64 m = merge<32>(a > rev ? a : rev, lane, true);

@@ -49,3 +49,28 @@ def test_reroute_edges_match_oracle(S, T, N, K, C, factor, renorm, kind):
     assert torch.equal(idx.cpu(), ref["idx"]) and torch.equal(miss.cpu(), ref["miss"]) and torch.equal(tot.cpu(), ref["total_miss"])
     if kind != "tiny":                         # a sum of K fp32 values and a division: K + 1 roundings of 2^-24
         assert torch.allclose(w.cpu().double(), ref["w"], rtol=(K + 1) * 2.0 ** -24, atol=1e-12 if kind != "signed" else 1e-5)
+
+
+def _reroute(p, K, C, factor):
+    S, T, _ = p.shape
+    idx = torch.full((S, T, K), -1, dtype=torch.int32, device=DEV)
+    w = torch.full((S, T, K), 7.0, dtype=torch.float32, device=DEV)
+    miss = torch.full((S, T), 255, dtype=torch.uint8, device=DEV)
+    tot = torch.full((S,), -1, dtype=torch.int64, device=DEV)
+    remoe.reroute_lru(p.to(DEV), K, C, factor, False, idx, w, miss, tot)
+    torch.cuda.synchronize()
+    return idx.cpu(), miss.cpu(), tot.cpu()
+
+
+@pytest.mark.parametrize("N,K,C", [(128, 8, 100), (128, 9, 18), (90, 2, 90)])
+def test_bonuses_that_overflow_are_ranked_by_id(N, K, C):
+    """Scores large enough that more boosted ones than a list holds are infinite: ties go to the lower id."""
+    print(f"reroute overflow N={N} K={K} C={C}", flush=True)
+    T, e = 60, torch.arange(N)
+    p = torch.zeros(1, T, N)
+    p[0, 0::3] = (e < K) * (2.0 + e)                                  # K low ids come in,
+    p[0, 1::3] = ((e >= N - 64) & (e < N - 64 + K)) * (2.0 + e)       # then K of the last 64, then those lead in the order of
+    p[0, 2::3] = 200.0 - e.roll(N - 64)                              # their ids and all residents' bonuses overflow
+    idx, miss, tot = _reroute(p, K, C, 2.9e38)
+    ref = oracle.reroute_lru(p, K, C, 2.9e38, False)
+    assert torch.equal(idx, ref["idx"]) and torch.equal(miss, ref["miss"]) and torch.equal(tot, ref["total_miss"])
