@@ -248,14 +248,15 @@ __device__ __forceinline__ uint32_t walk(const float *__restrict__ probs, int64_
                 // K rounds of wavefront maximum over the boosted scores
                 const float *pr = probs + (s * T + tb + a) * N;
                 const float NEG_INF = -__builtin_inff();
-                const float p0 = lane < N ? pr[lane] : 0.f, p1 = lane + 64 < N ? pr[lane + 64] : 0.f;
+                const float p0 = lane < N ? pr[lane] : 0.f, p1 = WIDE && lane + 64 < N ? pr[lane + 64] : 0.f;
                 const u64 res_lo = ballot(k0 >= cut), res_hi = WIDE ? ballot(k1 >= cut) : 0ull;
                 float m0 = lane < N ? (k0 >= cut ? p0 * factor : p0) : NEG_INF;
-                float m1 = lane + 64 < N ? (k1 >= cut ? p1 * factor : p1) : NEG_INF;
+                float m1 = WIDE && lane + 64 < N ? (k1 >= cut ? p1 * factor : p1) : NEG_INF;
                 u64 sel_lo = 0ull, sel_hi = 0ull;
                 for (int j = 0; j < K; ++j) {
-                    const float m = wave_max(fmaxf(m0, m1));
-                    const u64 b0 = ballot(m0 == m), b1 = ballot(m1 == m);
+                    // (64 NaNs: nothing equals the maximum, and expert 63 stands for them)
+                    const float m = wave_max(WIDE ? fmaxf(m0, m1) : m0);
+                    const u64 b0 = ballot(m0 == m), b1 = WIDE ? ballot(m1 == m) : 0ull;
                     const int x = b0 ? __ffsll((long long)b0) - 1 : 63 + __ffsll((long long)b1);
                     if (lane == j) e = (uint32_t)x;
                     if (x == lane) m0 = NEG_INF;

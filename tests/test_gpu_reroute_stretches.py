@@ -74,3 +74,26 @@ def test_bonuses_that_overflow_are_ranked_by_id(N, K, C):
     idx, miss, tot = _reroute(p, K, C, 2.9e38)
     ref = oracle.reroute_lru(p, K, C, 2.9e38, False)
     assert torch.equal(idx, ref["idx"]) and torch.equal(miss, ref["miss"]) and torch.equal(tot, ref["total_miss"])
+
+
+@pytest.mark.parametrize("N,T", [(64, 40), (64, 900), (128, 40)])
+def test_steps_of_nans_leave_the_others_alone(N, T):
+    """A step whose probabilities are all NaN names expert 63 in every place and touches it; what follows is rerouted
+    from that cache, which keeps its capacity."""
+    print(f"reroute NaN N={N} T={T}", flush=True)
+    K, C, factor = 4, 6, 3.0
+    p = _scores("plain", 1, T, N)
+    p[0, 5::11] = float("nan")
+    idx, miss, tot = _reroute(p, K, C, factor)
+    cache, misses = [], []                                             # least recent first
+    for t in range(T):
+        if torch.isnan(p[0, t]).any():
+            want = [63] * K
+        else:
+            score = p[0, t].clone()
+            score[cache] *= factor
+            want = sorted(range(N), key=lambda e: (-float(score[e]), e))[:K]
+        assert idx[0, t].tolist() == want, t
+        misses.append(len(set(want) - set(cache)))
+        cache = ([e for e in cache if e not in want] + sorted(set(want)))[-C:]
+    assert miss[0].tolist() == misses and int(tot) == sum(misses)
