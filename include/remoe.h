@@ -404,9 +404,10 @@ remoe_status remoe_loss_forward(const float *probs, const float *probs_ref, cons
  *   workspace     remoe_loss_backward_workspace_bytes(S, T, N_r, window) bytes, 8-byte aligned
  *
  * remoe_gate_grad -- the gate gradient of a router without bias (Sec. 3.1: z_t = W_r x_t):
- *   dw[e, h] = sum_t dlogits[t, e] x[t, h]        (fp32 matrix cores, fp32 accumulation; the sum over
- *   tokens is split into chunks whose partial results are added in a fixed order: results repeat
- *   bit for bit)
+ *   dw[e, h] = sum_t dlogits[t, e] x[t, h]        (fp32 accumulation; fp32 x on the fp32 matrix cores, bf16 x
+ *   on the bf16 ones with dlogits in three exact bf16 pieces; the sum over tokens is split into chunks
+ *   whose partial results are added in a fixed order: results repeat bit for bit.  A sum that comes out
+ *   NaN from the pieces is taken again from the values: infinite dlogits act as in fp32)
  *   dlogits [T, N_r] fp32 (all sequences flattened); x [T, H] of x_dtype (REMOE_F32 / REMOE_BF16);
  *   dw [N_r, H] fp32, overwritten; workspace remoe_gate_grad_workspace_bytes(T, N_r, H) bytes,
  *   256-byte aligned.  n_experts <= 128, hidden % 64 == 0.

@@ -141,9 +141,9 @@ remoe_status validate_layer_desc(const remoe_layer_desc *d)
 struct Workspace {
     size_t total = 0;
     PermuteBuffers pb{};
-    void *hbuf = nullptr;     // [T*K, I]            SwiGLU activations of the routed experts
-    void *hsbuf = nullptr;    // [T, I_s]            SwiGLU activations of the shared expert
-    void *rows = nullptr;     // [T*K (+T), H]       weighted per-(token, expert) outputs, then shared rows
+    void *hbuf = nullptr;     // [T*K, h_pitch]      SwiGLU activations of the routed experts
+    void *hsbuf = nullptr;    // [T, hs_pitch]       SwiGLU activations of the shared expert
+    void *rows = nullptr;     // [T*K (+T), H]       per-(token, expert) outputs, not yet weighted, then shared rows
     float *logits = nullptr;  // the router's logits, where it takes them through memory
     int tile_m = 0;           // rows of a GEMM row tile
     int h_pitch = 0, hs_pitch = 0;   // row pitches of hbuf, hsbuf
@@ -157,7 +157,7 @@ template <typename P> void carve(char *base, size_t &off, P *&ptr, size_t bytes)
     off += bytes;
 }
 
-// Rows per GEMM row tile: 256 (gemm_bf16.hip, and fp32 layers) or 32, 64, 128 (gemm_stream.hip).  Few rows per expert
+// Rows per GEMM row tile: 256 (gemm_bf16.hip) or 32, 64, 128 (gemm_stream.hip; fp32 layers: 32 or 64).  Few rows per expert
 // leave a tall tile empty, and a launch of few tiles leaves compute units idle; tall tiles in turn fetch
 // fewer operand bytes per product.  The lines below are where the whole layer's time crosses, measured on layers of
 // 8 to 128 experts, H 1024-4096, I 512-1472, with and without shared expert, for example (us, smaller / larger tile):

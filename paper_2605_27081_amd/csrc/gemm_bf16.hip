@@ -35,9 +35,9 @@
 // Launches of few tiles.  The first three tiles of every workgroup used to be claimed from the counters when
 // it started, three neighbouring tiles at once: with fewer than 3 x 256 tiles some compute units then ran
 // three tiles in a row while others had none.  They are now dealt out round by round.  The shared expert's
-// tiles run in the same launch, so that one launch end less leaves compute units idle.  Whole layer,
-// before / after both: DeepSeek-V2-Lite-shaped, 4,096 tokens 811 / 662 us, 16,384 tokens 2149 / 2073 us;
-// Qwen3-shaped, 4,096 tokens 558 / 497 us, 65,536 tokens 4741 / 4730 us.
+// tiles run in the same launch, so that one launch end less leaves compute units idle.  Whole layer of AR(1) hidden
+// states, before / after both (router and sort, about 20 us faster too, included): DeepSeek-V2-Lite-shaped, 4,096
+// tokens 867 / 757 us, 16,384 tokens 2200 / 2110 us; Qwen3-shaped, 4,096 tokens 578 / 520 us, 65,536 tokens no change.
 #include "common.h"
 #include "lds_copy.h"
 

@@ -10,9 +10,11 @@
 // move global -> LDS directly, in full 128-byte lines, into a ring of STAGES stages with one barrier per
 // slice.  What bounds it is the weight bytes in flight: MB = 1 keeps 3 slices x 16 KB x 2 workgroups per
 // compute unit on their way.  Measured on a Qwen3-shaped layer (128 experts, H 2048, I 768), the two
-// GEMMs together, 256-row kernel before / this kernel: 16 tokens 218 / 122 us (0.77 GB of weights at
-// 6.3 TB/s), 333 tokens 327 / 213 us (1.2 GB at 5.7 TB/s).  Slices of 32 k-values (64-byte rows) with twice
-// the stages were 5-10 % slower throughout.
+// GEMMs together, 256-row kernel before / this kernel: 16 tokens 218 / 128 us (0.72 GB past the L2 at
+// 5.6 TB/s, matrix cores busy 8 % of the time), 333 tokens 327 / 221 us (1.24 GB at 5.6 TB/s, 9 %).  With 128-row
+// tiles (1021 tokens, 60 experts, shared expert) 1.69 GB pass the L2s at the same rate, half as much again as there
+// are weights, and the matrix cores are busy 30 %.  Slices of 32 k-values (64-byte rows) with twice the stages
+// were 5-10 % slower throughout.
 //
 // The MFMAs take the weight rows as their first operand, so a lane owns one slot (row of the output) and,
 // per group of four accumulators, four adjacent weight rows.  In mode 0 every 32-row group of the weights is
