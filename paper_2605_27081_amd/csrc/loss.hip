@@ -65,8 +65,9 @@ __global__ __launch_bounds__(LR_WAVES * 64) void loss_partial_kernel(const LossA
     const int32_t *E = a.idx + s * T * K;
     double acc[LS_TERMS] = {0.0, 0.0, 0.0, 0.0, 0.0};
     fill_log_table(table);
-    bool has_unit = false;
-    for (int i = 0; i < a.n_lags; ++i) has_unit |= a.lags[i] == 1;
+    int unit = -1;                      // the lag that is L_Smooth's partner too (the first one, should it be given twice)
+    for (int i = a.n_lags - 1; i >= 0; --i)
+        if (a.lags[i] == 1) unit = i;
 
     const int64_t per = (T + LS_CHUNKS - 1) / LS_CHUNKS;
     const int64_t t_lo = chunk * per, t_hi = (t_lo + per < T) ? t_lo + per : T;
@@ -85,14 +86,14 @@ __global__ __launch_bounds__(LR_WAVES * 64) void loss_partial_kernel(const LossA
                 const double p = (double)P[t * N + e], lp = logs[(t - r0) * N + e];
                 acc[1] += kl_part(p, lp, log_f32(Q[t * N + e], table));
                 if (t < 1) continue;
-                if (!has_unit) acc[2] += symkl_part(p, lp, (double)P[(t - 1) * N + e], logs[(t - 1 - r0) * N + e]);
+                if (unit < 0) acc[2] += symkl_part(p, lp, (double)P[(t - 1) * N + e], logs[(t - 1 - r0) * N + e]);
                 for (int i = 0; i < a.n_lags; ++i) {
                     const int d = a.lags[i];
                     if (t - d < 0) continue;
                     const double r = (double)P[(t - d) * N + e];
                     const double v = symkl_part(p, lp, r, d <= a.blk.halo ? logs[(t - d - r0) * N + e] : log_f32((float)r, table));
                     acc[3] += v;
-                    if (d == 1) acc[2] += v;
+                    if (i == unit) acc[2] += v;
                 }
             }
         }

@@ -38,6 +38,10 @@ def test_losses_across_blocks(S, T, N, K, window, lags):
     assert err <= 1.5e-7, err                                             # one rounding to fp32
 
 
+def test_lag_one_given_twice_is_one_smoothness_term():
+    test_losses_across_blocks(2, 90, 60, 4, 8, [1, 5, 1])
+
+
 def _grad(P, Q, idx, lags, window, coef, vals):
     S, T, N = P.shape
     dz = torch.zeros(S, T, N, device=DEV)
