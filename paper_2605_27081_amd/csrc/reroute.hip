@@ -245,22 +245,23 @@ __device__ __forceinline__ uint32_t walk(const float *__restrict__ probs, int64_
             uint32_t e = b & 127u, slot = chosen ? e : 128u + (uint32_t)lane;
             int n_sel = K, miss = __popcll(sel & ~ballot(boost));
             if (((no_list >> a) & 1u) | (__popcll(live_mask) < K)) {
-                // K rounds of wavefront maximum over the boosted scores
+                // K rounds of wavefront maximum over the boosted scores; an expert that is out, taken or never there, is a NaN:
+                // no maximum takes it and nothing equals it, not even where the scores that are left are -inf
                 const float *pr = probs + (s * T + tb + a) * N;
-                const float NEG_INF = -__builtin_inff();
+                const float OUT = __builtin_nanf("");
                 const float p0 = lane < N ? pr[lane] : 0.f, p1 = WIDE && lane + 64 < N ? pr[lane + 64] : 0.f;
                 const u64 res_lo = ballot(k0 >= cut), res_hi = WIDE ? ballot(k1 >= cut) : 0ull;
-                float m0 = lane < N ? (k0 >= cut ? p0 * factor : p0) : NEG_INF;
-                float m1 = WIDE && lane + 64 < N ? (k1 >= cut ? p1 * factor : p1) : NEG_INF;
+                float m0 = lane < N ? (k0 >= cut ? p0 * factor : p0) : OUT;
+                float m1 = WIDE && lane + 64 < N ? (k1 >= cut ? p1 * factor : p1) : OUT;
                 u64 sel_lo = 0ull, sel_hi = 0ull;
                 for (int j = 0; j < K; ++j) {
-                    // (64 NaNs: nothing equals the maximum, and expert 63 stands for them)
                     const float m = wave_max(WIDE ? fmaxf(m0, m1) : m0);
                     const u64 b0 = ballot(m0 == m), b1 = WIDE ? ballot(m1 == m) : 0ull;
-                    const int x = b0 ? __ffsll((long long)b0) - 1 : 63 + __ffsll((long long)b1);
+                    // (where only NaNs are left nothing equals the maximum, and one expert stands for them)
+                    const int x = b0 ? __ffsll((long long)b0) - 1 : b1 ? 63 + __ffsll((long long)b1) : N < 64 ? N - 1 : 63;
                     if (lane == j) e = (uint32_t)x;
-                    if (x == lane) m0 = NEG_INF;
-                    if (x == lane + 64) m1 = NEG_INF;
+                    if (x == lane) m0 = OUT;
+                    if (x == lane + 64) m1 = OUT;
                     if (x < 64) sel_lo |= 1ull << x;
                     else sel_hi |= 1ull << (x - 64);
                 }

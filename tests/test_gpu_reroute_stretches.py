@@ -76,9 +76,9 @@ def test_bonuses_that_overflow_are_ranked_by_id(N, K, C):
     assert torch.equal(idx, ref["idx"]) and torch.equal(miss, ref["miss"]) and torch.equal(tot, ref["total_miss"])
 
 
-@pytest.mark.parametrize("N,T", [(64, 40), (64, 900), (128, 40)])
+@pytest.mark.parametrize("N,T", [(64, 40), (64, 900), (128, 40), (60, 40), (100, 300)])
 def test_steps_of_nans_leave_the_others_alone(N, T):
-    """A step whose probabilities are all NaN names expert 63 in every place and touches it; what follows is rerouted
+    """A step whose probabilities are all NaN names one expert, 63 or the last, in every place and touches it; what follows is rerouted
     from that cache, which keeps its capacity."""
     print(f"reroute NaN N={N} T={T}", flush=True)
     K, C, factor = 4, 6, 3.0
@@ -88,7 +88,7 @@ def test_steps_of_nans_leave_the_others_alone(N, T):
     cache, misses = [], []                                             # least recent first
     for t in range(T):
         if torch.isnan(p[0, t]).any():
-            want = [63] * K
+            want = [min(63, N - 1)] * K
         else:
             score = p[0, t].clone()
             score[cache] *= factor
@@ -97,3 +97,9 @@ def test_steps_of_nans_leave_the_others_alone(N, T):
         misses.append(len(set(want) - set(cache)))
         cache = ([e for e in cache if e not in want] + sorted(set(want)))[-C:]
     assert miss[0].tolist() == misses and int(tot) == sum(misses)
+
+
+@pytest.mark.parametrize("N,K,C", [(16, 16, 1), (63, 63, 63), (64, 64, 40), (100, 64, 90)])
+def test_scores_of_minus_infinity_are_chosen_once(N, K, C):
+    """Bonuses take negative scores to -inf and (nearly) all experts are asked for: none is named twice."""
+    test_reroute_edges_match_oracle(2, 200, N, K, C, 2.9e38, False, "signed")
