@@ -15,19 +15,30 @@
 //                          in their final order: one comparison, one ballot and a lane count instead of K
 //                          wavefront maxima.  A step whose first P entries hold fewer than K in force (or
 //                          that has no list) takes the K maxima from the probabilities instead.
-//                          A trace is walked by up to 16 wavefronts at once, each on its own stretch from a
-//                          guessed cache: a cold one warmed on the steps before the stretch.  A
-//                          stretch counts only if its first state is the last state of the stretch before
-//                          it, key for key; those that fail are walked again from that state until all
-//                          agree, so the result is that of the single walk whatever the guesses were.
+//                          A trace is walked by up to 56 wavefronts at once, each on its own stretch from a
+//                          guessed cache: a cold one warmed on the steps before the stretch.
+//   reroute_check_kernel   every stretch but the first again, from the cache that the choices of the steps before it
+//                          leave, until the cache holds only experts used inside the stretch: if every choice up to
+//                          there is the one made from the guess, so are all that follow.  A stretch that fails sets its
+//                          bit in the trace's word.
+//                          The trace's last workgroup walks the stretches that failed again, in order and as far as
+//                          anything changes, so the result is that of the single walk whatever the guesses were, and
+//                          sums the misses.
+//   reroute_group_kernel   short traces: up to 16 stretches in one workgroup, which compares their states in LDS.
 //   reroute_weights_kernel ids and gate weights from the entries the walk marked.
 // The lists and marks of a step live where its ids and weights will be (8 K bytes), so that no
-// scratch memory is needed: entries r < 4 K in the id row, the marks (one bit per entry) in front of the
-// weight row and the other entries behind them.
+// scratch memory is needed: entries r < 4 K in the id row, the marks (one bit per entry, K but at most 8 bytes) in front of
+// the weight row and the other entries behind them.  There are fewer entries than bits, so the last bit of the marks is
+// free: where it is set the step's K ids stand for the marks, a byte each in their place (K <= 8) or at the end of the
+// weight row.  The bits of the stretches that failed are kept in the trace's total.  Lists are only written by the first kernel and marks only by the stretch's own
+// wavefront, so that a wavefront may warm up on the lists of the stretch before while that one is walked.
 //
-// 16 traces x 4096 steps, 128 experts, top-8, C = 4: 7.5 ms as one walk of K maxima per step and wavefront,
-// 0.19 ms now (lists 37, walk 140, weights 15 us; the
-// walk is bound by the instructions its 16 wavefronts issue: 1.8 us a step before, 0.45 us now with 16 steps at once).
+// 16 traces x 4096 steps, 128 experts, top-8, C = 4: 7.5 ms as one walk of K maxima per step and wavefront, 0.19 ms with
+// 16 stretches of a trace in one workgroup (walk 140 us, bound by the instructions that 16 wavefronts issue on one
+// compute unit), 0.104 ms with 52 stretches of 80 steps over the chip: lists 37, walk 42 (one wavefront per SIMD, bound by
+// the latency of a step), check 16, weights 12 us.
+#include <type_traits>
+
 #include "common.h"
 #include "topk.h"
 
@@ -35,7 +46,11 @@ namespace remoe {
 
 namespace {
 
-constexpr int RR_WAVES = 16;            // stretches of a trace walked at once
+constexpr int RR_GROUP = 16;            // stretches of a trace that one workgroup walks at once
+constexpr int RR_GROUP_STEPS = 512;     // see launch_reroute
+constexpr int RR_STRETCHES = 56;        // of a trace, walked by several: a bit each in the trace's word, whose last eight bits
+                                        // count the workgroups that have checked theirs
+constexpr int RR_BLOCK_WAVES = 4;
 constexpr int RR_MIN_STEPS = 32;        // a shorter stretch is not worth its warm-up
 constexpr int RR_BATCH = 16;            // steps whose lists are staged in LDS at a time
 constexpr int RR_MAX_ENTRIES = 63;      // see reroute_rank_kernel
@@ -44,7 +59,7 @@ struct RowLayout {
     int K, marks, entries;              // marks: bytes in front of the weight row
     __host__ __device__ RowLayout(int N, int K_) : K(K_), marks(K_ < 8 ? K_ : 8)
     {
-        entries = 8 * K - marks;
+        entries = K > 8 ? 7 * K - marks : 8 * K - marks;       // more than 8 ids have a place of their own
         if (entries > 2 * N) entries = 2 * N;
         if (entries > RR_MAX_ENTRIES) entries = RR_MAX_ENTRIES;
     }
@@ -55,6 +70,9 @@ struct RowLayout {
                          : reinterpret_cast<uint8_t *>(w + row * K) + marks + (r - 4 * K);
     }
     __device__ uint8_t *mark(float *w, int64_t row) const { return reinterpret_cast<uint8_t *>(w + row * K); }
+    __device__ bool is_ids(unsigned long long m) const { return (m >> (8 * marks - 1)) & 1ull; }
+    // byte of id j of a row of ids, K > 8
+    __device__ uint8_t *id(float *w, int64_t row, int j) const { return reinterpret_cast<uint8_t *>(w + row * K) + 3 * K + j; }
 };
 
 // value of lane ^ J
@@ -193,22 +211,44 @@ __device__ __forceinline__ int nth(bool in0, bool in1, int n)
     return 63 + __ffsll((long long)ballot(in1 & (n0 + below(g1) == n)));
 }
 
-// One stretch [t0, t1) of a trace from the state in (keys, st).  keys[e] = (step of last use + 1) << 7 | e, 0 =
-// never used; slots 128 + lane take the writes of lanes without an expert.  STORE: marks, misses and
-// the ids of steps without a list are written.  FULL: K >= C.  Returns the misses that this lane counted.
-template <bool WIDE, bool FULL, bool STORE>
-__device__ __forceinline__ uint32_t walk(const float *__restrict__ probs, int64_t s, int64_t T, int64_t t0, int64_t t1, int N, int C, float factor,
-                    const RowLayout lay, int32_t *out_idx, float *out_w, uint8_t *out_miss, uint32_t *keys,
+// The marks of a row (weights are four-byte aligned, not more).
+__device__ __forceinline__ u64 load_marks(const RowLayout &lay, float *w, int64_t row)
+{
+    const uint8_t *mk = lay.mark(w, row);
+    const uint32_t *words = reinterpret_cast<const uint32_t *>(mk);
+    if (lay.marks == 8) return ((u64)words[1] << 32) | words[0];
+    if (lay.marks == 4) return words[0];
+    u64 m = 0ull;
+    for (int q = 0; q < lay.marks; ++q) m |= (u64)mk[q] << (8 * q);
+    return m;
+}
+
+struct WalkEnd {
+    int64_t t;                          // first step not walked
+    uint32_t misses;                    // counted by this lane
+    bool differ;                        // CHECK: some choice was not the stored one
+};
+
+// Steps [t0, t1) of a trace, t0 and stretch multiples of RR_BATCH, from the state in (keys, st).  keys[e] = (step of last
+// use + 1) << 7 | e, 0 = never used; slots 128 + lane take the writes of lanes without an expert.
+// STORE: marks and misses are written.  CHECK: they are compared with the stored ones first, and the walk ends
+// behind a batch when all that is resident was last used since the last difference and since the start of the current
+// stretch: from there on the stored choices stand.  Without STORE it also ends at a difference.  FULL: K >= C.
+template <bool WIDE, bool FULL, bool STORE, bool CHECK>
+__device__ __forceinline__ WalkEnd walk(const float *__restrict__ probs, int64_t s, int64_t T, int64_t t0, int64_t t1, int64_t stretch, int N, int C,
+                    float factor, const RowLayout lay, const int32_t *out_idx, float *out_w, uint8_t *out_miss, uint32_t *keys,
                     uint8_t *lists, WalkState &st)
 {
     const int lane = threadIdx.x & 63, K = lay.K;
     const bool has = lane < lay.entries;
     uint32_t cut = st.cut;
     int held = st.held;
+    int64_t same_from = t0, stretch_end = t0 - t0 % stretch + stretch;
+    bool differ = false;
     uint32_t lane_misses = 0;
     uint32_t next[RR_BATCH];            // the lists of the next batch, a byte per lane and step
     typedef const __attribute__((address_space(1))) uint8_t *global_bytes;
-    global_bytes list = (global_bytes)lay.entry(out_idx, out_w, s * T + t0, has ? lane : 0);
+    global_bytes list = (global_bytes)lay.entry(const_cast<int32_t *>(out_idx), out_w, s * T + t0, has ? lane : 0);
     int left = has ? (int)(t1 - t0) : 0;
     auto fetch = [&] {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -233,7 +273,8 @@ __device__ __forceinline__ uint32_t walk(const float *__restrict__ probs, int64_
         const uint32_t no_list = (uint32_t)ballot(lane < RR_BATCH && lists[lane * 64] == lists[lane * 64 + 1]);
         uint32_t b = lists[lane];
         uint32_t kr = keys[b & 127u];
-        uint32_t o_lo = 0, o_hi = 0, o_miss = 0;              // marks and misses of step tb + lane
+        uint32_t ids_differ = 0;                              // CHECK, K > 8: bit a in any lane
+        uint32_t o_lo = 0, o_hi = 0, o_miss = 0;              // marks (or ids) and misses of step tb + lane
         for (int a = 0; a < n; ++a) {
             const uint32_t t1u = (uint32_t)(tb + a) + 1u, stamp = t1u << 7;
             const uint32_t b_next = lists[(a + 1) * 64 + lane];        // behind the last step: not used
@@ -266,15 +307,17 @@ __device__ __forceinline__ uint32_t walk(const float *__restrict__ probs, int64_
                     else sel_hi |= 1ull << (x - 64);
                 }
                 sel = 0ull;
+                if (K <= 8) {
+                    for (int j = 0; j < K; ++j) sel |= (u64)(uint32_t)__shfl((int)e, j, 64) << (8 * j);
+                } else if (lane < K) {
+                    uint8_t *id = lay.id(out_w, s * T + tb + a, lane);
+                    if (CHECK && *id != (uint8_t)e) ids_differ |= 1u << a;
+                    if (STORE) *id = (uint8_t)e;
+                }
+                sel |= 1ull << (8 * lay.marks - 1);
                 slot = lane < K ? e : 128u + (uint32_t)lane;
                 n_sel = __popcll(sel_lo) + __popcll(sel_hi);
                 miss = __popcll(sel_lo & ~res_lo) + __popcll(sel_hi & ~res_hi);
-                if (STORE) {
-                    // two equal entries, then the ids; a row without marks is one of these
-                    uint8_t *row = lay.entry(out_idx, out_w, s * T + tb + a, 0);
-                    if (lane < 2) row[lane] = 0;
-                    if (lane < K) row[2 + lane] = (uint8_t)e;
-                }
             }
             // one wavefront: its LDS accesses are served in program order
             keys[slot] = stamp | e;
@@ -315,29 +358,101 @@ __device__ __forceinline__ uint32_t walk(const float *__restrict__ probs, int64_
             }
         }
         lane_misses += o_miss;
+        const u64 marks = ((u64)o_hi << 32) | o_lo;
+        const int64_t row = s * T + tb + lane;
+        if (CHECK) {
+            bool other = false;
+            if (lane < n) other = load_marks(lay, out_w, row) != marks || out_miss[row] != (uint8_t)o_miss;
+            u64 others = ballot(other);
+            if (K > 8) {
+                for (int a = 0; a < n; ++a)
+                    if (ballot((ids_differ >> a) & 1u)) others |= 1ull << a;
+            }
+            if (tb >= stretch_end) {
+                same_from = stretch_end;
+                stretch_end += stretch;
+            }
+            if (others) {
+                differ = true;
+                same_from = tb + 64 - __clzll((long long)others);
+            }
+        }
         if (STORE && lane < n) {
-            uint8_t *mk = lay.mark(out_w, s * T + tb + lane);
-            const u64 marks = ((u64)o_hi << 32) | o_lo;
+            uint8_t *mk = lay.mark(out_w, row);
             for (int q = 0; q < lay.marks; ++q) mk[q] = (uint8_t)(marks >> (8 * q));
-            out_miss[s * T + tb + lane] = (uint8_t)o_miss;
+            out_miss[row] = (uint8_t)o_miss;
+        }
+        if (CHECK && ((differ && !STORE) || (int64_t)(cut >> 7) > same_from)) {
+            st = WalkState{cut, held};
+            return WalkEnd{tb + n, lane_misses, differ};
         }
     }
     st.cut = cut;
     st.held = held;
-    return lane_misses;
+    return WalkEnd{t1, lane_misses, differ};
 }
 
+// The state in front of step t from the choices stored for the steps before it: walking back, the first C experts met,
+// within a step the higher ids first.
+template <bool WIDE>
+__device__ __forceinline__ WalkState state_before(int64_t s, int64_t T, int64_t t, int C, const RowLayout lay, const int32_t *out_idx, float *out_w,
+                                                  uint32_t *keys)
+{
+    const int lane = threadIdx.x & 63, K = lay.K;
+    const bool has = lane < lay.entries;
+    keys[lane] = 0u;
+    keys[lane + 64] = 0u;
+    int count = 0;
+    for (int64_t tb = t; tb > 0; tb -= RR_BATCH) {
+        const int n = tb < RR_BATCH ? (int)tb : RR_BATCH;
+        uint32_t entry[RR_BATCH];
+#pragma unroll
+        for (int a = 0; a < RR_BATCH; ++a) {
+            const int64_t row = s * T + (a < n ? tb - 1 - a : 0);
+            entry[a] = has ? *lay.entry(const_cast<int32_t *>(out_idx), out_w, row, lane) : 0u;
+        }
+        const u64 mine = lane < n ? load_marks(lay, out_w, s * T + tb - 1 - lane) : 0ull;
+#pragma unroll
+        for (int a = 0; a < RR_BATCH; ++a) {
+            if (a >= n) break;
+            const u64 m = ((u64)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), a) << 32) |
+                          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, a);
+            const bool ids = lay.is_ids(m);
+            uint32_t e = entry[a];
+            if (ids) e = K <= 8 ? (uint32_t)(m >> (8 * (lane & 7))) : lane < K ? *lay.id(out_w, s * T + tb - 1 - a, lane) : 0u;
+            e &= 127u;
+            const bool chosen = ids ? lane < K : (m >> lane) & 1ull;
+            const uint32_t step = (uint32_t)(tb - a);                  // of step tb - 1 - a, plus one
+            const bool first = chosen && keys[e] == 0u;
+            if (first) keys[e] = (step << 7) | e;
+            asm volatile("" ::: "memory");
+            // (of ids that stand for NaNs the same one may come up twice)
+            const uint32_t k0 = keys[lane], k1 = WIDE ? keys[lane + 64] : 0u;
+            count += __popcll(ballot((k0 >> 7) == step)) + (WIDE ? __popcll(ballot((k1 >> 7) == step)) : 0);
+            if (count < C) continue;
+            uint32_t cut = step << 7;
+            if (count > C) {
+                cut |= (uint32_t)nth((k0 >> 7) == step, WIDE & ((k1 >> 7) == step), count - C);
+            }
+            return WalkState{cut, C};
+        }
+    }
+    return WalkState{1u << 7, count};
+}
+
+// A whole trace in one workgroup, its stretches compared by their states: first state against last state of the one before, key for
+// key; those that differ are walked again from that state until all agree.
 template <bool WIDE, bool FULL>
-__global__ __launch_bounds__(64 * RR_WAVES) void reroute_walk_kernel(const float *__restrict__ probs, int64_t T, int N, int C, float factor,
-                                                                     RowLayout lay, int64_t stretch, int64_t warm, int32_t *out_idx,
+__global__ __launch_bounds__(64 * RR_GROUP) void reroute_group_kernel(const float *__restrict__ probs, int64_t T, int N, int C, float factor,
+                                                                     RowLayout lay, int64_t stretch, int64_t warm, const int32_t *out_idx,
                                                                      float *out_w, uint8_t *out_miss, u64 *__restrict__ out_total_miss)
 {
-    __shared__ uint32_t keys[RR_WAVES][192];
-    __shared__ uint32_t first[RR_WAVES][128];                 // state the stretch was walked from, 0 = not resident
-    __shared__ uint8_t lists[RR_WAVES][(RR_BATCH + 1) * 64];
-    __shared__ uint32_t cuts[RR_WAVES];
-    __shared__ int helds[RR_WAVES];
-    __shared__ uint32_t misses[RR_WAVES];
+    __shared__ uint32_t keys[RR_GROUP][192];
+    __shared__ uint32_t first[RR_GROUP][128];                 // state the stretch was walked from, 0 = not resident
+    __shared__ uint8_t lists[RR_GROUP][(RR_BATCH + 1) * 64];
+    __shared__ uint32_t cuts[RR_GROUP];
+    __shared__ int helds[RR_GROUP];
+    __shared__ uint32_t misses[RR_GROUP];
     const int64_t s = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6), waves = blockDim.x >> 6;
     const int64_t t0 = wave * stretch < T ? wave * stretch : T, t1 = t0 + stretch < T ? t0 + stretch : T;
@@ -347,9 +462,8 @@ __global__ __launch_bounds__(64 * RR_WAVES) void reroute_walk_kernel(const float
     const int64_t from = t0 > warm ? t0 - warm : 0;
     WalkState st{(uint32_t)(from + 1) << 7, 0};
     if (wave > 0 && t0 < t1) {
-        walk<WIDE, FULL, false>(probs, s, T, from, t0, N, C, factor, lay, out_idx, out_w, out_miss, keys[wave], lists[wave], st);
+        walk<WIDE, FULL, false, false>(probs, s, T, from, t0, stretch, N, C, factor, lay, out_idx, out_w, out_miss, keys[wave], lists[wave], st);
     }
-    __syncthreads();                    // the walks below may replace the list of a step that has none
     bool again = true;
     for (int pass = 0; pass <= waves; ++pass) {
         if (again) {
@@ -358,8 +472,7 @@ __global__ __launch_bounds__(64 * RR_WAVES) void reroute_walk_kernel(const float
                 keys[wave][e] = k;
                 first[wave][e] = k;
             }
-            const uint32_t m = walk<WIDE, FULL, true>(probs, s, T, t0, t1, N, C, factor, lay, out_idx, out_w, out_miss, keys[wave], lists[wave], st);
-            uint32_t sum = m;
+            uint32_t sum = walk<WIDE, FULL, true, false>(probs, s, T, t0, t1, stretch, N, C, factor, lay, out_idx, out_w, out_miss, keys[wave], lists[wave], st).misses;
             for (int d = 32; d > 0; d >>= 1) sum += (uint32_t)__shfl_xor((int)sum, d, 64);
             if (lane == 0) {
                 cuts[wave] = st.cut;
@@ -397,6 +510,77 @@ __global__ __launch_bounds__(64 * RR_WAVES) void reroute_walk_kernel(const float
     }
 }
 
+template <bool WIDE, bool FULL>
+__global__ __launch_bounds__(64 * RR_BLOCK_WAVES) void reroute_walk_kernel(const float *__restrict__ probs, int64_t T, int N, int C, float factor,
+                                                                           RowLayout lay, int64_t stretch, int64_t warm, const int32_t *out_idx,
+                                                                           float *out_w, uint8_t *out_miss, u64 *__restrict__ out_total_miss)
+{
+    __shared__ uint32_t keys[RR_BLOCK_WAVES][192];
+    __shared__ uint8_t lists[RR_BLOCK_WAVES][(RR_BATCH + 1) * 64];
+    const int lane = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6);
+    const int64_t s = blockIdx.y, t0 = ((int64_t)blockIdx.x * RR_BLOCK_WAVES + wave) * stretch, t1 = t0 + stretch < T ? t0 + stretch : T;
+    if (t0 == 0 && lane == 0) out_total_miss[s] = 0ull;               // no stretch has failed so far
+    if (t0 >= T) return;
+    keys[wave][lane] = 0u;
+    keys[wave][lane + 64] = 0u;
+    const int64_t from = t0 > warm ? t0 - warm : 0;
+    WalkState st{(uint32_t)(from + 1) << 7, 0};
+    if (t0 > 0) {
+        walk<WIDE, FULL, false, false>(probs, s, T, from, t0, stretch, N, C, factor, lay, out_idx, out_w, out_miss, keys[wave], lists[wave], st);
+        for (int e = lane; e < 128; e += 64) keys[wave][e] = keys[wave][e] >= st.cut ? keys[wave][e] : 0u;
+    }
+    walk<WIDE, FULL, true, false>(probs, s, T, t0, t1, stretch, N, C, factor, lay, out_idx, out_w, out_miss, keys[wave], lists[wave], st);
+}
+
+// Checks four stretches per workgroup; the workgroup that is the last of its trace to be done mends and sums.  (Marks and misses are
+// only read until then, and the bits of the stretches that failed arrive with the count.)
+template <bool WIDE, bool FULL>
+__global__ __launch_bounds__(64 * RR_BLOCK_WAVES) void reroute_check_kernel(const float *__restrict__ probs, int64_t T, int N, int C, float factor,
+                                                                            RowLayout lay, int64_t stretch, const int32_t *out_idx, float *out_w,
+                                                                            uint8_t *out_miss, u64 *__restrict__ out_total_miss)
+{
+    __shared__ uint32_t keys[RR_BLOCK_WAVES][192];
+    __shared__ uint8_t lists[RR_BLOCK_WAVES][(RR_BATCH + 1) * 64];
+    __shared__ u64 part[RR_BLOCK_WAVES], word;
+    const int lane = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6);
+    const int which = 1 + (int)blockIdx.x * RR_BLOCK_WAVES + wave;
+    const int64_t s = blockIdx.y, t0 = which * stretch, t1 = t0 + stretch < T ? t0 + stretch : T;
+    bool differ = false;
+    if (t0 < T) {
+        WalkState st = state_before<WIDE>(s, T, t0, C, lay, out_idx, out_w, keys[wave]);
+        differ = walk<WIDE, FULL, false, true>(probs, s, T, t0, t1, stretch, N, C, factor, lay, out_idx, out_w, out_miss, keys[wave], lists[wave], st).differ;
+    }
+    if (lane == 0) part[wave] = differ ? 1ull << which : 0ull;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        u64 mine = 1ull << 56;
+        for (int q = 0; q < RR_BLOCK_WAVES; ++q) mine |= part[q];
+        word = mine + atomicAdd(&out_total_miss[s], mine);
+    }
+    __syncthreads();
+    if ((word >> 56) != gridDim.x) return;
+    if (wave == 0) {
+        u64 failed = word & ((1ull << 56) - 1ull);
+        while (failed) {
+            const int first = uniform(__ffsll((long long)failed) - 1);
+            WalkState st = state_before<WIDE>(s, T, first * stretch, C, lay, out_idx, out_w, keys[0]);
+            const WalkEnd end = walk<WIDE, FULL, true, true>(probs, s, T, first * stretch, T, stretch, N, C, factor, lay, out_idx, out_w, out_miss, keys[0], lists[0], st);
+            failed &= ~0ull << (uniform((int)((end.t - 1) / stretch)) + 1);         // every stretch that it entered is done
+        }
+    }
+    __syncthreads();
+    u64 sum = 0;
+    for (int64_t t = threadIdx.x; t < T; t += 64 * RR_BLOCK_WAVES) sum += out_miss[s * T + t];
+    for (int d = 32; d > 0; d >>= 1) sum += (u64)__shfl_xor((unsigned long long)sum, d, 64);
+    if (lane == 0) part[wave] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        sum = 0;
+        for (int q = 0; q < RR_BLOCK_WAVES; ++q) sum += part[q];
+        out_total_miss[s] = sum;
+    }
+}
+
 // one wavefront per step; the sum of the chosen probabilities is taken in the order of their places
 __global__ __launch_bounds__(256) void reroute_weights_kernel(const float *__restrict__ probs, int64_t rows, int N, int renorm, RowLayout lay,
                                                               int32_t *out_idx, float *out_w)
@@ -404,15 +588,14 @@ __global__ __launch_bounds__(256) void reroute_weights_kernel(const float *__res
     const int lane = threadIdx.x & 63, K = lay.K;
     const int64_t stride = (int64_t)gridDim.x * 4;
     for (int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); row < rows; row += stride) {
-        const uint8_t *mk = lay.mark(out_w, row);
-        const bool mine = lane < lay.entries && ((mk[lane >> 3] >> (lane & 7)) & 1) != 0;
-        int e = 0;
+        const u64 m = load_marks(lay, out_w, row);
+        const bool ids = lay.is_ids(m);
+        int e = 0, id = (int)(m >> (8 * (lane & 7))) & 127;
         if (lane < lay.entries) e = *lay.entry(out_idx, out_w, row, lane) & 127;
-        int id = lane < K ? lay.entry(out_idx, out_w, row, 0)[lane + 2] : 0;     // a step that had no list
-        const u64 marks = ballot(mine);
-        if (marks) {
+        if (K > 8 && lane < K) id = *lay.id(out_w, row, lane) & 127;
+        if (!ids) {
 #if defined(__HIP_DEVICE_COMPILE__)
-            id = __builtin_amdgcn_ds_permute((mine ? below(marks) : 63) << 2, e);
+            id = __builtin_amdgcn_ds_permute(((m >> lane) & 1ull ? below(m) : 63) << 2, e);
 #endif
         }
         const float p = lane < K && id < N ? probs[row * N + id] : 0.f;
@@ -433,22 +616,51 @@ remoe_status launch_reroute(const float *probs, int64_t S, int64_t T, int N, int
     const RowLayout lay(N, K);
     const int64_t rows = S * T;
     const int64_t row_blocks = ceil_div(rows, 4) < 8192 ? ceil_div(rows, 4) : 8192;
-    // stretches of at least RR_MIN_STEPS, whole batches; the guessed state has forgotten the steps before the
-    // warm-up after a few times the steps that fill the cache
-    int64_t stretch = ceil_div(T, RR_WAVES);
+    // The guessed state has forgotten the steps before the warm-up after a few times the steps that fill the cache.
+    // Stretches are whole batches and not shorter than that, so that the warm-up at most doubles the work.
+    const int64_t warm = RR_BATCH * ceil_div(16 + 12 * (int64_t)(C < N ? C : N) / K, RR_BATCH);
+    // One workgroup per trace (16 stretches, one launch, states compared in LDS) against several (up to 56 stretches, a second launch
+    // that walks part of every stretch again to check it), whole calls of 128 experts in us, S traces x T steps, K, C:
+    //   16 x 256, 8, 4     35 / 43       16 x 1024, 8, 4    64 / 52      60 x 4096, 8, 4    295 / 230
+    //   16 x 512, 8, 4     44 / 46       16 x 640, 8, 4     51 / 48      16 x 4096, 4, 32   248 / 164
+    //   16 x 1024, 4, 32  110 / 127      16 x 2048, 4, 32  155 / 140     60 x 2048, 8, 64   262 / 248
+    //   16 x 4096, 2, 64  487 / 549      16 x 4096, 2, 32  271 / 234     60 x 4096, 2, 60   580 / 653
+    // A warm-up longer than a sixteenth of the trace leaves too few stretches for the second way to gain.
+    const bool group = T <= RR_GROUP_STEPS || T <= RR_GROUP * warm;
+    int64_t stretch = ceil_div(T, group ? RR_GROUP : RR_STRETCHES);
     if (stretch < RR_MIN_STEPS) stretch = RR_MIN_STEPS;
+    if (stretch < warm && !group) stretch = warm;
     stretch = ceil_div(stretch, RR_BATCH) * RR_BATCH;
-    const int waves = T > 0 ? (int)ceil_div(T, stretch) : 1;
-    int64_t warm = RR_BATCH * ceil_div(16 + 12 * (int64_t)(C < N ? C : N) / K, RR_BATCH);
-    if (warm > stretch) warm = stretch;
+    const int64_t n_stretch = ceil_div(T, stretch);
     u64 *total = reinterpret_cast<u64 *>(total_miss);
     if (rows > 0) {
         auto rank = N > 64 ? reroute_rank_kernel<true> : reroute_rank_kernel<false>;
         hipLaunchKernelGGL(rank, dim3((unsigned)row_blocks), dim3(256), 0, stream, probs, rows, N, factor, lay, idx, w);
     }
-    auto walk_kernel = N > 64 ? (K >= C ? reroute_walk_kernel<true, true> : reroute_walk_kernel<true, false>)
-                              : (K >= C ? reroute_walk_kernel<false, true> : reroute_walk_kernel<false, false>);
-    hipLaunchKernelGGL(walk_kernel, dim3((unsigned)S), dim3(64 * waves), 0, stream, probs, T, N, C, factor, lay, stretch, warm, idx, w, miss, total);
+    auto walk_all = [&](auto wide, auto full) {
+        constexpr bool W = decltype(wide)::value, F = decltype(full)::value;
+        if (group || n_stretch == 1) {
+            const int waves = T > 0 ? (int)n_stretch : 1;
+            hipLaunchKernelGGL((reroute_group_kernel<W, F>), dim3((unsigned)S), dim3(64 * waves), 0, stream, probs, T, N, C, factor, lay, stretch,
+                               warm < stretch ? warm : stretch, idx, w, miss, total);
+            return;
+        }
+        for (int64_t s0 = 0; s0 < S; s0 += 65535) {               // traces in the grid's second dimension
+            const unsigned n_s = (unsigned)(S - s0 < 65535 ? S - s0 : 65535);
+            const float *p = probs + s0 * T * N;
+            int32_t *i = idx + s0 * T * K;
+            float *v = w + s0 * T * K;
+            uint8_t *m = miss + s0 * T;
+            hipLaunchKernelGGL((reroute_walk_kernel<W, F>), dim3((unsigned)ceil_div(n_stretch, RR_BLOCK_WAVES), n_s), dim3(64 * RR_BLOCK_WAVES), 0, stream,
+                               p, T, N, C, factor, lay, stretch, warm, i, v, m, total + s0);
+            hipLaunchKernelGGL((reroute_check_kernel<W, F>), dim3((unsigned)ceil_div(n_stretch - 1, RR_BLOCK_WAVES), n_s), dim3(64 * RR_BLOCK_WAVES), 0, stream,
+                               p, T, N, C, factor, lay, stretch, i, v, m, total + s0);
+        }
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    if (N > 64) K >= C ? walk_all(yes, yes) : walk_all(yes, no);
+    else K >= C ? walk_all(no, yes) : walk_all(no, no);
     if (rows > 0) hipLaunchKernelGGL(reroute_weights_kernel, dim3((unsigned)row_blocks), dim3(256), 0, stream, probs, rows, N, renorm, lay, idx, w);
     return check_hip(hipGetLastError(), "reroute launch");
 }

@@ -103,3 +103,20 @@ def test_steps_of_nans_leave_the_others_alone(N, T):
 def test_scores_of_minus_infinity_are_chosen_once(N, K, C):
     """Bonuses take negative scores to -inf and (nearly) all experts are asked for: none is named twice."""
     test_reroute_edges_match_oracle(2, 200, N, K, C, 2.9e38, False, "signed")
+
+
+@pytest.mark.parametrize("S,T,N,K,C,factor,kind", [
+    # trace lengths around 64 stretches of 32 steps, and longer ones (stretches of 48 and 80 steps)
+    (2, 2047, 128, 8, 4, 1.5, "plain"), (2, 2049, 64, 6, 4, 1.5, "sticky"), (1, 4100, 128, 8, 8, 4.0, "sticky"),
+    # guesses that do not settle: stretches are walked again, across their ends, also one after the other
+    (2, 2100, 128, 2, 24, 4.0, "sticky"), (1, 3000, 128, 8, 120, 100.0, "sticky"), (1, 2500, 60, 4, 59, 4.0, "sticky"),
+    # steps without a list, in whose place stand up to 8 ids, 9 and 10 (the shortest row behind the marks), 11 and 64
+    (1, 400, 128, 7, 20, 1.5, "signed"), (2, 400, 128, 9, 20, 1.5, "signed"), (2, 400, 128, 10, 30, 1.5, "ties"),
+    (1, 400, 100, 11, 11, 1.5, "signed"), (1, 200, 128, 64, 100, 1.5, "signed"), (1, 200, 64, 1, 1, 1.5, "signed"),
+])
+def test_reroute_checked_stretches_match_oracle(S, T, N, K, C, factor, kind):
+    print(f"reroute checked stretches S={S} T={T} N={N} K={K} C={C} factor={factor} {kind}", flush=True)
+    p = _scores(kind, S, T, N)
+    idx, miss, tot = _reroute(p, K, C, factor)
+    ref = oracle.reroute_lru(p, K, C, factor, False)
+    assert torch.equal(idx, ref["idx"]) and torch.equal(miss, ref["miss"]) and torch.equal(tot, ref["total_miss"])
