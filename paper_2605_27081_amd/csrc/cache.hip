@@ -5,16 +5,17 @@
 // not; App. F.1 evaluates Belady under the same per-request resets).  Per step it reports the
 // unique misses |U_t \ C_t| and the token hits against the resident set BEFORE the step, and |U_t|
 // (App. E.2, "Per-step hits and misses"); per trace the totals that give #uMiss and uHR.
-// These policies carry state from step to step (unlike LRU, whose resident set is a function of
-// the last requests alone), so a trace is walked in order: one wavefront per trace, the resident set
+// The LRU cache is a function of the last requests alone and is found for every step in parallel (trace.hip).  The other policies
+// carry state from step to step, so a trace is walked in order: one wavefront per trace, the resident set
 // a 128-bit mask in wave-uniform registers, lane l holding the retention keys of experts l and
 // l + 64.  After a step every requested expert is held; while more than C are held, the one with the
 // smallest key among those the step did not request is dropped.  Keys (larger = kept longer), ending in the
 // order of the ids:
-//   LRU    step of last use, id                   FIFO  step of last fetch, id
+//   FIFO   step of last fetch, id
 //   LFU    requests so far, step of last use, id
 //   Belady steps_total - step of next request, 127 - id: the next request farthest ahead goes first
-// The next-request table of Belady comes from next_use_kernel, a backward walk over the same trace.
+// The next requests of Belady are looked up in masks of the steps that request an expert, a batch of 64 steps at a time: by
+// the walk itself for a trace of one batch, else by next_use_kernel, from the last batch to the first.
 //
 // step_summary_kernel / step_percentile_kernel: per-step sums of a miss table over the MoE layers,
 // their histogram and P50 / P95 / P99 (App. E.2, "Per-step (edge) reporting").
@@ -39,36 +40,58 @@ __device__ __forceinline__ void stage_rows(const int32_t *__restrict__ table, in
     for (int q = lane; q < n * K; q += 64) lds[q] = table[t0 * K + q];
 }
 
-// Belady: nxt[t, j] = first step after t that requests expert idx[t, j] again, or T (never).
-// A backward walk, one wavefront per trace: seen[e] (LDS) is the earliest request of expert e among
-// the steps already walked; lane j looks slot j's expert up and then enters the step itself.  One
-// wavefront's LDS accesses are served in program order, so the look-ups of a step see the table as
-// the later steps left it; a repeated id reads and writes the same values twice.
+// Belady: in a batch of n staged rows, first step after row t that requests expert ids[t, j] again -> out (may be ids itself).  when[e] is
+// the set of rows that request e; behind the batch the answer is later(e).  One wavefront.
+template <typename Later>
+__device__ __forceinline__ void next_uses(const int32_t *ids, int n, int K, int N, int64_t t0, unsigned long long *when, int32_t *out, Later later)
+{
+    const int lane = threadIdx.x & 63;
+    when[lane] = 0ull;
+    when[lane + 64] = 0ull;
+    __syncthreads();
+    if (lane < n) {
+        for (int j = 0; j < K; ++j) {
+            const int e = ids[lane * K + j];
+            if ((uint32_t)e < (uint32_t)N) atomicOr(&when[e], 1ull << lane);
+        }
+    }
+    __syncthreads();
+    if (lane < n) {
+        for (int j = 0; j < K; ++j) {
+            const int e = ids[lane * K + j];
+            int32_t next = later(-1);
+            if ((uint32_t)e < (uint32_t)N) {
+                const unsigned long long ahead = when[e] >> lane >> 1;
+                next = ahead ? (int32_t)(t0 + lane) + __ffsll((long long)ahead) : later(e);
+            }
+            out[lane * K + j] = next;
+        }
+    }
+    __syncthreads();
+}
+
+// nxt[t, j] = first step after t that requests expert idx[t, j] again, or T (never).  seen[e]: earliest request of expert e among the
+// batches already done.
 __global__ __launch_bounds__(64) void next_use_kernel(const int32_t *__restrict__ idx, int64_t T, int K, int N,
                                                       int32_t *__restrict__ nxt)
 {
-    extern __shared__ int32_t ids[];           // a batch of rows, replaced by their next requests step by step
+    extern __shared__ int32_t ids[];           // a batch of rows, replaced by their next requests
     __shared__ int32_t seen[128];
+    __shared__ unsigned long long when[128];
     const int64_t s = blockIdx.x;
     const int lane = threadIdx.x;
     const int32_t *tr = idx + s * T * K;
     int32_t *no = nxt + s * T * K;
     seen[lane] = (int32_t)T;
     seen[lane + 64] = (int32_t)T;
+    const int32_t never = (int32_t)T;
     for (int64_t hi = T; hi > 0; hi -= CP_BATCH) {
         const int64_t t0 = hi >= CP_BATCH ? hi - CP_BATCH : 0;
         const int n = (int)(hi - t0);
         stage_rows(tr, t0, n, K, ids);
-        __syncthreads();
-        for (int tt = n - 1; tt >= 0; --tt) {
-            if (lane < K) {
-                const int e = ids[tt * K + lane];
-                const bool valid = e >= 0 && e < N;
-                ids[tt * K + lane] = valid ? seen[e] : (int32_t)T;
-                if (valid) seen[e] = (int32_t)(t0 + tt);
-            }
-        }
-        __syncthreads();
+        next_uses(ids, n, K, N, t0, when, ids, [&](int e) { return e < 0 ? never : seen[e]; });
+        for (int e = lane; e < 128; e += 64)
+            if (when[e]) seen[e] = (int32_t)t0 + __ffsll((long long)when[e]) - 1;
         for (int q = lane; q < n * K; q += 64) no[t0 * K + q] = ids[q];
         __syncthreads();
     }
@@ -129,10 +152,10 @@ __device__ __forceinline__ void first_members(unsigned long long &lo, unsigned l
 // for more than 64 experts (WIDE).  A batch of 64 steps is staged in LDS (as much of it as K asks for: with room
 // for 64 ids a step, 10 wavefronts fitted a compute unit) and lane l first builds the request mask of step
 // l (one pass, all steps at once); the walk then fetches a step's mask with two or four lane reads.
-// Victims leave in groups of equal key, found by one wavefront minimum per group; only the group that is
-// not needed whole is gone through by id.
-// 3328 traces x 64 steps, 64 experts, top-6, capacity 12 (us, before / after): LRU 73 / 30, FIFO 78 / 31, LFU 90 / 32,
-// Belady 156 / 43 with its table of next requests.
+// Victims leave in groups of equal key, found by one wavefront minimum per group (a pointer over the steps, for
+// FIFO, took four times as long); only the group that is not needed whole is gone through by id.
+// 3328 traces x 64 steps, 64 experts, top-6, capacity 12 (us): FIFO 31, LFU 32, Belady 32 (43 with its next requests walked back
+// step by step in a launch of its own), LRU 9 (30 as a walk like these).
 template <int POLICY, bool WIDE>
 __global__ __launch_bounds__(64) void cache_policy_kernel(const int32_t *__restrict__ idx, int64_t T, int K, int N, int C,
                                                           unsigned long long expert_bytes,
@@ -146,6 +169,7 @@ __global__ __launch_bounds__(64) void cache_policy_kernel(const int32_t *__restr
     extern __shared__ int32_t stage[];
     int32_t *ids = stage, *nus = stage + CP_BATCH * K;
     __shared__ uint32_t kb[(POLICY == REMOE_CACHE_BELADY) ? 128 : 1];
+    __shared__ unsigned long long when[(POLICY == REMOE_CACHE_BELADY) ? 128 : 1];
     const int64_t s = blockIdx.x;
     const int lane = threadIdx.x;
     const int32_t *tr = idx + s * T * K;
@@ -157,8 +181,12 @@ __global__ __launch_bounds__(64) void cache_policy_kernel(const int32_t *__restr
     for (int64_t t0 = 0; t0 < T; t0 += CP_BATCH) {
         const int n = (int)((T - t0 < CP_BATCH) ? T - t0 : CP_BATCH);
         stage_rows(tr, t0, n, K, ids);
-        if (POLICY == REMOE_CACHE_BELADY) stage_rows(nxt + s * T * K, t0, n, K, nus);
+        if (POLICY == REMOE_CACHE_BELADY && T > CP_BATCH) stage_rows(nxt + s * T * K, t0, n, K, nus);
         __syncthreads();
+        if (POLICY == REMOE_CACHE_BELADY && T <= CP_BATCH) {
+            const int32_t never = (int32_t)T;
+            next_uses(ids, n, K, N, 0, when, nus, [&](int) { return never; });
+        }
         // request mask of step t0 + lane
         unsigned long long m_lo = 0ull, m_hi = 0ull;
         int valid = 0;
@@ -190,10 +218,6 @@ __global__ __launch_bounds__(64) void cache_policy_kernel(const int32_t *__restr
             }
             if (lane == tt) o_miss = (uint32_t)miss;
             // serve the step: every requested expert is held now; refresh its key
-            if (POLICY == REMOE_CACHE_LRU) {
-                if (mask_lane(req_lo)) key0 = stamp;
-                if (WIDE && mask_lane(req_hi)) key1 = stamp;
-            }
             if (POLICY == REMOE_CACHE_FIFO) {
                 if (mask_lane(req_lo & ~res_lo)) key0 = stamp;
                 if (WIDE && mask_lane(req_hi & ~res_hi)) key1 = stamp;
@@ -231,9 +255,9 @@ __global__ __launch_bounds__(64) void cache_policy_kernel(const int32_t *__restr
                 const int drop = held - C;
                 if (POLICY == REMOE_CACHE_LFU && n_g > drop) {
                     const uint32_t a0 = mask_lane(g_lo) ? age0 : CP_NONE, a1 = WIDE && mask_lane(g_hi) ? age1 : CP_NONE;
-                    const uint32_t oldest = wave_min_u32(WIDE && a1 < a0 ? a1 : a0);
-                    g_lo &= ballot64(age0 == oldest);
-                    if (WIDE) g_hi &= ballot64(age1 == oldest);
+                    const uint32_t least_age = wave_min_u32(WIDE && a1 < a0 ? a1 : a0);
+                    g_lo &= ballot64(age0 == least_age);
+                    if (WIDE) g_hi &= ballot64(age1 == least_age);
                     n_g = __popcll(g_lo) + (WIDE ? __popcll(g_hi) : 0);
                 }
                 if (n_g > drop) {
@@ -426,8 +450,7 @@ remoe_status launch_cache_policy(const int32_t *idx, int64_t S, int64_t T, int K
     const bool wide = N > 64;
     switch (policy) {
     case REMOE_CACHE_LRU:
-        run(wide ? cache_policy_kernel<REMOE_CACHE_LRU, true> : cache_policy_kernel<REMOE_CACHE_LRU, false>, rows);
-        break;
+        return launch_lru_detail(idx, S, T, K, N, C, expert_bytes, miss, uniq, hit_tok, total_miss, total_uniq, bytes, stream);
     case REMOE_CACHE_FIFO:
         run(wide ? cache_policy_kernel<REMOE_CACHE_FIFO, true> : cache_policy_kernel<REMOE_CACHE_FIFO, false>, rows);
         break;
@@ -435,7 +458,7 @@ remoe_status launch_cache_policy(const int32_t *idx, int64_t S, int64_t T, int K
         run(wide ? cache_policy_kernel<REMOE_CACHE_LFU, true> : cache_policy_kernel<REMOE_CACHE_LFU, false>, rows);
         break;
     case REMOE_CACHE_BELADY:
-        hipLaunchKernelGGL(next_use_kernel, grid, block, rows, stream, idx, T, K, N, nxt);
+        if (T > CP_BATCH) hipLaunchKernelGGL(next_use_kernel, grid, block, rows, stream, idx, T, K, N, nxt);
         run(wide ? cache_policy_kernel<REMOE_CACHE_BELADY, true> : cache_policy_kernel<REMOE_CACHE_BELADY, false>, 2 * rows);
         break;
     default:

@@ -152,7 +152,11 @@ remoe_status launch_lru(const int32_t *idx, int64_t S, int64_t T, int K, int N, 
                         uint64_t expert_bytes, int64_t step0, uint32_t *state, uint8_t *miss,
                         uint64_t *total, uint64_t *bytes, hipStream_t stream);
 
-// Cache policies beyond LRU, per-step sums over layers, routing balance.
+// the same with the distinct requests and token hits of every step, from an empty cache
+remoe_status launch_lru_detail(const int32_t *idx, int64_t S, int64_t T, int K, int N, int C, uint64_t expert_bytes, uint8_t *miss, uint8_t *uniq,
+                               uint8_t *hit_tok, uint64_t *total_miss, uint64_t *total_uniq, uint64_t *bytes, hipStream_t stream);
+
+// Cache policies, per-step sums over layers, routing balance.
 size_t cache_workspace_bytes(int64_t S, int64_t T, int K, int policy);
 remoe_status launch_cache_policy(const int32_t *idx, int64_t S, int64_t T, int K, int N, int C, int policy,
                                  uint64_t expert_bytes, uint8_t *miss, uint8_t *uniq, uint8_t *hit_tok,

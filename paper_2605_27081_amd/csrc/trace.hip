@@ -6,6 +6,8 @@
 //
 // lru_walk_kernel: the per-layer LRU expert cache of the paper's simulator (App. A cache model,
 // App. E.2 unique-miss accounting), one thread per step (see below).
+#include <type_traits>
+
 #include "common.h"
 #include "trace_mask.h"
 
@@ -67,70 +69,82 @@ __global__ void trace_reuse_kernel(const int32_t *__restrict__ idx, int64_t T, i
 // down, visits the experts in exactly that key order, so the first C collected are the resident
 // set; the walk also ends as soon as every expert of step t has been collected (all hits) or the
 // trace, and then the caller's prior state, is exhausted.  Each step of a trace is therefore an
-// independent piece of work: one thread per step, LRU_CHUNK consecutive steps per pass of a workgroup,
-// with the 128-bit masks of those steps and of the LRU_HALO before them staged in LDS.
+// independent piece of work: one thread per step, up to LRU_CHUNK consecutive steps per pass of a workgroup.
 //
-// A step adds at most K experts, so the first floor(C / K) steps are merged without looking.  Lanes end their
-// walks at different steps, so what happens only at the end of a walk (cutting the step in which the cache
-// fills up) waits until the whole wavefront is out of the loop.  The masks are put together in LDS, a lane
-// per id (one LDS OR instead of a dozen vector instructions), and the last LRU_HALO of a pass serve the next.
-// 768 traces x 4096 steps, top-8, C = 32: 120 us before, 62 us now.
-constexpr int LRU_CHUNK = 512;   // steps per pass (threads per workgroup)
-constexpr int LRU_HALO = 256;    // earlier steps whose masks are staged as well
+// The experts of the steps (i - 2^j, i] are kept in LDS for j = 0 .. LEVELS - 1, for the steps of the pass and a halo before
+// them, so that a walk takes 8 (4) steps at a time while they fit and then 4, 2 and 1: the lanes of a wavefront, whose walks
+// have different lengths, go through the same few look-ups.  One step at a time, they wait for the longest walk: 768 traces x
+// 4096 steps, top-8, C = 32 60 us, now 46; C = 64 166 and 54; top-2, C = 64 920 and 167.  A step adds at most K experts,
+// so the first floor(C / K) steps are merged without looking.  The masks are put together in LDS, a lane
+// per id (one LDS OR instead of a dozen vector instructions), and the last rows of a pass serve the next.
+constexpr int LRU_CHUNK = 512;   // steps per pass (threads per workgroup) of a trace that has as many
 
-__global__ __launch_bounds__(256) void lru_zero_kernel(uint64_t *__restrict__ total, uint64_t *__restrict__ bytes, int64_t S)
+__global__ __launch_bounds__(256) void lru_zero_kernel(uint64_t *__restrict__ total, uint64_t *__restrict__ uniq, uint64_t *__restrict__ bytes, int64_t S)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < S) { total[i] = 0; bytes[i] = 0; }
+    if (i < S) {
+        total[i] = 0;
+        if (uniq) uniq[i] = 0;
+        bytes[i] = 0;
+    }
 }
 
-// Workgroup (s, part): chunks [part * chunks_per_wg, ...) of trace s.  `whole`: one workgroup per trace, which
+struct LruOut {
+    uint8_t *miss, *uniq, *hit_tok;                  // uniq, hit_tok: DETAIL
+    unsigned long long *total, *total_uniq, *bytes;
+};
+
+// Workgroup (s, part): chunks [part * chunks_per_wg, ...) of trace s, blockDim.x steps each.  One part: one workgroup per trace, which
 // stores the totals; otherwise the workgroups add to totals that a kernel in front has cleared.
+// halo: steps before a chunk that are staged as well.  DETAIL: distinct requests and token hits are reported too.
+template <int W, int LEVELS, bool DETAIL>
 __global__ __launch_bounds__(LRU_CHUNK) void lru_walk_kernel(const int32_t *__restrict__ idx, int64_t T, int K,
                                                              int N, int C, unsigned long long expert_bytes,
-                                                             const uint32_t *__restrict__ state, int sure_steps, int parts, int64_t chunks_per_wg,
-                                                             uint8_t *__restrict__ miss_out,
-                                                             unsigned long long *__restrict__ total_out,
-                                                             unsigned long long *__restrict__ bytes_out)
+                                                             const uint32_t *__restrict__ prior, int sure_steps, int halo, int parts,
+                                                             int64_t chunks_per_wg, LruOut out)
 {
-    __shared__ Mask masks[LRU_CHUNK + LRU_HALO];
+    const uint32_t *const state = DETAIL ? nullptr : prior;              // an evaluation starts from an empty cache
+    extern __shared__ __align__(16) uint32_t lds_sets[];
     __shared__ uint32_t prev_key[128];
     __shared__ uint8_t prev_order[128];   // experts of the prior state, most recent first
     __shared__ int n_prev;
-    __shared__ unsigned long long wg_miss;
+    __shared__ unsigned long long wg_miss, wg_uniq;
 
     const int64_t s = blockIdx.x / parts;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, chunk = blockDim.x, rows = chunk + halo;
+    Set<W> *const sets = reinterpret_cast<Set<W> *>(lds_sets);           // [level][rows]; row halo + j is step t0 + j
     const int32_t *tr = idx + s * T * K;
     const bool wide = rows_are_wide(tr, K);
-    if (tid == 0) { n_prev = 0; wg_miss = 0; }
-    if (state && tid < 128) {
-        const uint32_t l = (tid < N) ? state[s * N + tid] : 0u;
-        prev_key[tid] = l ? ((l << 7) | (uint32_t)tid) : 0u;
-    }
-    __syncthreads();
-    if (state && tid < 128) {
-        const uint32_t k = prev_key[tid];
-        if (k) {
-            int above = 0;
-            for (int e = 0; e < 128; ++e) above += prev_key[e] > k;
-            prev_order[above] = (uint8_t)tid;   // nonzero keys are distinct: the ranks are a permutation
-            atomicAdd(&n_prev, 1);
+    if (tid == 0) { n_prev = 0; wg_miss = 0; wg_uniq = 0; }
+    if (state) {
+        for (int e = tid; e < 128; e += chunk) {
+            const uint32_t l = (e < N) ? state[s * N + e] : 0u;
+            prev_key[e] = l ? ((l << 7) | (uint32_t)e) : 0u;
+        }
+        __syncthreads();
+        for (int x = tid; x < 128; x += chunk) {
+            const uint32_t k = prev_key[x];
+            if (k) {
+                int above = 0;
+                for (int e = 0; e < 128; ++e) above += prev_key[e] > k;
+                prev_order[above] = (uint8_t)x;   // nonzero keys are distinct: the ranks are a permutation
+                atomicAdd(&n_prev, 1);
+            }
         }
     }
-    unsigned long long total = 0;
+    unsigned long long total = 0, total_uniq = 0;
     const int64_t c_lo = (int64_t)(blockIdx.x % parts) * chunks_per_wg;
-    // masks[LRU_HALO + j] is step t0 + j; `first` is the first staged one
-    auto stage = [&](int64_t t_from, int n, int at) {
-        for (int i = tid; i < n; i += LRU_CHUNK) masks[at + i] = Mask{};
+    // steps [t_from, t_from + n) -> rows [at, at + n); `first` is the first row that is staged
+    auto stage = [&](int64_t t_from, int n, int at, int first) {
+        for (int i = tid; i < n; i += chunk) sets[at + i] = Set<W>{};
         __syncthreads();
         const int32_t *src = tr + t_from * K;
         auto put = [&](int row, int e) {
-            if ((uint32_t)e < (uint32_t)N) atomicOr(&masks[at + row].w[e >> 5], 1u << (e & 31));
+            if ((uint32_t)e < (uint32_t)N) atomicOr(&sets[at + row].w[e >> 5], 1u << (e & 31));
         };
         if (wide) {
             const int per_row = K >> 2;
-            for (int q = tid; q < n * per_row; q += LRU_CHUNK) {
+            for (int q = tid; q < n * per_row; q += chunk) {
                 const int4 v = reinterpret_cast<const int4 *>(src)[q];
                 const int row = q / per_row;
                 put(row, v.x);
@@ -139,85 +153,155 @@ __global__ __launch_bounds__(LRU_CHUNK) void lru_walk_kernel(const int32_t *__re
                 put(row, v.w);
             }
         } else {
-            for (int q = tid; q < n * K; q += LRU_CHUNK) put(q / K, src[q]);
+            for (int q = tid; q < n * K; q += chunk) put(q / K, src[q]);
         }
         __syncthreads();
+#pragma unroll
+        for (int j = 1; j < LEVELS; ++j) {
+            for (int i = at + tid; i < at + n; i += chunk) {
+                if (i - (1 << j) + 1 < first) continue;
+                Set<W> v = sets[(j - 1) * rows + i];
+                v |= sets[(j - 1) * rows + i - (1 << (j - 1))];
+                sets[j * rows + i] = v;
+            }
+            __syncthreads();
+        }
     };
     for (int64_t c = c_lo; c < c_lo + chunks_per_wg; ++c) {
-        const int64_t t0 = c * LRU_CHUNK;
+        const int64_t t0 = c * chunk;
         if (t0 >= T) break;
-        const int back = t0 < LRU_HALO ? (int)t0 : LRU_HALO;
-        const int first = LRU_HALO - back;
+        const int back = t0 < halo ? (int)t0 : halo;
+        const int first = halo - back;
         if (c > c_lo) {
-            __syncthreads();               // the masks of the pass before are no longer read
-            if (tid < LRU_HALO) masks[tid] = masks[LRU_CHUNK + tid];
+            __syncthreads();               // the rows of the pass before are no longer read
+            for (int i = tid; i < halo; i += chunk)
+#pragma unroll
+                for (int j = 0; j < LEVELS; ++j) sets[j * rows + i] = sets[j * rows + chunk + i];
             __syncthreads();
-        } else {
-            stage(t0 - back, back, first);
+        } else if (back > 0) {
+            stage(t0 - back, back, first, first);
         }
-        stage(t0, (int)(T - t0 < LRU_CHUNK ? T - t0 : LRU_CHUNK), LRU_HALO);
+        stage(t0, (int)(T - t0 < chunk ? T - t0 : chunk), halo, first);
         const int64_t t = t0 + tid;
-        int miss = 0;
         if (t < T) {
-            const Mask want = masks[LRU_HALO + tid];
-            Mask seen{}, m{};
-            int i = LRU_HALO + tid - 1;    // next step to collect
+            const Set<W> want = sets[halo + tid];
+            Set<W> seen{};
+            int i = halo + tid - 1;        // next step to collect
             // the first steps fit whatever they hold
-            for (int stop = i - sure_steps < first - 1 ? first - 1 : i - sure_steps; i > stop; --i) seen |= masks[i];
-            int held = count(seen);
-            bool open = held < C && any(without(want, seen));
-            while (open && i >= first) {
-                m = masks[i];
-                --i;
-                Mask all = seen;
-                all |= m;
-                held = count(all);
-                open = held < C && any(without(want, all));
-                if (held <= C) seen = all;
+            int sure = sure_steps < i - first + 1 ? sure_steps : i - first + 1;
+#pragma unroll
+            for (int j = LEVELS - 1; j >= 0; --j) {
+                while (sure >= (1 << j)) {
+                    seen |= sets[j * rows + i];
+                    i -= 1 << j;
+                    sure -= 1 << j;
+                }
             }
-            int64_t u = t0 + (i - LRU_HALO);
-            while (open && u >= 0) {       // past the staged steps
-                m = step_mask(tr + u * K, K, N, wide);
-                --u;
-                Mask all = seen;
-                all |= m;
-                held = count(all);
-                open = held < C && any(without(want, all));
-                if (held <= C) seen = all;
+            bool open = count(seen) < C && any(without(want, seen));
+            Set<W> m{};                    // the step in which the cache fills up
+            int over = 0;                  // members that do not fit (LEVELS > 1: counted at the cut)
+            if constexpr (LEVELS == 1) {
+                int n = 0;
+                while (open && i >= first) {
+                    m = sets[i];
+                    --i;
+                    Set<W> all = seen;
+                    all |= m;
+                    n = count(all);
+                    open = n < C && any(without(want, all));
+                    if (n <= C) seen = all;
+                }
+                over = n - C;
+            } else {
+                // takes the 2^j steps up to i if the lane wants them and they fit (without a branch: the lanes differ)
+                auto take = [&](int j, int at, bool wanted) {
+                    Set<W> all = seen;
+                    all |= sets[j * rows + at];
+                    const int n = count(all);
+                    const bool fits = wanted & (n <= C);
+#pragma unroll
+                    for (int q = 0; q < W; ++q) seen.w[q] = fits ? all.w[q] : seen.w[q];
+                    i -= fits ? 1 << j : 0;
+                    open = open & !(fits & ((n == C) | !any(without(want, all))));
+                    return fits;
+                };
+                constexpr int TOP = 1 << (LEVELS - 1);
+                for (bool more = open & (i - TOP + 1 >= first); more;)
+                    more = take(LEVELS - 1, i, true) & open & (i - TOP + 1 >= first);
+#pragma unroll
+                for (int j = LEVELS - 2; j >= 0; --j) take(j, i > 0 ? i : 0, open & (i - (1 << j) + 1 >= first));
+                if (open && i >= first) m = sets[i];
             }
-            if (held > C) {                // the cut falls inside step m: its lowest ids were touched first and are out
-                Mask fresh = without(m, seen);
-                for (int over = held - C; over > 0; --over) drop_lowest(fresh);
-                seen |= fresh;
-            }
-            if (state && u < 0) {
-                int cnt = count(seen);
-                const int np = n_prev;
-                for (int j = 0; j < np && cnt < C && any(without(want, seen)); ++j) {
-                    const Mask bit = single(prev_order[j]);
-                    if (any(without(bit, seen))) {
-                        seen |= bit;
-                        ++cnt;
+            if (open && i < first) {       // past the staged steps
+                int64_t u = t0 + (i - halo);
+                while (open && u >= 0) {
+                    m = step_mask<W>(tr + u * K, K, N, wide);
+                    --u;
+                    Set<W> all = seen;
+                    all |= m;
+                    const int n = count(all);
+                    if (n > C) { over = n - C; break; }
+                    seen = all;
+                    m = Set<W>{};
+                    open = n < C && any(without(want, all));
+                }
+                if (state && open && over <= 0) {      // (the walk is through the trace)
+                    int cnt = count(seen);
+                    const int np = n_prev;
+                    for (int j = 0; j < np && cnt < C && any(without(want, seen)); ++j) {
+                        const Set<W> bit = single<W>(prev_order[j]);
+                        if (any(without(bit, seen))) {
+                            seen |= bit;
+                            ++cnt;
+                        }
                     }
                 }
             }
-            miss = count(without(want, seen));
-            miss_out[s * T + t] = (uint8_t)miss;
+            // the cut falls inside step m: its lowest ids were touched first and are out
+            if (LEVELS == 1 ? over > 0 : any(m)) {
+                Set<W> fresh = without(m, seen);
+                if (LEVELS == 1) drop_one_by_one(fresh, over);
+                else drop_lowest(fresh, count(seen) + count(fresh) - C);
+                seen |= fresh;
+            }
+            const int miss = count(without(want, seen));
+            out.miss[s * T + t] = (uint8_t)miss;
+            total += (unsigned long long)miss;
+            if (DETAIL) {
+                const int uniq = count(want);
+                int hits = 0;              // a repeated id counts every time
+                for (int j = 0; j < K; ++j) {
+                    const int e = tr[t * K + j];
+                    hits += (uint32_t)e < (uint32_t)N && holds(seen, e) ? 1 : 0;
+                }
+                out.uniq[s * T + t] = (uint8_t)uniq;
+                out.hit_tok[s * T + t] = (uint8_t)hits;
+                total_uniq += (unsigned long long)uniq;
+            }
         }
-        total += (unsigned long long)miss;
     }
     // integer sums: exact and independent of the order in which they are added
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) total += __shfl_xor(total, off, 64);
-    if ((tid & 63) == 0 && total) atomicAdd(&wg_miss, total);
+    for (int off = 32; off >= 1; off >>= 1) {
+        total += __shfl_xor(total, off, 64);
+        if (DETAIL) total_uniq += __shfl_xor(total_uniq, off, 64);
+    }
+    if ((tid & 63) == 0) {
+        if (total) atomicAdd(&wg_miss, total);
+        if (DETAIL && total_uniq) atomicAdd(&wg_uniq, total_uniq);
+    }
     __syncthreads();
     if (tid == 0) {
         if (parts == 1) {
-            total_out[s] = wg_miss;
-            bytes_out[s] = wg_miss * expert_bytes;
-        } else if (wg_miss) {
-            atomicAdd(&total_out[s], wg_miss);
-            atomicAdd(&bytes_out[s], wg_miss * expert_bytes);
+            out.total[s] = wg_miss;
+            out.bytes[s] = wg_miss * expert_bytes;
+            if (DETAIL) out.total_uniq[s] = wg_uniq;
+        } else {
+            if (wg_miss) {
+                atomicAdd(&out.total[s], wg_miss);
+                atomicAdd(&out.bytes[s], wg_miss * expert_bytes);
+            }
+            if (DETAIL && wg_uniq) atomicAdd(&out.total_uniq[s], wg_uniq);
         }
     }
 }
@@ -256,30 +340,72 @@ remoe_status launch_trace_reuse(const int32_t *idx, int64_t S, int64_t T, int K,
     return check_hip(hipGetLastError(), "trace_reuse_kernel launch");
 }
 
-remoe_status launch_lru(const int32_t *idx, int64_t S, int64_t T, int K, int N, int C,
-                        uint64_t expert_bytes, int64_t step0, uint32_t *state, uint8_t *miss,
-                        uint64_t *total, uint64_t *bytes, hipStream_t stream)
+static remoe_status launch_lru_walk(const int32_t *idx, int64_t S, int64_t T, int K, int N, int C, uint64_t expert_bytes, const uint32_t *state,
+                                    const LruOut &out, hipStream_t stream)
 {
-    if (S == 0) return REMOE_OK;
-    const int64_t n_chunks = ceil_div(T, LRU_CHUNK);
+    const int chunk = T < LRU_CHUNK ? (int)align_up((size_t)T, 64) : LRU_CHUNK;
+    const int64_t n_chunks = chunk > 0 ? ceil_div(T, chunk) : 0;
     // a workgroup takes a whole trace where the traces alone fill the chip (no clearing launch, no global atomics)
     const int64_t parts = S >= 512 || n_chunks <= 1 ? 1 : n_chunks;
     if (parts > 1 || T == 0) {
-        hipLaunchKernelGGL(lru_zero_kernel, dim3((unsigned)ceil_div(S, 256)), dim3(256), 0, stream, total, bytes, S);
+        hipLaunchKernelGGL(lru_zero_kernel, dim3((unsigned)ceil_div(S, 256)), dim3(256), 0, stream, reinterpret_cast<uint64_t *>(out.total),
+                           reinterpret_cast<uint64_t *>(out.total_uniq), reinterpret_cast<uint64_t *>(out.bytes), S);
         REMOE_HIP_TRY(hipGetLastError());
     }
     if (T == 0) return REMOE_OK;
     if (S * parts >= ((int64_t)1 << 31))
         return fail(REMOE_E_UNSUPPORTED, "lru_simulate: %lld traces x %lld steps exceed one launch", (long long)S, (long long)T);
-    hipLaunchKernelGGL(lru_walk_kernel, dim3((unsigned)(S * parts)), dim3(LRU_CHUNK), 0, stream, idx, T, K, N, C,
-                       (unsigned long long)expert_bytes, state, (int)(C / K < LRU_HALO ? C / K : LRU_HALO), (int)parts, ceil_div(n_chunks, parts), miss,
-                       reinterpret_cast<unsigned long long *>(total), reinterpret_cast<unsigned long long *>(bytes));
+    // 128 steps of halo leave room for three workgroups of 512 threads on a compute unit; a cache of many times what a step
+    // asks for needs longer walks, which read the trace itself past the halo (768 x 4096 steps, top-2, C = 64: 634 us with
+    // 256 steps, 206 with 512).
+    const int halo = n_chunks <= 1 ? 0 : C <= 12 * K ? 128 : C <= 20 * K ? 256 : 512;
+    // Tables cost a pass over the staged steps for each level.  768 x 4096 steps, 128 experts (us with 1 / 2 / 3 / 4 / 5 levels): top-8,
+    // C = 8 23 / 26 / 28 / 31 / 35, 16 38 / 41 / 41 / 44 / 49, 24 48 / 46 / 44 / 46 / 49, 32 59 / 54 / 47 / 46 / 49, 48 97 / 74 / 57 / 51 / 52,
+    // top-2, C = 64 680 / 405 / 220 / 167 / 172; 64 experts, top-6: C = 12 45 / 43 / 43 / 45 / 48, 24 69 / 55 / 50 / 47 / 49.
+    const int words = N > 64 ? 4 : 2, levels = C <= (words == 4 ? 2 : 1) * K ? 1 : C <= 3 * K ? 3 : 4;
+    const size_t lds = (size_t)levels * (chunk + halo) * words * 4;
+    const int sure = (int)(C / K < chunk + halo ? C / K : chunk + halo);
+    auto pick = [&](auto w, auto l) {
+        constexpr int W = decltype(w)::value, L = decltype(l)::value;
+        return out.uniq ? lru_walk_kernel<W, L, true> : lru_walk_kernel<W, L, false>;
+    };
+    const std::integral_constant<int, 1> one;
+    const std::integral_constant<int, 2> two;
+    const std::integral_constant<int, 3> three;
+    const std::integral_constant<int, 4> four;
+    auto kernel = words == 4 ? (levels == 1 ? pick(four, one) : levels == 3 ? pick(four, three) : pick(four, four))
+                             : (levels == 1 ? pick(two, one) : levels == 3 ? pick(two, three) : pick(two, four));
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(S * parts)), dim3((unsigned)chunk), lds, stream, idx, T, K, N, C, (unsigned long long)expert_bytes, state,
+                       sure, halo, (int)parts, ceil_div(n_chunks, parts), out);
     REMOE_HIP_TRY(hipGetLastError());
+    return REMOE_OK;
+}
+
+remoe_status launch_lru(const int32_t *idx, int64_t S, int64_t T, int K, int N, int C,
+                        uint64_t expert_bytes, int64_t step0, uint32_t *state, uint8_t *miss,
+                        uint64_t *total, uint64_t *bytes, hipStream_t stream)
+{
+    if (S == 0) return REMOE_OK;
+    LruOut out{};
+    out.miss = miss;
+    out.total = reinterpret_cast<unsigned long long *>(total);
+    out.bytes = reinterpret_cast<unsigned long long *>(bytes);
+    const remoe_status st = launch_lru_walk(idx, S, T, K, N, C, expert_bytes, state, out, stream);
+    if (st != REMOE_OK || T == 0) return st;
     if (state) {   // after every walk has read the prior state
         hipLaunchKernelGGL(lru_state_kernel, dim3((unsigned)S), dim3(256), 0, stream, idx, T, K, N, step0, state);
         REMOE_HIP_TRY(hipGetLastError());
     }
     return REMOE_OK;
+}
+
+remoe_status launch_lru_detail(const int32_t *idx, int64_t S, int64_t T, int K, int N, int C, uint64_t expert_bytes, uint8_t *miss, uint8_t *uniq,
+                               uint8_t *hit_tok, uint64_t *total_miss, uint64_t *total_uniq, uint64_t *bytes, hipStream_t stream)
+{
+    if (S == 0) return REMOE_OK;
+    const LruOut out{miss, uniq, hit_tok, reinterpret_cast<unsigned long long *>(total_miss), reinterpret_cast<unsigned long long *>(total_uniq),
+                     reinterpret_cast<unsigned long long *>(bytes)};
+    return launch_lru_walk(idx, S, T, K, N, C, expert_bytes, nullptr, out, stream);
 }
 
 }  // namespace remoe
