@@ -543,6 +543,141 @@ __global__ __launch_bounds__(RF_THREADS) void route_few_kernel(const bf16_t *__r
     }
 }
 
+// ---- 33 to 64 experts, one block of tokens per compute unit ----------------------------------------------------
+// route_kernel's four wavefronts split the weights for their own MFMAs, 1000 cycles a slice with nothing else on their SIMD.  Here
+// eight wavefronts split the weights of both expert tiles into LDS, once for the block, in steps of 64 k-values, and copy the
+// tokens; four, one per SIMD, only read operands and multiply, a tile of 32 tokens x 32 experts each.  The MFMAs
+// of a tile are route_kernel's, in its order on its operands: the logits are the same bits.
+// The copies of a splitter's step go out in front of its weight loads, and the wait in front of the barrier counts both.
+// What bounds it: about 600 cycles a step, MFMAs (384), split, LDS writes and operand reads each close to that (any one of them left
+// out gives 1-2 us, no more), and 7 us that a call of one step takes.
+// H = 2048, 64 experts, moe_route, route_kernel / this (us): 16 tokens 26.4 / 16.0, 2048 tokens 26.7 / 17.2, 16384 tokens 30.3 / 22.8,
+// caches flushed 28.0 / 20.0, 27.8 / 23.0, 40.4 / 37.4; 32768 tokens, two blocks each, 38 / 45.  128 experts: 8192 tokens 31.3 / 30.1, flushed
+// 38.0 / 39.4 (a step's pieces are 48 KB there, two steps in all fit the LDS): left to route_kernel.
+constexpr int RB_THREADS = 12 * 64, RB_SPLIT = 8;
+
+__global__ __launch_bounds__(RB_THREADS) void route_block_kernel(const bf16_t *__restrict__ x, int64_t T, int H, const float *__restrict__ wr, int N,
+                                                                 int K, int renorm, int32_t *__restrict__ out_idx, float *__restrict__ out_w,
+                                                                 float *__restrict__ out_margin, float *__restrict__ out_probs)
+{
+    constexpr int NE = 2, TT = 4 / NE, TOKENS = 32 * TT;             // expert tiles, token tiles
+    typedef LogitLayout<NE> LL;
+    constexpr int DEPTH = 6, STAGES = DEPTH + 2;                     // steps of weights and tokens on their way; stages of the tokens
+    constexpr int COPIES = TT * 4 / RB_SPLIT;                        // copy instructions (1 KB each) per wavefront and step
+    constexpr int X_U4 = TT * RF_X, P_U4 = NE * 3 * RF_PIECE;
+    __shared__ u32x4_t smem[STAGES * X_U4 + 2 * P_U4];
+    static_assert(sizeof(smem) >= sizeof(float) * TOKENS * LL::STRIDE, "the logits are parked in the stages");
+    u32x4_t *const ring = smem, *const pieces = smem + STAGES * X_U4;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int64_t t0 = (int64_t)blockIdx.x * TOKENS, left = T - t0;
+    const int n = H / RF_BK;
+    float *Ls = reinterpret_cast<float *>(smem);
+    if (wave >= 4) {
+        const int s = wave - 4;
+        uint32_t x_off[COPIES];
+#pragma unroll
+        for (int i = 0; i < COPIES; ++i) {
+            const int q = s * COPIES + i, rs = (q & 3) * 8 + (lane >> 3), rt = rs ^ ((rs >> 3) & 1), c = (lane & 7) ^ (rt & 7), r = (q >> 2) * 32 + rt;
+            x_off[i] = (uint32_t)((r < left ? r : (int)left - 1) * H * 2 + c * 16);      // tokens past the end repeat the last one
+        }
+        const char *x_base = reinterpret_cast<const char *>(x + t0 * H);
+        // this lane splits four weights of NE rows a step (rows past the end repeat the last expert, masked in the ranking)
+        const floatx4_t *src[NE];
+        int place[NE];
+#pragma unroll
+        for (int f = 0; f < NE; ++f) {
+            const int r = (s * NE + f) * 4 + (lane >> 4);
+            src[f] = reinterpret_cast<const floatx4_t *>(wr + (int64_t)(r < N ? r : N - 1) * H) + (lane & 15);
+            place[f] = ((r >> 5) * 3 * RF_PIECE + slot_f32(r & 31, (lane & 15) >> 1)) * 2 + (lane & 1);
+        }
+        floatx4_t w[DEPTH][NE];
+        int fill = 0;
+        // the tokens of step j -> the next stage, its weights -> w[u] (past the end the last step again)
+        auto request = [&](int j, int u) __attribute__((always_inline)) {
+            const int j_ = j < n ? j : n - 1;
+#pragma unroll
+            for (int i = 0; i < COPIES; ++i) copy16_to_lds(x_base + (int64_t)j_ * RF_BK * 2, x_off[i], ring + fill * X_U4 + (s * COPIES + i) * 64);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int f = 0; f < NE; ++f) w[u][f] = src[f][j_ * (RF_BK / 4)];
+            fill = fill + 1 == STAGES ? 0 : fill + 1;
+            __builtin_amdgcn_sched_barrier(0);
+        };
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u) request(u, u);
+        auto step = [&](int j, int u) __attribute__((always_inline)) {
+            uint2 *out = reinterpret_cast<uint2 *>(pieces + (j & 1) * P_U4);
+#pragma unroll
+            for (int f = 0; f < NE; ++f) {
+                uint32_t p0[3], p1[3];
+                split3_pair(w[u][f][0], w[u][f][1], p0[0], p0[1], p0[2]);
+                split3_pair(w[u][f][2], w[u][f][3], p1[0], p1[1], p1[2]);
+#pragma unroll
+                for (int pc = 0; pc < 3; ++pc) out[pc * RF_PIECE * 2 + place[f]] = make_uint2(p0[pc], p1[pc]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            request(j + DEPTH, u);                   // tokens: into the stage of step j - 2
+            wait_vmem<DEPTH * (NE + COPIES)>();      // (the step's copies are older than that)
+            lds_barrier();                           // tokens and pieces of this step are there, those of the step before last have been read
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        int j = 0;
+        for (; j + DEPTH <= n; j += DEPTH) {         // (a condition around every step and the compiler waits for all loads in flight)
+#pragma unroll
+            for (int u = 0; u < DEPTH; ++u) step(j + u, u);
+        }
+#pragma unroll
+        for (int u = 0; u < DEPTH - 1; ++u)
+            if (j + u < n) step(j + u, u);
+        wait_vmem<0>();
+        lds_barrier();                             // everything has landed and has been read
+    } else {
+        __builtin_amdgcn_s_setprio(3);
+        const int li = lane & 31, lh = lane >> 5, et = wave % NE, tt = wave / NE;
+        floatx16_t acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+        StepFrags fa, fb;
+        int cur = 0;
+        auto step = [&](int j, const StepFrags &prev, StepFrags &next) __attribute__((always_inline)) {
+            lds_barrier();
+            const u32x4_t *xs = ring + cur * X_U4 + tt * RF_X, *ps = pieces + (j & 1) * P_U4 + et * 3 * RF_PIECE;
+            cur = cur + 1 == STAGES ? 0 : cur + 1;
+#pragma unroll
+            for (int i = 0; i < 12; ++i) {
+                if (j > 0) prev.mfma(acc, i);
+                if (i < 6) {
+                    next.read(xs, ps, 2 * i, li, lh);
+                    next.read(xs, ps, 2 * i + 1, li, lh);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        step(0, fb, fa);
+        int j = 1;
+        for (; j + 1 < n; j += 2) {
+            step(j, fa, fb);
+            step(j + 1, fb, fa);
+        }
+        if (j < n) {
+            step(j, fa, fb);
+#pragma unroll
+            for (int i = 0; i < 12; ++i) fb.mfma(acc, i);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 12; ++i) fa.mfma(acc, i);
+        }
+        __builtin_amdgcn_s_setprio(0);
+        lds_barrier();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) Ls[LL::at(tt * 32 + (r >> 2) * 8 + lh * 4 + (r & 3), et * 32 + li)] = acc[r];
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int tl = threadIdx.x / RT_LANES; tl < TOKENS; tl += RB_THREADS / RT_LANES)
+        route_topk<NE>(Ls + tl * LL::STRIDE, threadIdx.x % RT_LANES, t0 + tl, tl < left, N, K, renorm, out_idx, out_w, out_margin, out_probs);
+}
+
 // 32 tokens per workgroup, a row of NE * 32 logits each (columns past N hold anything), or `parts` shares of them, added
 // in order
 template <int NE>
@@ -640,6 +775,13 @@ remoe_status launch_tiles(const XT *x, int64_t T, int H, const float *wr, int N,
     int cus = 0;
     const remoe_status st = compute_units(&cus);
     if (st != REMOE_OK) return st;
+    if constexpr (BF16 && NE == 2) {
+        if (ceil_div(T, UNIT) <= cus && H % RF_BK == 0) {
+            hipLaunchKernelGGL(route_block_kernel, dim3((unsigned)ceil_div(T, UNIT)), dim3(RB_THREADS), 0, stream, x, T, H, wr, N, K, renorm, out_idx,
+                               out_w, out_margin, out_probs);
+            return check_hip(hipGetLastError(), "route_block_kernel launch");
+        }
+    }
     const int64_t mt = ceil_div(T, (int64_t)UNIT * cus);
     if (mt > 2 && MAX_MT >= 4) RT_LAUNCH((MAX_MT >= 4 ? 4 : 1));
     else if (mt > 1 && MAX_MT >= 2) RT_LAUNCH((MAX_MT >= 2 ? 2 : 1));
