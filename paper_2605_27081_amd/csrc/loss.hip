@@ -18,7 +18,8 @@
 // normalisations, so results repeat bit for bit.
 //
 // Bound by the fp64 logarithms: (1 + halo / steps) + 1 per entry instead of the 2 + |D| of a step that computes
-// its partners' itself.  8 sequences x 2048 steps, 64 experts, |D| = 5: 130 us before, 22 us now.
+// its partners' itself.  8 sequences x 2048 steps, 64 experts, |D| = 5: 130 us at first, 22 us with the logarithms in LDS, 17 us with the
+// probabilities beside them (16 x 4096 steps, 128 experts: 114 -> 78 us).
 #include "common.h"
 #include "loss_rows.h"
 
@@ -56,6 +57,7 @@ __global__ __launch_bounds__(LR_WAVES * 64) void loss_partial_kernel(const LossA
     extern __shared__ double logs[];
     __shared__ double part[LR_WAVES][LS_TERMS];
     __shared__ double2 table[LT_BINS];
+    float *const vals = reinterpret_cast<float *>(logs + a.blk.rows * a.N);
     const int chunk = blockIdx.x;
     const int64_t s = blockIdx.y;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -75,23 +77,47 @@ __global__ __launch_bounds__(LR_WAVES * 64) void loss_partial_kernel(const LossA
         const int64_t b1 = b0 + a.blk.steps < t_hi ? b0 + a.blk.steps : t_hi;
         const int64_t r0 = b0 > a.blk.halo ? b0 - a.blk.halo : 0;
         __syncthreads();                // the block before is done with the LDS
-        stage_logs(P, r0, b1, N, table, logs);
+        stage_rows(P, r0, b1, N, table, logs, vals);
         __syncthreads();
+        // the reference row and the requests of the wavefront's next step are on their way during this one
+        float ref[HALVES];
+        int id = 0;
+        auto request = [&](int64_t t) {
+            if (t >= b1) t = b1 - 1;
+#pragma unroll
+            for (int h = 0; h < HALVES; ++h) ref[h] = Q[t * N + (lane + 64 * h < N ? lane + 64 * h : N - 1)];
+            if (t >= 1 && lane < K) id = E[(t - 1) * K + lane];
+        };
+        request(b0 + wave);
         for (int64_t t = b0 + wave; t < b1; t += LR_WAVES) {
-            if (t >= 1 && lane < K) acc[0] += (double)P[t * N + E[(t - 1) * K + lane]];
+            const int row = (int)(t - r0) * N;
+            float q[HALVES];
+#pragma unroll
+            for (int h = 0; h < HALVES; ++h) q[h] = ref[h];
+            const int before = id;
+            request(t + LR_WAVES);
+            if (t >= 1 && lane < K) acc[0] += (double)vals[row + before];
 #pragma unroll
             for (int h = 0; h < HALVES; ++h) {
                 const int e = lane + 64 * h;
                 if (e >= N) continue;
-                const double p = (double)P[t * N + e], lp = logs[(t - r0) * N + e];
-                acc[1] += kl_part(p, lp, log_f32(Q[t * N + e], table));
+                const double p = (double)vals[row + e], lp = logs[row + e];
+                acc[1] += kl_part(p, lp, log_f32(q[h], table));
                 if (t < 1) continue;
-                if (unit < 0) acc[2] += symkl_part(p, lp, (double)P[(t - 1) * N + e], logs[(t - 1 - r0) * N + e]);
+                if (unit < 0) acc[2] += symkl_part(p, lp, (double)vals[row - N + e], logs[row - N + e]);
                 for (int i = 0; i < a.n_lags; ++i) {
                     const int d = a.lags[i];
                     if (t - d < 0) continue;
-                    const double r = (double)P[(t - d) * N + e];
-                    const double v = symkl_part(p, lp, r, d <= a.blk.halo ? logs[(t - d - r0) * N + e] : log_f32((float)r, table));
+                    float r;
+                    double lr;
+                    if (d <= a.blk.halo) {
+                        r = vals[row - d * N + e];
+                        lr = logs[row - d * N + e];
+                    } else {
+                        r = P[(t - d) * N + e];
+                        lr = log_f32(r, table);
+                    }
+                    const double v = symkl_part(p, lp, (double)r, lr);
                     acc[3] += v;
                     if (i == unit) acc[2] += v;
                 }
@@ -158,9 +184,14 @@ remoe_status launch_loss_forward(const float *probs, const float *probs_ref, con
     a.T = T; a.N = N; a.K = K; a.n_lags = n_lags; a.window = window;
     for (int i = 0; i < 8; ++i) a.lags[i] = i < n_lags ? lags[i] : 0;
     a.blk = plan_rows(N, lags, n_lags, 1);
+    const int64_t per = ceil_div(T, LS_CHUNKS);
+    if (per < a.blk.steps) {             // less LDS, more workgroups on a compute unit
+        a.blk.steps = per > 0 ? (int)per : 1;
+        a.blk.rows = a.blk.steps + a.blk.halo;
+    }
     a.partial = static_cast<double *>(workspace);
     a.out = out;
-    const size_t rows_bytes = sizeof(double) * (size_t)a.blk.rows * N, win_bytes = sizeof(double) * LR_WAVES * 128;
+    const size_t rows_bytes = (size_t)LR_ENTRY * a.blk.rows * N, win_bytes = sizeof(double) * LR_WAVES * 128;
     const size_t lds = rows_bytes > win_bytes ? rows_bytes : win_bytes;
     const dim3 grid(LS_CHUNKS, (unsigned)S), block(LR_WAVES * 64);
     if (N <= 64) hipLaunchKernelGGL(loss_partial_kernel<1>, grid, block, lds, stream, a);

@@ -20,7 +20,8 @@
 // loss_grad_kernel: blocks of consecutive steps whose logarithms, and those of the partners on both
 //   sides, lie in LDS (loss_rows.h); one wavefront per step, lane l holding experts l and l + 64; fp64
 //   arithmetic from the fp32 probabilities, fp32 result.  8 sequences x 2048 steps, 64 experts, |D| = 5:
-//   81 us + 19 us for the window logarithms before, 23 us + 5 us now.
+//   81 us + 19 us for the window logarithms at first, 23 us + 5 us with the logarithms in LDS, 21 us with the probabilities
+//   beside them (16 x 4096 steps, 128 experts: 195 -> 140 us for both).
 // gate_grad_bf16_kernel (bf16 hidden states): dz^T x on the bf16 matrix cores.  x is exact in bf16; each fp32
 //   dz is split into three bf16 pieces (hi + mid + lo, 24+ significand bits in all), so that every product is
 //   exact in fp32 and the sums are fp32, as with fp32 instructions but at a fifth of their matrix time.  The
@@ -72,6 +73,7 @@ __global__ __launch_bounds__(LR_WAVES * 64) void loss_grad_kernel(const GradArgs
 {
     extern __shared__ double logs[];
     __shared__ double2 table[LT_BINS];
+    float *const vals = reinterpret_cast<float *>(logs + a.blk.rows * a.N);
     fill_log_table(table);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t s = blockIdx.y;
@@ -90,42 +92,74 @@ __global__ __launch_bounds__(LR_WAVES * 64) void loss_grad_kernel(const GradArgs
     const int64_t b0 = (int64_t)blockIdx.x * a.blk.steps, b1 = b0 + a.blk.steps < T ? b0 + a.blk.steps : T;
     const int64_t r0 = b0 > a.blk.halo ? b0 - a.blk.halo : 0, r1 = b1 + a.blk.halo < T ? b1 + a.blk.halo : T;
     __syncthreads();
-    stage_logs(P, r0, r1, N, table, logs);
+    stage_rows(P, r0, r1, N, table, logs, vals);
     __syncthreads();
+    // what the wavefront's next step reads from memory is on its way during this one
+    float ref[HALVES];
+    double bar[HALVES];
+    int ids = 0;
+    auto request = [&](int64_t t) {
+        if (t >= b1) t = b1 - 1;
+        const int64_t b = t / a.window;
+#pragma unroll
+        for (int h = 0; h < HALVES; ++h) {
+            const int e = lane + 64 * h < N ? lane + 64 * h : N - 1;
+            ref[h] = Q[t * N + e];
+            if (b < n_win) bar[h] = a.logbar[(s * n_win + b) * N + e];
+        }
+        if (t >= 1 && lane < K) ids = E[(t - 1) * K + lane];
+    };
+    request(b0 + wave);
     for (int64_t t = b0 + wave; t < b1; t += LR_WAVES) {
         double p[HALVES], g[HALVES];
         const int64_t b = t / a.window;
+        const int row = (int)(t - r0) * N, before = ids;
+        float q[HALVES];
+        double lbar[HALVES];
+#pragma unroll
+        for (int h = 0; h < HALVES; ++h) {
+            q[h] = ref[h];
+            lbar[h] = bar[h];
+        }
+        request(t + LR_WAVES);
 #pragma unroll
         for (int h = 0; h < HALVES; ++h) {
             const int e = lane + 64 * h;
             p[h] = 0.0;
             g[h] = 0.0;
             if (e >= N) continue;
-            p[h] = (double)P[t * N + e];
+            p[h] = (double)vals[row + e];
             if (!(p[h] > 0.0)) continue;
-            const double lp = logs[(t - r0) * N + e], inv = 1.0 / p[h];
-            // 2 phi(P_t, R) = ln P_t - ln R + 1 - R / P_t for the partner step u
-            auto phi2 = [&](int64_t u, bool near) {
-                const double r = (double)P[u * N + e];
-                const double lr = near ? logs[(u - r0) * N + e] : log_f32((float)r, table);
-                return lp - lr + 1.0 - r * inv;
+            const double lp = logs[row + e], inv = 1.0 / p[h];
+            // 2 phi(P_t, R) = ln P_t - ln R + 1 - R / P_t for the partner step t + by
+            auto phi2 = [&](int by, bool near) {
+                float r;
+                double lr;
+                if (near) {
+                    r = vals[row + by * N + e];
+                    lr = logs[row + by * N + e];
+                } else {
+                    r = P[(t + by) * N + e];
+                    lr = log_f32(r, table);
+                }
+                return lp - lr + 1.0 - (double)r * inv;
             };
             double sm = 0.0, lg = 0.0;
-            if (t >= 1) sm += phi2(t - 1, true);
-            if (t + 1 < T) sm += phi2(t + 1, true);
+            if (t >= 1) sm += phi2(-1, true);
+            if (t + 1 < T) sm += phi2(1, true);
             for (int i = 0; i < a.n_lags; ++i) {
                 const int d = a.lags[i];
                 if (d == 1) { lg += sm; continue; }
                 const bool near = d <= a.blk.halo;
-                if (t - d >= 0) lg += phi2(t - d, near);
-                if (t + d < T) lg += phi2(t + d, near);
+                if (t - d >= 0) lg += phi2(-d, near);
+                if (t + d < T) lg += phi2(d, near);
             }
-            g[h] = c_trust * (lp - log_f32(Q[t * N + e], table) + 1.0) + c_smooth * sm + c_lag * lg;
-            if (b < n_win) g[h] -= c_ws * (a.logbar[(s * n_win + b) * N + e] + 1.0);
+            g[h] = c_trust * (lp - log_f32(q[h], table) + 1.0) + c_smooth * sm + c_lag * lg;
+            if (b < n_win) g[h] -= c_ws * (lbar[h] + 1.0);
         }
         if (t >= 1)
             for (int j = 0; j < K; ++j) {
-                const int e = E[(t - 1) * K + j];
+                const int e = __builtin_amdgcn_readlane(before, j);
 #pragma unroll
                 for (int h = 0; h < HALVES; ++h)
                     if (e == lane + 64 * h && p[h] > 0.0) g[h] += c_reuse;
@@ -456,8 +490,9 @@ remoe_status launch_loss_backward(const float *probs, const float *probs_ref, co
     const int64_t want = ceil_div(512, S);
     int64_t steps = ceil_div(ceil_div(T, want), LR_WAVES) * LR_WAVES;
     if (steps < a.blk.steps) a.blk.steps = (int)steps;
+    a.blk.rows = a.blk.steps + 2 * a.blk.halo;
     const dim3 grid((unsigned)ceil_div(T, a.blk.steps), (unsigned)S), block(LR_WAVES * 64);
-    const size_t lds = sizeof(double) * (size_t)(a.blk.steps + 2 * a.blk.halo) * N;
+    const size_t lds = (size_t)LR_ENTRY * a.blk.rows * N;
     if (N <= 64) hipLaunchKernelGGL(loss_grad_kernel<1>, grid, block, lds, stream, a);
     else hipLaunchKernelGGL(loss_grad_kernel<2>, grid, block, lds, stream, a);
     return check_hip(hipGetLastError(), "loss gradient kernels launch");

@@ -63,9 +63,11 @@ __device__ __forceinline__ double log_f32(float p, const double2 *table)
 // Every logarithm a step needs belongs to its own row or to the row of a partner step t +- d, and every row is
 // the partner of several steps.  A workgroup therefore takes a block of consecutive steps, computes the
 // logarithms of the block's rows and of `halo` rows around it once, and keeps them in LDS as fp64
-// (-inf for a zero probability); the probabilities themselves are read again where needed (they are in the
-// caches then).  Partners farther away than the halo are computed on the spot.
-constexpr int LR_BYTES = 60 * 1024;      // LDS for the logarithms: two workgroups per compute unit
+// (-inf for a zero probability), the probabilities beside them.  (Read from memory again for every partner, these kept a wavefront
+// waiting a round trip to the caches per lag: 8 x 2048 steps, 64 experts, 5 lags, loss values 21.5 us, gradient 22.5.)
+// Partners farther away than the halo are computed on the spot.
+constexpr int LR_BYTES = 76 * 1024;      // LDS for both: two workgroups per compute unit
+constexpr int LR_ENTRY = sizeof(double) + sizeof(float);
 constexpr int LR_WAVES = 8;
 constexpr int LR_MAX_ROWS = 128;
 
@@ -79,7 +81,7 @@ struct RowBlocks {
 inline RowBlocks plan_rows(int N, const int32_t *lags, int n_lags, int sides)
 {
     RowBlocks b;
-    b.rows = LR_BYTES / (8 * N);
+    b.rows = LR_BYTES / (LR_ENTRY * N);
     if (b.rows > LR_MAX_ROWS) b.rows = LR_MAX_ROWS;
     b.halo = 1;       // adjacent steps are always partners (L_Smooth)
     for (int i = 0; i < n_lags; ++i)
@@ -88,12 +90,17 @@ inline RowBlocks plan_rows(int N, const int32_t *lags, int n_lags, int sides)
     return b;
 }
 
-// ln of the rows [r_lo, r_hi) of P ([T, N]) -> lds[(r - r_lo) * N + e]
-__device__ __forceinline__ void stage_logs(const float *__restrict__ P, int64_t r_lo, int64_t r_hi, int N, const double2 *table, double *lds)
+// ln of the rows [r_lo, r_hi) of P ([T, N]) -> logs[(r - r_lo) * N + e], and the rows -> vals
+__device__ __forceinline__ void stage_rows(const float *__restrict__ P, int64_t r_lo, int64_t r_hi, int N, const double2 *table, double *logs, float *vals)
 {
     const int n = (int)(r_hi - r_lo) * N;
     const float *src = P + r_lo * N;
-    for (int q = threadIdx.x; q < n; q += LR_WAVES * 64) lds[q] = log_f32(src[q], table);
+#pragma unroll 4
+    for (int q = threadIdx.x; q < n; q += LR_WAVES * 64) {
+        const float v = src[q];
+        vals[q] = v;
+        logs[q] = log_f32(v, table);
+    }
 }
 
 // Means of the windows of `window` steps, entry by entry: 8 wavefronts share one window's rows (lane = expert, a
