@@ -17,7 +17,7 @@ namespace {
 
 // A wavefront walks its own run of consecutive steps 64 at a time, so a step's predecessor is in the
 // neighbouring lane (lane 0: in the last lane of the pass before) and every id is read once.  Bound by
-// reading the trace: 768 traces x 4096 steps x 8 ids (101 MB) 90 us before, 23 us now.
+// the instructions that put a step's set together: 768 traces x 4096 steps x 8 ids (101 MB) 90 us at first, 21 us now.
 __global__ void trace_reuse_kernel(const int32_t *__restrict__ idx, int64_t T, int K, int N, uint8_t *__restrict__ ov,
                                    uint64_t *__restrict__ sum)
 {
@@ -332,8 +332,10 @@ remoe_status launch_trace_reuse(const int32_t *idx, int64_t S, int64_t T, int K,
                                 uint8_t *ov, uint64_t *sum, hipStream_t stream)
 {
     if (S == 0) return REMOE_OK;
-    // few traces: more wavefronts for each, as long as every wavefront has a pass of 64 steps
-    int64_t waves = S >= 1024 ? 4 : ceil_div(4096, S);
+    // few traces: more wavefronts for each, as long as every wavefront has a pass of 64 steps; six to a SIMD where the traces are long
+    // (4 / 6 / 8 to a SIMD: 768 x 4096 steps, top-8 21.9 / 20.9 / 22.5 us, top-6 25.6 / 23.0 / 27.2; 300 x 1000 steps 5.1 / 6.6 / -)
+    int64_t waves = ceil_div(T >= 2048 ? 6144 : 4096, S);
+    if (waves < 4) waves = 4;
     if (waves > ceil_div(T, 64)) waves = ceil_div(T, 64);
     waves = waves < 1 ? 1 : waves > 16 ? 16 : waves;
     hipLaunchKernelGGL(trace_reuse_kernel, dim3((unsigned)S), dim3((unsigned)(64 * waves)), 0, stream, idx, T, K, N, ov, sum);

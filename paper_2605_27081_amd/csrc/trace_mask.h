@@ -91,11 +91,12 @@ __device__ __forceinline__ bool rows_are_wide(const int32_t *table, int K)
     return (K & 3) == 0 && (reinterpret_cast<uintptr_t>(table) & 15) == 0;
 }
 
+// The word is picked by a one-hot number, a bit of which is shifted into place: two instructions a word instead of three.
 template <int W> __device__ __forceinline__ void mask_add(Set<W> &m, int e, int N)
 {
-    const uint32_t bit = (uint32_t)e < (uint32_t)N ? 1u << (e & 31) : 0u;      // ids outside [0, N) are ignored
+    const uint32_t word = (uint32_t)e < (uint32_t)N ? 1u << (e >> 5) : 0u;      // ids outside [0, N) are ignored
 #pragma unroll
-    for (int q = 0; q < W; ++q) m.w[q] |= (e >> 5) == q ? bit : 0u;
+    for (int q = 0; q < W; ++q) m.w[q] |= ((word >> q) & 1u) << (e & 31);
 }
 
 // set of the distinct ids of one step
