@@ -414,13 +414,13 @@ __global__ __launch_bounds__(WM * WN * 64) void grouped_gemm_bf16_kernel(const K
         }                                                                                           \
         static_assert(NJ == 2 || NJ == 4, "the pin below is written for two or four chunks per thread"); \
         /* Every LDS read of both bands is issued before the first store (a read would otherwise sink  \
-           into its store's branch, behind stores that can stand in a full queue).  The staging areas   \
-           are the landing zone of the next tile's second slice, whose copies a wavefront issues once   \
-           its own stores are out: by then every other wavefront's reads, a dozen instructions behind   \
-           the barrier, are long done, and the copied data is an L2 round trip further away. */         \
+           into its store's branch, behind stores that can stand in a full queue), and the staging areas \
+           are free once all wavefronts are past the barrier behind the reads: the next two bands, or the \
+           copies of the next tile's second slice, go there next. */                                     \
         if (NJ == 4) asm volatile("" : "+v"(v[0][0]), "+v"(v[0][1]), "+v"(v[0][NJ - 2]), "+v"(v[0][NJ - 1]), \
                                        "+v"(v[1][0]), "+v"(v[1][1]), "+v"(v[1][NJ - 2]), "+v"(v[1][NJ - 1])); \
         else asm volatile("" : "+v"(v[0][0]), "+v"(v[0][1]), "+v"(v[1][0]), "+v"(v[1][1]));         \
+        GM_LDS_BARRIER();                                                                           \
         _Pragma("unroll") for (int b = 0; b < 2; ++b)                                                \
             _Pragma("unroll") for (int j = 0; j < NJ; ++j) {                                         \
                 const int mi_ = b ? (mi_b) : (mi_a);                                                \
@@ -544,7 +544,6 @@ __global__ __launch_bounds__(WM * WN * 64) void grouped_gemm_bf16_kernel(const K
         GM_EPI_STAGE(1, lds_b1)
         GM_LDS_BARRIER();
         GM_EPI_STORE2(0, lds_a1, 1, lds_b1, e_base, e_rows, e_cols)
-        GM_LDS_BARRIER();      // everyone has read bands 0 and 1
         GM_EPI_STAGE(2, lds_a1)
         GM_EPI_STAGE(3, lds_b1)
         GM_LDS_BARRIER();

@@ -47,3 +47,19 @@ def test_direct_to_lds_copies_need_no_outside_wait_states():
         assert lines[i - 1] == "s_nop 0" and re.match(r"s_mov_b32 m0, s\d+$", lines[i - 2]), (
             f"copy not preceded by its own M0 write and wait state: {lines[i - 2:i + 1]}")
     assert copies >= 16, f"only {copies} direct-to-LDS copies found: has the kernel changed?"
+
+
+def test_staging_areas_are_free_before_they_are_filled_again():
+    """The epilogue of the grouped GEMM stages its bands in the LDS that the next bands, and the next tile's second slice, land in.
+    A wavefront's stores stand behind its own reads of the bands, so a barrier between the two says that every wavefront has read."""
+    with tempfile.TemporaryDirectory() as tmp:
+        out = os.path.join(tmp, "gemm.s")
+        flags = [f for f in libbuild.FLAGS if f != "-fPIC"]
+        r = subprocess.run([libbuild.HIPCC, *flags, "-S", "--cuda-device-only", SRC, "-o", out], capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
+        lines = [l.strip() for l in open(out).read().split("\n") if _real_instruction(l)]
+    stores = [i for i, l in enumerate(lines) if l.startswith("global_store_dwordx4")]
+    assert len(stores) >= 16
+    for i in stores:
+        last = next(j for j in range(i, -1, -1) if lines[j].startswith(("ds_read", "s_barrier")))
+        assert lines[last] == "s_barrier", f"store without a barrier behind '{lines[last]}'"
