@@ -21,10 +21,11 @@
 //                          leave, until the cache holds only experts used inside the stretch: if every choice up to
 //                          there is the one made from the guess, so are all that follow.  A stretch that fails sets its
 //                          bit in the trace's word.
-//                          The trace's last workgroup walks the stretches that failed again, in order and as far as
-//                          anything changes, so the result is that of the single walk whatever the guesses were, and
-//                          sums the misses.
-//   reroute_group_kernel   short traces: up to 16 stretches in one workgroup, which compares their states in LDS.
+//                          The trace's last workgroup mends what failed: up to 16 wavefronts walk again at once, each as far as
+//                          anything changes or to where the next one started, until no start differs from what arrives
+//                          there, so the result is that of the single walk whatever the guesses were.  It then sums the misses.
+//   reroute_group_kernel   short traces and those whose guesses are not likely to settle: up to 16 stretches in one workgroup,
+//                          which compares their states in LDS.
 //   reroute_weights_kernel ids and gate weights from the entries the walk marked.
 // The lists and marks of a step live where its ids and weights will be (8 K bytes), so that no
 // scratch memory is needed: entries r < 4 K in the id row, the marks (one bit per entry, K but at most 8 bytes) in front of
@@ -35,8 +36,9 @@
 //
 // 16 traces x 4096 steps, 128 experts, top-8, C = 4: 7.5 ms as one walk of K maxima per step and wavefront, 0.19 ms with
 // 16 stretches of a trace in one workgroup (walk 140 us, bound by the instructions that 16 wavefronts issue on one
-// compute unit), 0.104 ms with 52 stretches of 80 steps over the chip: lists 37, walk 42 (one wavefront per SIMD, bound by
-// the latency of a step), check 16, weights 12 us.
+// compute unit), 0.102 ms with 52 stretches of 80 steps over the chip: lists 37, walk 42 (one wavefront per SIMD, bound by
+// the latency of a step), check 14, weights 12 us.  With C = 32, a bonus of 4 and scores more alike from step to step (AR(1) of
+// 0.9) 23 of 51 stretches fail: 0.29 ms; mended by one wavefront, one stretch after the other, 1.1 ms, and 0.44 ms in one workgroup.
 #include <type_traits>
 
 #include "common.h"
@@ -223,17 +225,40 @@ __device__ __forceinline__ u64 load_marks(const RowLayout &lay, float *w, int64_
     return m;
 }
 
+// The cut behind which `drop` > 0 fewer of the experts from `cut` on are: whole steps while they fit, then the lowest ids of one.
+// `last`: no key is of a later step.
+template <bool WIDE>
+__device__ __forceinline__ uint32_t evict(uint32_t k0, uint32_t k1, uint32_t cut, int drop, uint32_t last)
+{
+    uint32_t step = cut >> 7;
+    do {
+        const bool in0 = (k0 >= cut) & ((k0 >> 7) == step), in1 = WIDE & (k1 >= cut) & ((k1 >> 7) == step);
+        const int n_g = __popcll(ballot(in0)) + (WIDE ? __popcll(ballot(in1)) : 0);
+        if (n_g <= drop) {
+            drop -= n_g;
+            cut = ++step << 7;
+        } else {
+            cut = (step << 7) | (uint32_t)nth(in0, in1, drop);
+            drop = 0;
+        }
+    } while (drop > 0 && step <= last);
+    return cut;
+}
+
 struct WalkEnd {
     int64_t t;                          // first step not walked
     uint32_t misses;                    // counted by this lane
     bool differ;                        // CHECK: some choice was not the stored one
+    bool settled;                       // CHECK: the stored choices stand from here to the end of the stretch
 };
 
 // Steps [t0, t1) of a trace, t0 and stretch multiples of RR_BATCH, from the state in (keys, st).  keys[e] = (step of last
 // use + 1) << 7 | e, 0 = never used; slots 128 + lane take the writes of lanes without an expert.
 // STORE: marks and misses are written.  CHECK: they are compared with the stored ones first, and the walk ends
-// behind a batch when all that is resident was last used since the last difference and since the start of the current
-// stretch: from there on the stored choices stand.  Without STORE it also ends at a difference.  FULL: K >= C.
+// behind a batch when the cache is full and all that is resident was last used since the last difference and since the start of
+// the current stretch: the walk that stored the choices then held the same, and from there on they stand.  (The cut says
+// less: it moves with evictions only, and a cache that has stopped missing would never be seen to be renewed.)
+// Without STORE it also ends at a difference.  FULL: K >= C.
 template <bool WIDE, bool FULL, bool STORE, bool CHECK>
 __device__ __forceinline__ WalkEnd walk(const float *__restrict__ probs, int64_t s, int64_t T, int64_t t0, int64_t t1, int64_t stretch, int N, int C,
                     float factor, const RowLayout lay, const int32_t *out_idx, float *out_w, uint8_t *out_miss, uint32_t *keys,
@@ -269,6 +294,12 @@ __device__ __forceinline__ WalkEnd walk(const float *__restrict__ probs, int64_t
         asm volatile("" ::: "memory");
         const int n = (int)(t1 - tb < RR_BATCH ? t1 - tb : RR_BATCH);
         fetch();
+        u64 stored = 0ull;                                    // CHECK: marks and misses of step tb + lane
+        uint32_t stored_miss = 0;
+        if (CHECK && lane < n) {
+            stored = load_marks(lay, out_w, s * T + tb + lane);
+            stored_miss = out_miss[s * T + tb + lane];
+        }
         // bit a: step tb + a has no list
         const uint32_t no_list = (uint32_t)ballot(lane < RR_BATCH && lists[lane * 64] == lists[lane * 64 + 1]);
         uint32_t b = lists[lane];
@@ -339,21 +370,9 @@ __device__ __forceinline__ WalkEnd walk(const float *__restrict__ probs, int64_t
                 if (n_sel > C) cut |= (uint32_t)nth(k0 >= stamp, WIDE & (k1 >= stamp), n_sel - C);
             } else {
                 held += miss;
-                int drop = held - C;
-                if (drop > 0) {
+                if (held > C) {
+                    cut = evict<WIDE>(k0, k1, cut, held - C, t1u);
                     held = C;
-                    uint32_t step = cut >> 7;
-                    do {
-                        const bool in0 = (k0 >= cut) & ((k0 >> 7) == step), in1 = WIDE & (k1 >= cut) & ((k1 >> 7) == step);
-                        const int n_g = __popcll(ballot(in0)) + (WIDE ? __popcll(ballot(in1)) : 0);
-                        if (n_g <= drop) {
-                            drop -= n_g;
-                            cut = ++step << 7;
-                        } else {
-                            cut = (step << 7) | (uint32_t)nth(in0, in1, drop);
-                            drop = 0;
-                        }
-                    } while (drop > 0 && step <= t1u);
                 }
             }
         }
@@ -361,9 +380,7 @@ __device__ __forceinline__ WalkEnd walk(const float *__restrict__ probs, int64_t
         const u64 marks = ((u64)o_hi << 32) | o_lo;
         const int64_t row = s * T + tb + lane;
         if (CHECK) {
-            bool other = false;
-            if (lane < n) other = load_marks(lay, out_w, row) != marks || out_miss[row] != (uint8_t)o_miss;
-            u64 others = ballot(other);
+            u64 others = ballot(lane < n && (stored != marks || stored_miss != o_miss));
             if (K > 8) {
                 for (int a = 0; a < n; ++a)
                     if (ballot((ids_differ >> a) & 1u)) others |= 1ull << a;
@@ -382,18 +399,26 @@ __device__ __forceinline__ WalkEnd walk(const float *__restrict__ probs, int64_t
             for (int q = 0; q < lay.marks; ++q) mk[q] = (uint8_t)(marks >> (8 * q));
             out_miss[row] = (uint8_t)o_miss;
         }
-        if (CHECK && ((differ && !STORE) || (int64_t)(cut >> 7) > same_from)) {
-            st = WalkState{cut, held};
-            return WalkEnd{tb + n, lane_misses, differ};
+        if (CHECK) {
+            bool settled = false;
+            if (held == C) {
+                const uint32_t r0 = k0 >= cut ? k0 : ~0u, r1 = WIDE && k1 >= cut ? k1 : ~0u;
+                settled = (int64_t)(wave_min_u32(r1 < r0 ? r1 : r0) >> 7) > same_from;
+            }
+            if (settled || (differ && !STORE)) {
+                st = WalkState{cut, held};
+                return WalkEnd{tb + n, lane_misses, differ, settled};
+            }
         }
     }
     st.cut = cut;
     st.held = held;
-    return WalkEnd{t1, lane_misses, differ};
+    return WalkEnd{t1, lane_misses, differ, false};
 }
 
 // The state in front of step t from the choices stored for the steps before it: walking back, the first C experts met,
-// within a step the higher ids first.
+// within a step the higher ids first.  Four steps at a time are entered without looking (the latest use of an expert is its
+// largest key) before the experts are counted; the next batch is requested once the first four did not do.
 template <bool WIDE>
 __device__ __forceinline__ WalkState state_before(int64_t s, int64_t T, int64_t t, int C, const RowLayout lay, const int32_t *out_idx, float *out_w,
                                                   uint32_t *keys)
@@ -402,39 +427,49 @@ __device__ __forceinline__ WalkState state_before(int64_t s, int64_t T, int64_t 
     const bool has = lane < lay.entries;
     keys[lane] = 0u;
     keys[lane + 64] = 0u;
+    uint32_t next[RR_BATCH];
+    u64 next_marks = 0ull;
+    auto fetch = [&](int64_t tb) {
+#pragma unroll
+        for (int a = 0; a < RR_BATCH; ++a)
+            next[a] = has && a < tb ? *lay.entry(const_cast<int32_t *>(out_idx), out_w, s * T + tb - 1 - a, lane) : 0u;
+        next_marks = lane < RR_BATCH && lane < tb ? load_marks(lay, out_w, s * T + tb - 1 - lane) : 0ull;
+    };
+    fetch(t);
     int count = 0;
     for (int64_t tb = t; tb > 0; tb -= RR_BATCH) {
-        const int n = tb < RR_BATCH ? (int)tb : RR_BATCH;
         uint32_t entry[RR_BATCH];
 #pragma unroll
-        for (int a = 0; a < RR_BATCH; ++a) {
-            const int64_t row = s * T + (a < n ? tb - 1 - a : 0);
-            entry[a] = has ? *lay.entry(const_cast<int32_t *>(out_idx), out_w, row, lane) : 0u;
-        }
-        const u64 mine = lane < n ? load_marks(lay, out_w, s * T + tb - 1 - lane) : 0ull;
+        for (int a = 0; a < RR_BATCH; ++a) entry[a] = next[a];
+        const u64 marks = next_marks;
 #pragma unroll
-        for (int a = 0; a < RR_BATCH; ++a) {
-            if (a >= n) break;
-            const u64 m = ((u64)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), a) << 32) |
-                          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, a);
-            const bool ids = lay.is_ids(m);
-            uint32_t e = entry[a];
-            if (ids) e = K <= 8 ? (uint32_t)(m >> (8 * (lane & 7))) : lane < K ? *lay.id(out_w, s * T + tb - 1 - a, lane) : 0u;
-            e &= 127u;
-            const bool chosen = ids ? lane < K : (m >> lane) & 1ull;
-            const uint32_t step = (uint32_t)(tb - a);                  // of step tb - 1 - a, plus one
-            const bool first = chosen && keys[e] == 0u;
-            if (first) keys[e] = (step << 7) | e;
-            asm volatile("" ::: "memory");
-            // (of ids that stand for NaNs the same one may come up twice)
-            const uint32_t k0 = keys[lane], k1 = WIDE ? keys[lane + 64] : 0u;
-            count += __popcll(ballot((k0 >> 7) == step)) + (WIDE ? __popcll(ballot((k1 >> 7) == step)) : 0);
-            if (count < C) continue;
-            uint32_t cut = step << 7;
-            if (count > C) {
-                cut |= (uint32_t)nth((k0 >> 7) == step, WIDE & ((k1 >> 7) == step), count - C);
+        for (int q = 0; q < RR_BATCH; q += 4) {
+#pragma unroll
+            for (int a = q; a < q + 4; ++a) {                              // (no marks in front of the trace: nothing is chosen there)
+                const u64 m = ((u64)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(marks >> 32), a) << 32) |
+                              (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)marks, a);
+                uint32_t e = entry[a];
+                bool chosen = (m >> lane) & 1ull;
+                if (lay.is_ids(m)) {
+                    e = K <= 8 ? (uint32_t)(m >> (8 * (lane & 7))) : lane < K ? *lay.id(out_w, s * T + tb - 1 - a, lane) : 0u;
+                    chosen = lane < K;
+                }
+                e &= 127u;
+                if (chosen) atomicMax(&keys[e], ((uint32_t)(tb - a) << 7) | e);       // step tb - 1 - a, plus one
             }
-            return WalkState{cut, C};
+            asm volatile("" ::: "memory");
+            const uint32_t k0 = keys[lane], k1 = WIDE ? keys[lane + 64] : 0u;
+            const int now = __popcll(ballot(k0 != 0u)) + (WIDE ? __popcll(ballot(k1 != 0u)) : 0);
+            if (now < C) {
+                count = now;
+                if (q == 0) fetch(tb - RR_BATCH);
+                continue;
+            }
+            for (uint32_t step = (uint32_t)(tb - q);; --step) {               // the last of the four in which the cache is full
+                const bool in0 = (k0 >> 7) == step, in1 = WIDE & ((k1 >> 7) == step);
+                count += __popcll(ballot(in0)) + (WIDE ? __popcll(ballot(in1)) : 0);
+                if (count >= C) return WalkState{(step << 7) | (count > C ? (uint32_t)nth(in0, in1, count - C) : 0u), C};
+            }
         }
     }
     return WalkState{1u << 7, count};
@@ -532,21 +567,29 @@ __global__ __launch_bounds__(64 * RR_BLOCK_WAVES) void reroute_walk_kernel(const
     walk<WIDE, FULL, true, false>(probs, s, T, t0, t1, stretch, N, C, factor, lay, out_idx, out_w, out_miss, keys[wave], lists[wave], st);
 }
 
-// Checks four stretches per workgroup; the workgroup that is the last of its trace to be done mends and sums.  (Marks and misses are
-// only read until then, and the bits of the stretches that failed arrive with the count.)
+// The first `checkers` wavefronts of a workgroup check a stretch each; the workgroup that is the last of its trace to be done mends and
+// sums.  (Marks and misses are only read until then, and the bits of the stretches that failed arrive with the count.)
+// Mending: up to 16 wavefronts, each from a stretch that failed to where the next one's first is, all at once from the states that the
+// stored choices leave in front of theirs; where a wavefront does not settle, the next one's state is compared with the one it
+// arrives at, and those that differ walk again, until none does.  A wavefront that settles has left the state behind it as it was.
 template <bool WIDE, bool FULL>
-__global__ __launch_bounds__(64 * RR_BLOCK_WAVES) void reroute_check_kernel(const float *__restrict__ probs, int64_t T, int N, int C, float factor,
-                                                                            RowLayout lay, int64_t stretch, const int32_t *out_idx, float *out_w,
-                                                                            uint8_t *out_miss, u64 *__restrict__ out_total_miss)
+__global__ __launch_bounds__(64 * RR_GROUP) void reroute_check_kernel(const float *__restrict__ probs, int64_t T, int N, int C, float factor,
+                                                                      RowLayout lay, int64_t stretch, int checkers, const int32_t *out_idx,
+                                                                      float *out_w, uint8_t *out_miss, u64 *__restrict__ out_total_miss)
 {
-    __shared__ uint32_t keys[RR_BLOCK_WAVES][192];
-    __shared__ uint8_t lists[RR_BLOCK_WAVES][(RR_BATCH + 1) * 64];
-    __shared__ u64 part[RR_BLOCK_WAVES], word;
+    __shared__ uint32_t keys[RR_GROUP][192];
+    __shared__ uint32_t first[RR_GROUP][128];                 // state the wavefront walked from, 0 = not resident
+    __shared__ uint8_t lists[RR_GROUP][(RR_BATCH + 1) * 64];
+    __shared__ uint32_t cuts[RR_GROUP];
+    __shared__ int helds[RR_GROUP];
+    __shared__ bool arrived[RR_GROUP];                        // at its last step, without having settled
+    __shared__ u64 part[RR_GROUP], word;
     const int lane = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6);
-    const int which = 1 + (int)blockIdx.x * RR_BLOCK_WAVES + wave;
-    const int64_t s = blockIdx.y, t0 = which * stretch, t1 = t0 + stretch < T ? t0 + stretch : T;
+    const int which = 1 + (int)blockIdx.x * checkers + wave;
+    const int64_t s = blockIdx.y;
     bool differ = false;
-    if (t0 < T) {
+    if (wave < checkers && which * stretch < T) {
+        const int64_t t0 = which * stretch, t1 = t0 + stretch < T ? t0 + stretch : T;
         WalkState st = state_before<WIDE>(s, T, t0, C, lay, out_idx, out_w, keys[wave]);
         differ = walk<WIDE, FULL, false, true>(probs, s, T, t0, t1, stretch, N, C, factor, lay, out_idx, out_w, out_miss, keys[wave], lists[wave], st).differ;
     }
@@ -554,29 +597,80 @@ __global__ __launch_bounds__(64 * RR_BLOCK_WAVES) void reroute_check_kernel(cons
     __syncthreads();
     if (threadIdx.x == 0) {
         u64 mine = 1ull << 56;
-        for (int q = 0; q < RR_BLOCK_WAVES; ++q) mine |= part[q];
+        for (int q = 0; q < RR_GROUP; ++q) mine |= part[q];
         word = mine + atomicAdd(&out_total_miss[s], mine);
     }
     __syncthreads();
     if ((word >> 56) != gridDim.x) return;
-    if (wave == 0) {
-        u64 failed = word & ((1ull << 56) - 1ull);
-        while (failed) {
-            const int first = uniform(__ffsll((long long)failed) - 1);
-            WalkState st = state_before<WIDE>(s, T, first * stretch, C, lay, out_idx, out_w, keys[0]);
-            const WalkEnd end = walk<WIDE, FULL, true, true>(probs, s, T, first * stretch, T, stretch, N, C, factor, lay, out_idx, out_w, out_miss, keys[0], lists[0], st);
-            failed &= ~0ull << (uniform((int)((end.t - 1) / stretch)) + 1);         // every stretch that it entered is done
+    const u64 failed = word & ((1ull << 56) - 1ull);
+    if (failed) {
+        const int n_failed = __popcll(failed), waves = n_failed < RR_GROUP ? n_failed : RR_GROUP;
+        // where wavefront w starts: at a failed stretch each, or, if there are more of them, evenly over the rest of the trace
+        auto start = [&](int w) {
+            if (w >= waves) return T;
+            u64 m = failed;
+            for (int q = n_failed <= RR_GROUP ? w : 0; q > 0; --q) m &= m - 1ull;
+            const int64_t t = (int64_t)(__ffsll((long long)m) - 1) * stretch;
+            return n_failed <= RR_GROUP ? t : t + (T - t) / RR_BATCH * w / RR_GROUP * RR_BATCH;
+        };
+        const bool takes_part = wave < waves;
+        const int64_t t0 = start(wave), t1 = start(wave + 1);
+        WalkState st{0u, 0};
+        if (takes_part) {
+            st = state_before<WIDE>(s, T, t0, C, lay, out_idx, out_w, keys[wave]);
+            for (int e = lane; e < 128; e += 64) first[wave][e] = keys[wave][e] >= st.cut ? keys[wave][e] : 0u;
+        }
+        bool again = takes_part;
+        for (int pass = 0; pass <= waves; ++pass) {
+            __syncthreads();                                  // nobody reads what the wavefronts write now
+            bool open = again;
+            for (int64_t t = t0; again;) {
+                const WalkEnd end = walk<WIDE, FULL, true, true>(probs, s, T, t, t1, stretch, N, C, factor, lay, out_idx, out_w, out_miss, keys[wave], lists[wave], st);
+                open = !end.settled;
+                if (open || pass > 0) break;
+                // every stretch that it entered is done; its own steps fill the cache in front of the next that failed
+                u64 left = failed & (~0ull << (uniform((int)((end.t - 1) / stretch)) + 1));
+                if (!left) break;
+                t = (int64_t)uniform(__ffsll((long long)left) - 1) * stretch;
+                if (t >= t1) break;
+                st = state_before<WIDE>(s, T, t, C, lay, out_idx, out_w, keys[wave]);
+            }
+            if (lane == 0) {
+                cuts[wave] = st.cut;
+                helds[wave] = st.held;
+                arrived[wave] = open;
+            }
+            __syncthreads();
+            again = false;
+            uint32_t k[2] = {0u, 0u};
+            if (takes_part && wave > 0 && arrived[wave - 1]) {
+                const uint32_t c = (uint32_t)uniform((int)cuts[wave - 1]);
+                bool other = false;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const uint32_t v = keys[wave - 1][lane + 64 * h];
+                    k[h] = v >= c ? v : 0u;
+                    other = other || k[h] != first[wave][lane + 64 * h];
+                }
+                again = ballot(other) != 0ull;
+                if (again) st = WalkState{c, uniform(helds[wave - 1])};
+            }
+            if (!__syncthreads_or(again ? 1 : 0)) break;
+            if (again) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) keys[wave][lane + 64 * h] = first[wave][lane + 64 * h] = k[h];
+            }
         }
     }
     __syncthreads();
     u64 sum = 0;
-    for (int64_t t = threadIdx.x; t < T; t += 64 * RR_BLOCK_WAVES) sum += out_miss[s * T + t];
+    for (int64_t t = threadIdx.x; t < T; t += 64 * RR_GROUP) sum += out_miss[s * T + t];
     for (int d = 32; d > 0; d >>= 1) sum += (u64)__shfl_xor((unsigned long long)sum, d, 64);
     if (lane == 0) part[wave] = sum;
     __syncthreads();
     if (threadIdx.x == 0) {
         sum = 0;
-        for (int q = 0; q < RR_BLOCK_WAVES; ++q) sum += part[q];
+        for (int q = 0; q < RR_GROUP; ++q) sum += part[q];
         out_total_miss[s] = sum;
     }
 }
@@ -613,25 +707,36 @@ remoe_status launch_reroute(const float *probs, int64_t S, int64_t T, int N, int
                             int32_t *idx, float *w, uint8_t *miss, uint64_t *total_miss, hipStream_t stream)
 {
     if (S == 0) return REMOE_OK;
+    if (C > N) C = N;                   // nothing is evicted either way, and a cache of N can be seen to be full
     const RowLayout lay(N, K);
     const int64_t rows = S * T;
     const int64_t row_blocks = ceil_div(rows, 4) < 8192 ? ceil_div(rows, 4) : 8192;
     // The guessed state has forgotten the steps before the warm-up after a few times the steps that fill the cache.
     // Stretches are whole batches and not shorter than that, so that the warm-up at most doubles the work.
-    const int64_t warm = RR_BATCH * ceil_div(16 + 12 * (int64_t)(C < N ? C : N) / K, RR_BATCH);
+    const int64_t warm = RR_BATCH * ceil_div(16 + 12 * (int64_t)C / K, RR_BATCH);
     // One workgroup per trace (16 stretches, one launch, states compared in LDS) against several (up to 56 stretches, a second launch
     // that walks part of every stretch again to check it), whole calls of 128 experts in us, S traces x T steps, K, C:
     //   16 x 256, 8, 4     35 / 43       16 x 1024, 8, 4    64 / 52      60 x 4096, 8, 4    295 / 230
     //   16 x 512, 8, 4     44 / 46       16 x 640, 8, 4     51 / 48      16 x 4096, 4, 32   248 / 164
     //   16 x 1024, 4, 32  110 / 127      16 x 2048, 4, 32  155 / 140     60 x 2048, 8, 64   262 / 248
     //   16 x 4096, 2, 64  487 / 549      16 x 4096, 2, 32  271 / 234     60 x 4096, 2, 60   580 / 653
-    // A warm-up longer than a sixteenth of the trace leaves too few stretches for the second way to gain.
-    const bool group = T <= RR_GROUP_STEPS || T <= RR_GROUP * warm;
+    // (bonus 1.5, rho 0.8).  A warm-up longer than a sixteenth of the trace leaves too few stretches for the second way to gain.
+    // Where guesses do not settle, as with a strong bonus and a cache of more than half of the experts, both walk most of the trace again
+    // several times, 16 wavefronts at once, and the second way has walked it once more before.  1900 calls of 16 traces of AR(1) scores
+    // (16 to 128 experts, C = 4 to 64, bonus 1 to 4, rho 0.5 to 0.9), time of the second way against the first, geometric mean and worst:
+    //   bonus 2.5 or 4, C > N / 2, up to 64 warm-ups  0.98, 1.41 (two of five calls lose)     the same, longer traces  0.54, 0.88
+    //   bonus 2.5 or 4, C <= N / 2  0.68, 1.32 (one of 25 loses)                              bonus 1 or 1.5, any C < N  0.66, 1.28 (one of 70)
+    // A cache of all experts settles when the last of them has been used: 1.0 to 1.3, and the states are what has to be compared.
+    const bool sticky = factor > 2.0f && 2 * C > N;
+    const bool group = T <= RR_GROUP_STEPS || T <= RR_GROUP * warm * (sticky ? 4 : 1) || C == N;
     int64_t stretch = ceil_div(T, group ? RR_GROUP : RR_STRETCHES);
     if (stretch < RR_MIN_STEPS) stretch = RR_MIN_STEPS;
     if (stretch < warm && !group) stretch = warm;
     stretch = ceil_div(stretch, RR_BATCH) * RR_BATCH;
     const int64_t n_stretch = ceil_div(T, stretch);
+    // few checking wavefronts in a workgroup (the others wait to mend) as long as the workgroups, one to a compute unit, run at once
+    int checkers = 4;
+    while (checkers < RR_GROUP && S * ceil_div(n_stretch - 1, checkers) > 256) checkers *= 2;
     u64 *total = reinterpret_cast<u64 *>(total_miss);
     if (rows > 0) {
         auto rank = N > 64 ? reroute_rank_kernel<true> : reroute_rank_kernel<false>;
@@ -653,8 +758,8 @@ remoe_status launch_reroute(const float *probs, int64_t S, int64_t T, int N, int
             uint8_t *m = miss + s0 * T;
             hipLaunchKernelGGL((reroute_walk_kernel<W, F>), dim3((unsigned)ceil_div(n_stretch, RR_BLOCK_WAVES), n_s), dim3(64 * RR_BLOCK_WAVES), 0, stream,
                                p, T, N, C, factor, lay, stretch, warm, i, v, m, total + s0);
-            hipLaunchKernelGGL((reroute_check_kernel<W, F>), dim3((unsigned)ceil_div(n_stretch - 1, RR_BLOCK_WAVES), n_s), dim3(64 * RR_BLOCK_WAVES), 0, stream,
-                               p, T, N, C, factor, lay, stretch, i, v, m, total + s0);
+            hipLaunchKernelGGL((reroute_check_kernel<W, F>), dim3((unsigned)ceil_div(n_stretch - 1, checkers), n_s), dim3(64 * RR_GROUP), 0, stream,
+                               p, T, N, C, factor, lay, stretch, checkers, i, v, m, total + s0);
         }
     };
     const std::true_type yes;
