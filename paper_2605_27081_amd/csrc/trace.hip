@@ -71,13 +71,22 @@ __global__ void trace_reuse_kernel(const int32_t *__restrict__ idx, int64_t T, i
 // trace, and then the caller's prior state, is exhausted.  Each step of a trace is therefore an
 // independent piece of work: one thread per step, up to LRU_CHUNK consecutive steps per pass of a workgroup.
 //
-// The experts of the steps (i - 2^j, i] are kept in LDS for j = 0 .. LEVELS - 1, for the steps of the pass and a halo before
+// The experts of the steps (i - 2^j, i] are kept in LDS for j = 0 .. LEVELS - 1, for the steps of the pass and LRU_HALO before
 // them, so that a walk takes 8 (4) steps at a time while they fit and then 4, 2 and 1: the lanes of a wavefront, whose walks
 // have different lengths, go through the same few look-ups.  One step at a time, they wait for the longest walk: 768 traces x
-// 4096 steps, top-8, C = 32 60 us, now 46; C = 64 166 and 54; top-2, C = 64 920 and 167.  A step adds at most K experts,
+// 4096 steps, 128 experts, top-8, C = 32 60 us, now 47; C = 64 166 and 59.  A step adds at most K experts,
 // so the first floor(C / K) steps are merged without looking.  The masks are put together in LDS, a lane
 // per id (one LDS OR instead of a dozen vector instructions), and the last rows of a pass serve the next.
+//
+// Walks that are not done where the staged steps begin go on without walking: there an expert is in the cache if fewer than C are more
+// recent than it, and those are the ones seen so far and the ones used after it before the staged steps.  The workgroup keeps the last use
+// of every expert before the staged steps, brought up to date for the passes that ask for it.  (A lane that read on through the
+// trace a step at a time kept its workgroup waiting wherever an expert is rare or the capacity close to the experts in use: AR(1) of 0.9,
+// some experts more popular, 64 experts, top-4, C = 48 820 us, now 114; 128 experts, top-8, C = 64, popularity more uneven 10.9 ms,
+// now 0.20, and 0.65 for a cache that is walked step by step.)
 constexpr int LRU_CHUNK = 512;   // steps per pass (threads per workgroup) of a trace that has as many
+constexpr int LRU_HALO = 128;    // leaves room for three workgroups on a compute unit; 256: 768 x 4096 steps as above 115 and 231 us
+constexpr uint32_t LRU_OWN = 1u << 31;      // keys of this call's steps (below 2^24) are larger than any of the prior state
 
 __global__ __launch_bounds__(256) void lru_zero_kernel(uint64_t *__restrict__ total, uint64_t *__restrict__ uniq, uint64_t *__restrict__ bytes, int64_t S)
 {
@@ -96,18 +105,19 @@ struct LruOut {
 
 // Workgroup (s, part): chunks [part * chunks_per_wg, ...) of trace s, blockDim.x steps each.  One part: one workgroup per trace, which
 // stores the totals; otherwise the workgroups add to totals that a kernel in front has cleared.
-// halo: steps before a chunk that are staged as well.  DETAIL: distinct requests and token hits are reported too.
-template <int W, int LEVELS, bool DETAIL>
+// halo: steps before a chunk that are staged as well.  DETAIL: distinct requests and token hits are reported too.  PRIOR: the traces
+// go on from the caller's state.
+template <int W, int LEVELS, bool DETAIL, bool PRIOR>
 __global__ __launch_bounds__(LRU_CHUNK) void lru_walk_kernel(const int32_t *__restrict__ idx, int64_t T, int K,
                                                              int N, int C, unsigned long long expert_bytes,
                                                              const uint32_t *__restrict__ prior, int sure_steps, int halo, int parts,
                                                              int64_t chunks_per_wg, LruOut out)
 {
-    const uint32_t *const state = DETAIL ? nullptr : prior;              // an evaluation starts from an empty cache
+    const uint32_t *const state = PRIOR ? prior : nullptr;
     extern __shared__ __align__(16) uint32_t lds_sets[];
-    __shared__ uint32_t prev_key[128];
-    __shared__ uint8_t prev_order[128];   // experts of the prior state, most recent first
-    __shared__ int n_prev;
+    __shared__ uint32_t far_key[128];     // last use in front of the staged steps: LRU_OWN | step << 7 | e, in the prior state (step + 1) << 7 | e
+    __shared__ Set<W> above[32 * W];      // the experts of larger far_key
+    __shared__ int far_pass;              // the latest pass in which a walk went past the staged steps
     __shared__ unsigned long long wg_miss, wg_uniq;
 
     const int64_t s = blockIdx.x / parts;
@@ -115,23 +125,8 @@ __global__ __launch_bounds__(LRU_CHUNK) void lru_walk_kernel(const int32_t *__re
     Set<W> *const sets = reinterpret_cast<Set<W> *>(lds_sets);           // [level][rows]; row halo + j is step t0 + j
     const int32_t *tr = idx + s * T * K;
     const bool wide = rows_are_wide(tr, K);
-    if (tid == 0) { n_prev = 0; wg_miss = 0; wg_uniq = 0; }
-    if (state) {
-        for (int e = tid; e < 128; e += chunk) {
-            const uint32_t l = (e < N) ? state[s * N + e] : 0u;
-            prev_key[e] = l ? ((l << 7) | (uint32_t)e) : 0u;
-        }
-        __syncthreads();
-        for (int x = tid; x < 128; x += chunk) {
-            const uint32_t k = prev_key[x];
-            if (k) {
-                int above = 0;
-                for (int e = 0; e < 128; ++e) above += prev_key[e] > k;
-                prev_order[above] = (uint8_t)x;   // nonzero keys are distinct: the ranks are a permutation
-                atomicAdd(&n_prev, 1);
-            }
-        }
-    }
+    if (tid == 0) { far_pass = 0; wg_miss = 0; wg_uniq = 0; }
+    for (int e = tid; e < 128; e += chunk) far_key[e] = 0u;
     unsigned long long total = 0, total_uniq = 0;
     const int64_t c_lo = (int64_t)(blockIdx.x % parts) * chunks_per_wg;
     // steps [t_from, t_from + n) -> rows [at, at + n); `first` is the first row that is staged
@@ -167,25 +162,77 @@ __global__ __launch_bounds__(LRU_CHUNK) void lru_walk_kernel(const int32_t *__re
             __syncthreads();
         }
     };
+    auto report = [&](int64_t t, const Set<W> &want, const Set<W> &seen) __attribute__((always_inline)) {
+        const int miss = count(without(want, seen));
+        out.miss[s * T + t] = (uint8_t)miss;
+        total += (unsigned long long)miss;
+        if (DETAIL) {
+            const int uniq = count(want);
+            int hits = 0;              // a repeated id counts every time
+            for (int j = 0; j < K; ++j) {
+                const int e = tr[t * K + j];
+                hits += (uint32_t)e < (uint32_t)N && holds(seen, e) ? 1 : 0;
+            }
+            out.uniq[s * T + t] = (uint8_t)uniq;
+            out.hit_tok[s * T + t] = (uint8_t)hits;
+            total_uniq += (unsigned long long)uniq;
+        }
+    };
+    // far_key and above for the steps in front of `hi` (growing): those since the last call, then further back until C experts are known
+    // (more can not matter), and behind the start of the trace the prior state
+    int64_t far_lo = -1, far_hi = 0;           // steps in far_key
+    auto look_back = [&](int64_t hi) __attribute__((always_inline)) {
+        const bool prior_to_come = state && far_lo != 0;
+        if (far_lo < 0) far_lo = far_hi = hi;
+        for (;;) {
+            const bool ahead = far_hi < hi;
+            const int64_t from = ahead ? far_hi : far_lo > LRU_CHUNK ? far_lo - LRU_CHUNK : 0;
+            const int64_t to = !ahead ? far_lo : far_hi + LRU_CHUNK < hi ? far_hi + LRU_CHUNK : hi;
+            const int32_t *src = tr + from * K;
+#pragma unroll 1
+            for (int q = tid; q < (int)(to - from) * K; q += chunk) {
+                const int e = src[q];
+                const uint32_t key = LRU_OWN | (uint32_t)(from + q / K) << 7 | (uint32_t)e;
+                if ((uint32_t)e < (uint32_t)N && far_key[e] < key) atomicMax(&far_key[e], key);
+            }
+            if (ahead) far_hi = to;
+            else far_lo = from;
+            __syncthreads();
+            const int known = __popcll(__ballot(far_key[tid & 63] != 0u)) + __popcll(__ballot(far_key[(tid & 63) + 64] != 0u));
+            __syncthreads();
+            if (far_hi == hi && (known >= C || known >= N || far_lo == 0)) break;
+        }
+        if (prior_to_come && far_lo == 0) {
+            for (int e = tid; e < N; e += chunk) {
+                const uint32_t l = state[s * N + e];
+                if (l && far_key[e] == 0u) far_key[e] = (l << 7 | (uint32_t)e) & ~LRU_OWN;
+            }
+            __syncthreads();
+        }
+#pragma unroll 1
+        for (int q = tid; q < 32 * W * W; q += chunk) {
+            const int e = q & (32 * W - 1), word = q / (32 * W);
+            const uint32_t k = far_key[e];
+            uint32_t bits = 0u;
+#pragma unroll 8
+            for (int x = 0; x < 32; ++x) bits |= far_key[32 * word + x] > k ? 1u << x : 0u;
+            above[e].w[word] = bits;
+        }
+        __syncthreads();
+    };
     for (int64_t c = c_lo; c < c_lo + chunks_per_wg; ++c) {
         const int64_t t0 = c * chunk;
         if (t0 >= T) break;
         const int back = t0 < halo ? (int)t0 : halo;
         const int first = halo - back;
-        if (c > c_lo) {
-            __syncthreads();               // the rows of the pass before are no longer read
-            for (int i = tid; i < halo; i += chunk)
-#pragma unroll
-                for (int j = 0; j < LEVELS; ++j) sets[j * rows + i] = sets[j * rows + chunk + i];
-            __syncthreads();
-        } else if (back > 0) {
-            stage(t0 - back, back, first, first);
-        }
+        if (c > c_lo) __syncthreads();     // the halo is there
+        else if (back > 0) stage(t0 - back, back, first, first);
         stage(t0, (int)(T - t0 < chunk ? T - t0 : chunk), halo, first);
         const int64_t t = t0 + tid;
+        Set<W> want{}, seen{};
+        bool far = false;                  // the walk is through the staged steps and not done
         if (t < T) {
-            const Set<W> want = sets[halo + tid];
-            Set<W> seen{};
+            want = sets[halo + tid];
             int i = halo + tid - 1;        // next step to collect
             // the first steps fit whatever they hold
             int sure = sure_steps < i - first + 1 ? sure_steps : i - first + 1;
@@ -232,31 +279,6 @@ __global__ __launch_bounds__(LRU_CHUNK) void lru_walk_kernel(const int32_t *__re
                 for (int j = LEVELS - 2; j >= 0; --j) take(j, i > 0 ? i : 0, open & (i - (1 << j) + 1 >= first));
                 if (open && i >= first) m = sets[i];
             }
-            if (open && i < first) {       // past the staged steps
-                int64_t u = t0 + (i - halo);
-                while (open && u >= 0) {
-                    m = step_mask<W>(tr + u * K, K, N, wide);
-                    --u;
-                    Set<W> all = seen;
-                    all |= m;
-                    const int n = count(all);
-                    if (n > C) { over = n - C; break; }
-                    seen = all;
-                    m = Set<W>{};
-                    open = n < C && any(without(want, all));
-                }
-                if (state && open && over <= 0) {      // (the walk is through the trace)
-                    int cnt = count(seen);
-                    const int np = n_prev;
-                    for (int j = 0; j < np && cnt < C && any(without(want, seen)); ++j) {
-                        const Set<W> bit = single<W>(prev_order[j]);
-                        if (any(without(bit, seen))) {
-                            seen |= bit;
-                            ++cnt;
-                        }
-                    }
-                }
-            }
             // the cut falls inside step m: its lowest ids were touched first and are out
             if (LEVELS == 1 ? over > 0 : any(m)) {
                 Set<W> fresh = without(m, seen);
@@ -264,19 +286,32 @@ __global__ __launch_bounds__(LRU_CHUNK) void lru_walk_kernel(const int32_t *__re
                 else drop_lowest(fresh, count(seen) + count(fresh) - C);
                 seen |= fresh;
             }
-            const int miss = count(without(want, seen));
-            out.miss[s * T + t] = (uint8_t)miss;
-            total += (unsigned long long)miss;
-            if (DETAIL) {
-                const int uniq = count(want);
-                int hits = 0;              // a repeated id counts every time
-                for (int j = 0; j < K; ++j) {
-                    const int e = tr[t * K + j];
-                    hits += (uint32_t)e < (uint32_t)N && holds(seen, e) ? 1 : 0;
+            far = open && i < first && (t0 > back || state);
+            if (far) far_pass = (int)(c - c_lo) + 1;
+            else report(t, want, seen);
+        }
+        __syncthreads();                   // the rows of this pass are no longer read
+        const int last_far = far_pass;
+        if (c + 1 < c_lo + chunks_per_wg) {
+            for (int i = tid; i < halo; i += chunk)
+#pragma unroll
+                for (int j = 0; j < LEVELS; ++j) sets[j * rows + i] = sets[j * rows + chunk + i];
+        }
+        if (last_far == (int)(c - c_lo) + 1) {
+            look_back(t0 - back);
+            if (far) {
+                // an expert is in the cache if fewer than C are more recent: those of the staged steps, and those above it in front of them
+                const Set<W> left = without(want, seen), staged = seen;
+#pragma unroll
+                for (int q = 0; q < W; ++q) {
+                    for (uint32_t bits = left.w[q]; bits; bits &= bits - 1u) {
+                        const int e = 32 * q + __ffs((int)bits) - 1;
+                        Set<W> newer = above[e];
+                        newer |= staged;
+                        if (far_key[e] != 0u && count(newer) < C) seen |= single<W>(e);
+                    }
                 }
-                out.uniq[s * T + t] = (uint8_t)uniq;
-                out.hit_tok[s * T + t] = (uint8_t)hits;
-                total_uniq += (unsigned long long)uniq;
+                report(t, want, seen);
             }
         }
     }
@@ -356,11 +391,8 @@ static remoe_status launch_lru_walk(const int32_t *idx, int64_t S, int64_t T, in
     }
     if (T == 0) return REMOE_OK;
     if (S * parts >= ((int64_t)1 << 31))
-        return fail(REMOE_E_UNSUPPORTED, "lru_simulate: %lld traces x %lld steps exceed one launch", (long long)S, (long long)T);
-    // 128 steps of halo leave room for three workgroups of 512 threads on a compute unit; a cache of many times what a step
-    // asks for needs longer walks, which read the trace itself past the halo (768 x 4096 steps, top-2, C = 64: 634 us with
-    // 256 steps, 206 with 512).
-    const int halo = n_chunks <= 1 ? 0 : C <= 12 * K ? 128 : C <= 20 * K ? 256 : 512;
+        return fail(REMOE_E_UNSUPPORTED, "%lld LRU traces x %lld steps exceed one launch", (long long)S, (long long)T);
+    const int halo = n_chunks <= 1 ? 0 : LRU_HALO;
     // Tables cost a pass over the staged steps for each level.  768 x 4096 steps, 128 experts (us with 1 / 2 / 3 / 4 / 5 levels): top-8,
     // C = 8 23 / 26 / 28 / 31 / 35, 16 38 / 41 / 41 / 44 / 49, 24 48 / 46 / 44 / 46 / 49, 32 59 / 54 / 47 / 46 / 49, 48 97 / 74 / 57 / 51 / 52,
     // top-2, C = 64 680 / 405 / 220 / 167 / 172; 64 experts, top-6: C = 12 45 / 43 / 43 / 45 / 48, 24 69 / 55 / 50 / 47 / 49.
@@ -369,7 +401,7 @@ static remoe_status launch_lru_walk(const int32_t *idx, int64_t S, int64_t T, in
     const int sure = (int)(C / K < chunk + halo ? C / K : chunk + halo);
     auto pick = [&](auto w, auto l) {
         constexpr int W = decltype(w)::value, L = decltype(l)::value;
-        return out.uniq ? lru_walk_kernel<W, L, true> : lru_walk_kernel<W, L, false>;
+        return out.uniq ? lru_walk_kernel<W, L, true, false> : state ? lru_walk_kernel<W, L, false, true> : lru_walk_kernel<W, L, false, false>;
     };
     const std::integral_constant<int, 1> one;
     const std::integral_constant<int, 2> two;
