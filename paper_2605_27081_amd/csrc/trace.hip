@@ -390,8 +390,6 @@ static remoe_status launch_lru_walk(const int32_t *idx, int64_t S, int64_t T, in
         REMOE_HIP_TRY(hipGetLastError());
     }
     if (T == 0) return REMOE_OK;
-    if (S * parts >= ((int64_t)1 << 31))
-        return fail(REMOE_E_UNSUPPORTED, "%lld LRU traces x %lld steps exceed one launch", (long long)S, (long long)T);
     const int halo = n_chunks <= 1 ? 0 : LRU_HALO;
     // Tables cost a pass over the staged steps for each level.  768 x 4096 steps, 128 experts (us with 1 / 2 / 3 / 4 / 5 levels): top-8,
     // C = 8 23 / 26 / 28 / 31 / 35, 16 38 / 41 / 41 / 44 / 49, 24 48 / 46 / 44 / 46 / 49, 32 59 / 54 / 47 / 46 / 49, 48 97 / 74 / 57 / 51 / 52,
@@ -409,9 +407,21 @@ static remoe_status launch_lru_walk(const int32_t *idx, int64_t S, int64_t T, in
     const std::integral_constant<int, 4> four;
     auto kernel = words == 4 ? (levels == 1 ? pick(four, one) : levels == 3 ? pick(four, three) : pick(four, four))
                              : (levels == 1 ? pick(two, one) : levels == 3 ? pick(two, three) : pick(two, four));
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(S * parts)), dim3((unsigned)chunk), lds, stream, idx, T, K, N, C, (unsigned long long)expert_bytes, state,
-                       sure, halo, (int)parts, ceil_div(n_chunks, parts), out);
-    REMOE_HIP_TRY(hipGetLastError());
+    const int64_t most = (((int64_t)1 << 31) / chunk) / parts;           // traces of a launch, whose threads are counted in 32 bits
+    for (int64_t s0 = 0; s0 < S; s0 += most) {
+        LruOut o = out;
+        o.miss += s0 * T;
+        o.total += s0;
+        o.bytes += s0;
+        if (out.uniq) {
+            o.uniq += s0 * T;
+            o.hit_tok += s0 * T;
+            o.total_uniq += s0;
+        }
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((S - s0 < most ? S - s0 : most) * parts)), dim3((unsigned)chunk), lds, stream, idx + s0 * T * K, T, K, N, C,
+                           (unsigned long long)expert_bytes, state ? state + s0 * N : nullptr, sure, halo, (int)parts, ceil_div(n_chunks, parts), o);
+        REMOE_HIP_TRY(hipGetLastError());
+    }
     return REMOE_OK;
 }
 

@@ -83,3 +83,19 @@ def test_long_walks_cost_no_more_than_a_sequential_cache(S, N, K, C, popularity)
     lru, fifo = best(remoe.REMOE_CACHE_LRU), best(remoe.REMOE_CACHE_FIFO)
     print(f"cache S={S} N={N} K={K} C={C}: LRU {lru * 1e3:.0f} us, FIFO {fifo * 1e3:.0f} us", flush=True)
     assert lru < 1.5 * fifo
+
+
+def test_more_threads_than_one_launch_counts():
+    """Traces whose threads do not fit the 32 bits that a launch counts them in: one request each but the last, which is a miss at first."""
+    S, T = (1 << 25) + 3, 65                                # 128 threads each
+    idx = torch.zeros(S, T, 1, dtype=torch.int32, device=DEV)
+    idx[-2:, 1::2] = 1                                      # the last two take turns
+    steps = [torch.full((S, T), 255, dtype=torch.uint8, device=DEV) for _ in range(3)]
+    totals = [torch.full((S,), -1, dtype=torch.int64, device=DEV) for _ in range(3)]
+    remoe.cache_simulate(idx, 2, 1, remoe.REMOE_CACHE_LRU, 3, *steps, *totals, None)
+    miss, uniq, hit_tok = steps
+    assert (miss[:-2, 0] == 1).all() and not miss[:-2, 1:].any() and (miss[-2:] == 1).all()
+    assert (uniq == 1).all() and torch.equal(hit_tok, 1 - miss)
+    want = torch.ones(S, dtype=torch.int64, device=DEV)
+    want[-2:] = T
+    assert torch.equal(totals[0], want) and (totals[1] == T).all() and torch.equal(totals[2], 3 * want)
