@@ -17,7 +17,9 @@ DEV = "cuda:0"
 @pytest.mark.parametrize("T,H,N,I,K,shared,gate", [
     (1, 256, 16, 192, 2, 64, 1), (2, 128, 128, 64, 8, 0, 0), (31, 384, 5, 320, 5, 192, 0), (33, 256, 4, 64, 1, 704, 1),
     (64, 128, 9, 128, 4, 0, 0), (65, 256, 2, 256, 2, 128, 0), (127, 512, 60, 64, 4, 64, 0), (257, 256, 3, 448, 2, 320, 1),
-    (300, 128, 7, 704, 6, 0, 0), (700, 256, 8, 192, 8, 64, 0), (1025, 128, 6, 128, 3, 192, 0), (2300, 128, 8, 192, 6, 64, 1)])
+    (300, 128, 7, 704, 6, 0, 0), (700, 256, 8, 192, 8, 64, 0), (1025, 128, 6, 128, 3, 192, 0), (2300, 128, 8, 192, 6, 64, 1),
+    # the shared expert's row tiles in groups of 9 and 8, several column tiles in both launches: row tiles of 32, 64 and 128
+    (530, 384, 100, 64, 1, 704, 0), (1060, 256, 60, 64, 1, 320, 1), (2100, 512, 100, 64, 5, 320, 0)])
 def test_layer_tile_edges(T, H, N, I, K, shared, gate):
     print(f"layer tiles T={T} H={H} N={N} I={I} K={K} shared={shared}", flush=True)
     g = lambda name, shape, dt: wl.gaussian(91, name, shape, 0.05, 0, T, dt, DEV)
