@@ -1,12 +1,12 @@
 // The rest of the paper's expert-cache simulator on routing traces, and routing-balance statistics.
 //
-// cache_policy_kernel: per-layer expert cache of capacity C under LRU, FIFO, LFU or Belady's MIN
+// launch_cache_policy: per-layer expert cache of capacity C under LRU, FIFO, LFU or Belady's MIN
 // (App. E.2 "Cache state": the update rule depends on the policy, the hit / miss definitions do
 // not; App. F.1 evaluates Belady under the same per-request resets).  Per step it reports the
 // unique misses |U_t \ C_t| and the token hits against the resident set BEFORE the step, and |U_t|
 // (App. E.2, "Per-step hits and misses"); per trace the totals that give #uMiss and uHR.
 // The LRU cache is a function of the last requests alone and is found for every step in parallel (trace.hip).  The other policies
-// carry state from step to step, so a trace is walked in order: one wavefront per trace, the resident set
+// carry state from step to step, so cache_policy_kernel walks a trace in order: one wavefront per trace, the resident set
 // a 128-bit mask in wave-uniform registers, lane l holding the retention keys of experts l and
 // l + 64.  After a step every requested expert is held; while more than C are held, the one with the
 // smallest key among those the step did not request is dropped.  Keys (larger = kept longer), ending in the
@@ -166,6 +166,7 @@ __global__ __launch_bounds__(64) void cache_policy_kernel(const int32_t *__restr
                                                           unsigned long long *__restrict__ out_total_uniq,
                                                           unsigned long long *__restrict__ out_bytes)
 {
+    static_assert(POLICY == REMOE_CACHE_FIFO || POLICY == REMOE_CACHE_LFU || POLICY == REMOE_CACHE_BELADY, "LRU keeps no keys here");
     extern __shared__ int32_t stage[];
     int32_t *ids = stage, *nus = stage + CP_BATCH * K;
     __shared__ uint32_t kb[(POLICY == REMOE_CACHE_BELADY) ? 128 : 1];

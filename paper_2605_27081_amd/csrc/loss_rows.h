@@ -65,7 +65,10 @@ __device__ __forceinline__ double log_f32(float p, const double2 *table)
 // logarithms of the block's rows and of `halo` rows around it once, and keeps them in LDS as fp64
 // (-inf for a zero probability), the probabilities beside them.  (Read from memory again for every partner, these kept a wavefront
 // waiting a round trip to the caches per lag: 8 x 2048 steps, 64 experts, 5 lags, loss values 21.5 us, gradient 22.5.)
-// Partners farther away than the halo are computed on the spot.
+// Partners farther away than the halo are read and computed on the spot: with 128 experts from a lag of 34 on (17 for the gradient, whose
+// halo is on both sides), with 64 experts 68 and 34.  (With 8 bytes an entry and the probabilities in memory the halo reached 40 and
+// 20, 80 and 40, and these lags took longer all the same: 16 x 4096 steps, 128 experts, lags 1, 2, 4, 8 and 20, gradient 208 us, now 142; 1, 2,
+// 4, 8 and 40, values 140 and 88.  90 KB, which reach as far, leave one workgroup on a compute unit: 213 and 151.)
 constexpr int LR_BYTES = 76 * 1024;      // LDS for both: two workgroups per compute unit
 constexpr int LR_ENTRY = sizeof(double) + sizeof(float);
 constexpr int LR_WAVES = 8;

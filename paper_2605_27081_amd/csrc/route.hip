@@ -562,7 +562,9 @@ __global__ __launch_bounds__(RB_THREADS) void route_block_kernel(const bf16_t *_
 {
     constexpr int NE = 2, TT = 4 / NE, TOKENS = 32 * TT;             // expert tiles, token tiles
     typedef LogitLayout<NE> LL;
-    constexpr int DEPTH = 6, STAGES = DEPTH + 2;                     // steps of weights and tokens on their way; stages of the tokens
+    // Weights and tokens are requested DEPTH steps ahead.  In front of a step's split the compiler waits until no more loads are outstanding
+    // than the weights it has asked for since, 10, and does not count the copies among them: three steps and a load stay on their way.
+    constexpr int DEPTH = 6, STAGES = DEPTH + 2;                     // ...; stages of the tokens
     constexpr int COPIES = TT * 4 / RB_SPLIT;                        // copy instructions (1 KB each) per wavefront and step
     constexpr int X_U4 = TT * RF_X, P_U4 = NE * 3 * RF_PIECE;
     __shared__ u32x4_t smem[STAGES * X_U4 + 2 * P_U4];
