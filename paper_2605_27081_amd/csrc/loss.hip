@@ -50,9 +50,11 @@ struct LossArgs {
     double *out;                        // [S, 6]
 };
 
-// HALVES: 64-expert halves of a row
-template <int HALVES>
-__global__ __launch_bounds__(LR_WAVES * 64) void loss_partial_kernel(const LossArgs a)
+// HALVES: 64-expert halves of a row.  MANY: registers for four workgroups on a compute unit (three for two halves) at the cost of a slower
+// staging of the rows, where the LDS of one leaves room for three and more.  With the registers of two everywhere, few experts or short
+// chunks had half of the wavefronts: 32 sequences x 1024 steps, 32 experts, 5 lags 39 us, now 30; 64 x 512 steps, 64 experts 69 and 49.
+template <int HALVES, bool MANY>
+__global__ __launch_bounds__(LR_WAVES * 64, !MANY ? 4 : HALVES == 1 ? 8 : 6) void loss_partial_kernel(const LossArgs a)
 {
     extern __shared__ double logs[];
     __shared__ double part[LR_WAVES][LS_TERMS];
@@ -77,7 +79,7 @@ __global__ __launch_bounds__(LR_WAVES * 64) void loss_partial_kernel(const LossA
         const int64_t b1 = b0 + a.blk.steps < t_hi ? b0 + a.blk.steps : t_hi;
         const int64_t r0 = b0 > a.blk.halo ? b0 - a.blk.halo : 0;
         __syncthreads();                // the block before is done with the LDS
-        stage_rows(P, r0, b1, N, table, logs, vals);
+        stage_rows<!MANY ? 4 : HALVES == 1 ? 1 : 2>(P, r0, b1, N, table, logs, vals);
         __syncthreads();
         // the reference row and the requests of the wavefront's next step are on their way during this one
         float ref[HALVES];
@@ -194,8 +196,10 @@ remoe_status launch_loss_forward(const float *probs, const float *probs_ref, con
     const size_t rows_bytes = (size_t)LR_ENTRY * a.blk.rows * N, win_bytes = sizeof(double) * LR_WAVES * 128;
     const size_t lds = rows_bytes > win_bytes ? rows_bytes : win_bytes;
     const dim3 grid(LS_CHUNKS, (unsigned)S), block(LR_WAVES * 64);
-    if (N <= 64) hipLaunchKernelGGL(loss_partial_kernel<1>, grid, block, lds, stream, a);
-    else hipLaunchKernelGGL(loss_partial_kernel<2>, grid, block, lds, stream, a);
+    const bool many = 3 * (lds + 2432) <= 160 * 1024;
+    auto kernel = N <= 64 ? (many ? loss_partial_kernel<1, true> : loss_partial_kernel<1, false>)
+                          : (many ? loss_partial_kernel<2, true> : loss_partial_kernel<2, false>);
+    hipLaunchKernelGGL(kernel, grid, block, lds, stream, a);
     hipLaunchKernelGGL(loss_final_kernel, dim3((unsigned)S), dim3(64), 0, stream, a);
     return check_hip(hipGetLastError(), "loss kernels launch");
 }

@@ -68,8 +68,8 @@ __global__ __launch_bounds__(LR_WAVES * 64) void loss_window_log_kernel(const Gr
     if (lane + 64 < N) o[lane + 64] = log(m1);
 }
 
-template <int HALVES>
-__global__ __launch_bounds__(LR_WAVES * 64) void loss_grad_kernel(const GradArgs a)
+template <int HALVES>        // (up to 64 experts: registers for three workgroups on a compute unit, where their LDS leaves room for them)
+__global__ __launch_bounds__(LR_WAVES * 64, HALVES == 1 ? 6 : 4) void loss_grad_kernel(const GradArgs a)
 {
     extern __shared__ double logs[];
     __shared__ double2 table[LT_BINS];
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(LR_WAVES * 64) void loss_grad_kernel(const GradArgs
     const int64_t b0 = (int64_t)blockIdx.x * a.blk.steps, b1 = b0 + a.blk.steps < T ? b0 + a.blk.steps : T;
     const int64_t r0 = b0 > a.blk.halo ? b0 - a.blk.halo : 0, r1 = b1 + a.blk.halo < T ? b1 + a.blk.halo : T;
     __syncthreads();
-    stage_rows(P, r0, r1, N, table, logs, vals);
+    stage_rows<4>(P, r0, r1, N, table, logs, vals);
     __syncthreads();
     // what the wavefront's next step reads from memory is on its way during this one
     float ref[HALVES];

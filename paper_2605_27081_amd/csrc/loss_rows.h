@@ -94,11 +94,12 @@ inline RowBlocks plan_rows(int N, const int32_t *lags, int n_lags, int sides)
 }
 
 // ln of the rows [r_lo, r_hi) of P ([T, N]) -> logs[(r - r_lo) * N + e], and the rows -> vals
+template <int UNROLL>
 __device__ __forceinline__ void stage_rows(const float *__restrict__ P, int64_t r_lo, int64_t r_hi, int N, const double2 *table, double *logs, float *vals)
 {
     const int n = (int)(r_hi - r_lo) * N;
     const float *src = P + r_lo * N;
-#pragma unroll 4
+#pragma unroll UNROLL
     for (int q = threadIdx.x; q < n; q += LR_WAVES * 64) {
         const float v = src[q];
         vals[q] = v;

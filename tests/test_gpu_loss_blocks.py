@@ -15,7 +15,8 @@ DEV = "cuda:0"
 
 @pytest.mark.parametrize("S,T,N,K,window,lags", [
     (1, 700, 128, 8, 64, [1, 16, 31, 200]), (2, 65, 64, 6, 64, [3, 40]), (1, 9, 65, 3, 2, [1, 8]), (3, 4500, 16, 2, 4500, [2, 90]),
-    (70, 33, 33, 5, 7, []), (1, 2, 128, 1, 1, [1])])
+    (70, 33, 33, 5, 7, []), (1, 2, 128, 1, 1, [1]),
+    (1, 4200, 64, 2, 64, [1, 16]), (2, 300, 64, 6, 16, [4, 20]), (2, 500, 128, 8, 1, [2])])
 def test_losses_across_blocks(S, T, N, K, window, lags):
     print(f"loss blocks S={S} T={T} N={N} window={window} lags={lags}", flush=True)
     g = torch.Generator().manual_seed(T * 31 + N)
