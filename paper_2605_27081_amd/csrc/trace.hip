@@ -126,7 +126,12 @@ __global__ __launch_bounds__(LRU_CHUNK) void lru_walk_kernel(const int32_t *__re
     const int32_t *tr = idx + s * T * K;
     const bool wide = rows_are_wide(tr, K);
     if (tid == 0) { far_pass = 0; wg_miss = 0; wg_uniq = 0; }
-    for (int e = tid; e < 128; e += chunk) far_key[e] = 0u;
+    auto prior_key = [&](int e) {
+        const uint32_t l = e < N ? state[s * N + e] : 0u;
+        return l ? (l << 7 | (uint32_t)e) & ~LRU_OWN : 0u;
+    };
+    const bool one_pass = T <= chunk;         // only the prior state is in front of it
+    for (int e = tid; e < 128; e += chunk) far_key[e] = PRIOR && one_pass ? prior_key(e) : 0u;
     unsigned long long total = 0, total_uniq = 0;
     const int64_t c_lo = (int64_t)(blockIdx.x % parts) * chunks_per_wg;
     // steps [t_from, t_from + n) -> rows [at, at + n); `first` is the first row that is staged
@@ -180,11 +185,11 @@ __global__ __launch_bounds__(LRU_CHUNK) void lru_walk_kernel(const int32_t *__re
     };
     // far_key and above for the steps in front of `hi` (growing): those since the last call, then further back until C experts are known
     // (more can not matter), and behind the start of the trace the prior state
-    int64_t far_lo = -1, far_hi = 0;           // steps in far_key
+    int64_t far_lo = PRIOR && one_pass ? 0 : -1, far_hi = 0;           // steps in far_key
     auto look_back = [&](int64_t hi) __attribute__((always_inline)) {
         const bool prior_to_come = state && far_lo != 0;
         if (far_lo < 0) far_lo = far_hi = hi;
-        for (;;) {
+        while (hi > 0) {
             const bool ahead = far_hi < hi;
             const int64_t from = ahead ? far_hi : far_lo > LRU_CHUNK ? far_lo - LRU_CHUNK : 0;
             const int64_t to = !ahead ? far_lo : far_hi + LRU_CHUNK < hi ? far_hi + LRU_CHUNK : hi;
@@ -203,10 +208,8 @@ __global__ __launch_bounds__(LRU_CHUNK) void lru_walk_kernel(const int32_t *__re
             if (far_hi == hi && (known >= C || known >= N || far_lo == 0)) break;
         }
         if (prior_to_come && far_lo == 0) {
-            for (int e = tid; e < N; e += chunk) {
-                const uint32_t l = state[s * N + e];
-                if (l && far_key[e] == 0u) far_key[e] = (l << 7 | (uint32_t)e) & ~LRU_OWN;
-            }
+            for (int e = tid; e < N; e += chunk)
+                if (far_key[e] == 0u) far_key[e] = prior_key(e);
             __syncthreads();
         }
 #pragma unroll 1
@@ -380,7 +383,10 @@ remoe_status launch_trace_reuse(const int32_t *idx, int64_t S, int64_t T, int K,
 static remoe_status launch_lru_walk(const int32_t *idx, int64_t S, int64_t T, int K, int N, int C, uint64_t expert_bytes, const uint32_t *state,
                                     const LruOut &out, hipStream_t stream)
 {
-    const int chunk = T < LRU_CHUNK ? (int)align_up((size_t)T, 64) : LRU_CHUNK;
+    // (a few steps that go on from a state, as in decoding, leave most threads without a step, but they put above together: 48 traces of
+    // one step, 128 experts, 13.0 us with 64 threads)
+    const int64_t least = state && T > 0 ? 256 : 0;
+    const int chunk = T < LRU_CHUNK ? (int)align_up((size_t)(T > least ? T : least), 64) : LRU_CHUNK;
     const int64_t n_chunks = chunk > 0 ? ceil_div(T, chunk) : 0;
     // a workgroup takes a whole trace where the traces alone fill the chip (no clearing launch, no global atomics)
     const int64_t parts = S >= 512 || n_chunks <= 1 ? 1 : n_chunks;
@@ -394,7 +400,7 @@ static remoe_status launch_lru_walk(const int32_t *idx, int64_t S, int64_t T, in
     // Tables cost a pass over the staged steps for each level.  768 x 4096 steps, 128 experts (us with 1 / 2 / 3 / 4 / 5 levels): top-8,
     // C = 8 23 / 26 / 28 / 31 / 35, 16 38 / 41 / 41 / 44 / 49, 24 48 / 46 / 44 / 46 / 49, 32 59 / 54 / 47 / 46 / 49, 48 97 / 74 / 57 / 51 / 52,
     // top-2, C = 64 680 / 405 / 220 / 167 / 172; 64 experts, top-6: C = 12 45 / 43 / 43 / 45 / 48, 24 69 / 55 / 50 / 47 / 49.
-    const int words = N > 64 ? 4 : 2, levels = C <= (words == 4 ? 2 : 1) * K ? 1 : C <= 3 * K ? 3 : 4;
+    const int words = N > 64 ? 4 : 2, levels = T < 16 || C <= (words == 4 ? 2 : 1) * K ? 1 : C <= 3 * K ? 3 : 4;
     const size_t lds = (size_t)levels * (chunk + halo) * words * 4;
     const int sure = (int)(C / K < chunk + halo ? C / K : chunk + halo);
     auto pick = [&](auto w, auto l) {
