@@ -9,6 +9,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "lds_copy.h"
 #include "trace_mask.h"
 
 namespace remoe {
@@ -290,10 +291,11 @@ __global__ __launch_bounds__(LRU_CHUNK) void lru_walk_kernel(const int32_t *__re
                 seen |= fresh;
             }
             far = open && i < first && (t0 > back || state);
-            if (far) far_pass = (int)(c - c_lo) + 1;
-            else report(t, want, seen);
+            report(t, want, seen);         // (taken back where far: one branch less for the others)
         }
-        __syncthreads();                   // the rows of this pass are no longer read
+        if (__ballot(far)) far_pass = (int)(c - c_lo) + 1;
+        if (!PRIOR && one_pass) break;     // nothing is in front of it
+        lds_barrier();                     // the rows of this pass are no longer read (its results may still be on their way)
         const int last_far = far_pass;
         if (c + 1 < c_lo + chunks_per_wg) {
             for (int i = tid; i < halo; i += chunk)
@@ -303,6 +305,8 @@ __global__ __launch_bounds__(LRU_CHUNK) void lru_walk_kernel(const int32_t *__re
         if (last_far == (int)(c - c_lo) + 1) {
             look_back(t0 - back);
             if (far) {
+                total -= (unsigned long long)count(without(want, seen));
+                if (DETAIL) total_uniq -= (unsigned long long)count(want);
                 // an expert is in the cache if fewer than C are more recent: those of the staged steps, and those above it in front of them
                 const Set<W> left = without(want, seen), staged = seen;
 #pragma unroll
