@@ -160,7 +160,7 @@ def test_reroute_checked_stretches_match_oracle(S, T, N, K, C, factor, kind, men
     assert torch.equal(idx, ref["idx"]) and torch.equal(miss, ref["miss"]) and torch.equal(tot, ref["total_miss"])
 
 
-@pytest.mark.parametrize("N,K,C,times", [(16, 8, 64, 6), (32, 8, 32, 6), (128, 8, 32, 8)])
+@pytest.mark.parametrize("N,K,C,times", [(16, 8, 64, 9), (32, 8, 32, 9), (128, 8, 32, 9)])
 def test_wrong_guesses_are_mended_at_once(N, K, C, times):
     """Guesses that do not settle cost some walks in parallel, not one of the whole trace: 16 traces of 4096 steps with a bonus of
     4, against the same probabilities with a cache of top-k and no bonus (one wavefront mending a trace took 10 to 20 times as long)."""
