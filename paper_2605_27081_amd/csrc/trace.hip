@@ -135,10 +135,12 @@ __global__ __launch_bounds__(LRU_CHUNK) void lru_walk_kernel(const int32_t *__re
     for (int e = tid; e < 128; e += chunk) far_key[e] = PRIOR && one_pass ? prior_key(e) : 0u;
     unsigned long long total = 0, total_uniq = 0;
     const int64_t c_lo = (int64_t)(blockIdx.x % parts) * chunks_per_wg;
-    // steps [t_from, t_from + n) -> rows [at, at + n); `first` is the first row that is staged
-    auto stage = [&](int64_t t_from, int n, int at, int first) {
-        for (int i = tid; i < n; i += chunk) sets[at + i] = Set<W>{};
-        __syncthreads();
+    // steps [t_from, t_from + n) -> rows [at, at + n), which are empty unless `clear`; `first` is the first row that is staged
+    auto stage = [&](int64_t t_from, int n, int at, int first, bool clear) {
+        if (clear) {
+            for (int i = tid; i < n; i += chunk) sets[at + i] = Set<W>{};
+            __syncthreads();
+        }
         const int32_t *src = tr + t_from * K;
         auto put = [&](int row, int e) {
             if ((uint32_t)e < (uint32_t)N) atomicOr(&sets[at + row].w[e >> 5], 1u << (e & 31));
@@ -229,9 +231,9 @@ __global__ __launch_bounds__(LRU_CHUNK) void lru_walk_kernel(const int32_t *__re
         if (t0 >= T) break;
         const int back = t0 < halo ? (int)t0 : halo;
         const int first = halo - back;
-        if (c > c_lo) __syncthreads();     // the halo is there
-        else if (back > 0) stage(t0 - back, back, first, first);
-        stage(t0, (int)(T - t0 < chunk ? T - t0 : chunk), halo, first);
+        if (c > c_lo) __syncthreads();     // the halo is there, the other rows are empty
+        else if (back > 0) stage(t0 - back, back, first, first, true);
+        stage(t0, (int)(T - t0 < chunk ? T - t0 : chunk), halo, first, c == c_lo);
         const int64_t t = t0 + tid;
         Set<W> want{}, seen{};
         bool far = false;                  // the walk is through the staged steps and not done
@@ -298,9 +300,12 @@ __global__ __launch_bounds__(LRU_CHUNK) void lru_walk_kernel(const int32_t *__re
         lds_barrier();                     // the rows of this pass are no longer read (its results may still be on their way)
         const int last_far = far_pass;
         if (c + 1 < c_lo + chunks_per_wg) {
-            for (int i = tid; i < halo; i += chunk)
+            const int row = halo + tid;
+            if (row >= chunk) {
 #pragma unroll
-                for (int j = 0; j < LEVELS; ++j) sets[j * rows + i] = sets[j * rows + chunk + i];
+                for (int j = 0; j < LEVELS; ++j) sets[j * rows + row - chunk] = sets[j * rows + row];
+            }
+            sets[row] = Set<W>{};
         }
         if (last_far == (int)(c - c_lo) + 1) {
             look_back(t0 - back);
