@@ -38,7 +38,7 @@
 // 16 stretches of a trace in one workgroup (walk 140 us, bound by the instructions that 16 wavefronts issue on one
 // compute unit), 0.102 ms with 52 stretches of 80 steps over the chip: lists 37, walk 42 (one wavefront per SIMD, bound by
 // the latency of a step), check 14, weights 12 us.  With C = 32, a bonus of 4 and scores more alike from step to step (AR(1) of
-// 0.9) 23 of 51 stretches fail: 0.29 ms; mended by one wavefront, one stretch after the other, 1.1 ms, and 0.44 ms in one workgroup.
+// 0.9) about 23 of 51 stretches fail: 0.31 ms; mended by one wavefront, one stretch after the other, 1.1 ms, and 0.44 ms in one workgroup.
 #include <type_traits>
 
 #include "common.h"
